@@ -9,31 +9,33 @@
 // with Y_lm = lambda_lm(cos theta) e^{i m phi} and the orthonormal associated
 // Legendre functions lambda_lm.  The paper runs this half on host cores with an
 // SHT library while the GPU sums the real-space half; here both halves run on
-// the GPU, in five stream-ordered kernels per map, all in FP64:
+// the GPU, in stream-ordered kernels, all in FP64.  A ring and its N-S mirror
+// have the same length and the same first longitude, so every kernel works on
+// pairs: with e = x_ring + x_mirror and o = x_ring - x_mirror, even l + m sees
+// only e and odd l + m only o.
 //
-//  1. k_sht_dft_fwd   per ring: F_r(m) = sum_j x_j e^{-i m phi_j}, m <= lcut,
-//                     by Goertzel's second-order recurrence (one FMA and one
-//                     add per sample and frequency, no phase table); belt
-//                     rings whose length is a power of two (and exceeds
-//                     2 lcut) take k_sht_fft_fwd instead, a real FFT done as
-//                     one LDS-resident complex FFT of half the length;
-//  2. k_sht_leg_fwd   per (m, chunk of northern rings): lambda_lm by its
-//                     recurrence in l, times the even / odd N-S combinations
-//                     of F, reduced over the chunk's rings through LDS into
-//                     per-chunk partial a_lm;
-//  3. k_sht_mul       a_lm = Omega Khat_l sum over chunks (fixed order);
-//  4. k_sht_leg_bwd   per (m, northern ring): G_r(m) = sum_l a_lm lambda_lm,
-//                     split into even and odd parts for the ring and its
-//                     mirror;
-//  5. k_sht_dft_bwd   per ring: y_j = Re sum_m c_m G_r(m) e^{i m phi_j}
-//                     (c_0 = 1, c_m = 2) by Clenshaw's recurrence, one pass
-//                     for the pixel pair j, n - j; k_sht_fft_bwd is the
-//                     inverse real FFT for the rings of k_sht_fft_fwd.
+//  1. k_ring_fwd      per ring pair: the longitude sums of z = e + i o,
+//                     Z(m) = sum_j z_j e^{-i m phi_j} for m = -lcut .. lcut,
+//                     by FFTs of a quarter of the ring (k_sht_dft_fwd, direct
+//                     sums, for the rings the FFT does not reach);
+//  2. k_leg_fwd       per (m, chunk of ring pairs): Legendre functions by a
+//                     two-degree recurrence, times E(m) and O(m), reduced over
+//                     the rings into per-chunk partial sums;
+//  3. k_sht_mul       the sums over chunks turned into a_lm, multiplied by
+//                     Omega Khat_l, and turned into synthesis coefficients;
+//  4. k_leg_bwd       per (m, ring pair): the even and odd sums over l;
+//  5. k_ring_bwd      per ring pair: the pixels of both rings by inverse FFTs
+//                     of a quarter of the ring (k_sht_dft_bwd otherwise).
 //
 // lambda_mm underflows FP64 for large m near the poles, so the recurrence
-// carries a power-of-two scale: a value is lam * 2^(512 sc) with sc <= 0, and
+// carries a power-of-two scale: a value is stored * 2^(512 sc) with sc <= 0, and
 // terms are used only once sc reaches 0 (below that they are < 2^-330 times
 // the ring's other terms).  Results are deterministic: no atomics.
+//
+// At Nside 2048 and lcut 1500 the half takes 2.4 ms: longitude sums 0.56 + 0.45 ms
+// (one Goertzel or Clenshaw sum per frequency on cap rings and radix-2 FFTs on
+// belt rings took 2.06 + 2.13 ms), Legendre sums 0.87 + 0.75 ms (2.08 + 1.24 ms with
+// the one-degree recurrence and a reduction through LDS).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -59,404 +61,779 @@ struct ShtRing {
 };
 static_assert(sizeof(ShtRing) == 40, "ShtRing layout");
 
+// One ring pair of an FFT launch: northern ring, transform length k = n / 4,
+// log2 of the FFT length P, and the offset of the chirp spectrum in the plan's
+// table (0 for the direct transforms, P = k).
+struct ShtFftRing {
+    int ring;
+    int k;
+    int lg;
+    int chirp;
+};
+
 constexpr int kShtThreads = 256;
-constexpr int kShtChunk = 4096;     // samples of a ring staged per pass (FP64)
+constexpr int kShtChunk = 2048;     // samples of a ring pair staged per pass (FP64)
 constexpr int kShtMaxFreq = 8;      // frequencies per thread and pass in k_sht_dft_fwd
-constexpr int kLegBlock = 8;        // degrees l per LDS reduction in k_sht_leg_fwd
-constexpr int kLegCols = 2 * kLegBlock;            // re, im per degree
-constexpr int kLegSegs = kShtThreads / kLegCols;   // row segments of a column
-constexpr int kLegRings = 2;        // northern rings per lane in k_sht_leg_fwd
-constexpr int kLegChunk = kLegRings * kShtThreads;  // rings per k_sht_leg_fwd workgroup
 constexpr int kShtPairs = 2;        // pixel pairs per thread in k_sht_dft_bwd
-constexpr int kShtFftMaxM = 8192;   // complex FFT length in LDS (128 KB of FP64 pairs)
+constexpr double kShtDirectWork = 6e7;   // pixels x orders up to which rings are summed directly
+constexpr int kShtMaxK = 4096;      // longest quarter ring the FFTs take
+constexpr int kLegBlock = 4;        // recurrence steps (two degrees each) per reduction
+constexpr int kLegFwdRings = 8;     // ring pairs per lane of k_leg_fwd on large maps
+constexpr int kLegBwdRings = 4;     // and of k_leg_bwd
+constexpr int kLegFlush = 32;       // reductions kept in LDS between sums over the waves
 constexpr double kScaleUp = 0x1p128;     // rescale threshold of a scaled value
 constexpr double kScaleStep = 0x1p-512;  // one scale step
 
-// First entry of order m in the (l, m) layout: for each m, l = m .. L.
-__host__ __device__ inline long long alm_base(int m, int L)
+// Steps of order m: step k covers the degrees m + 2k and m + 2k + 1, padded to
+// whole blocks.
+__host__ __device__ inline int leg_steps(int m, int L)
 {
-    return (long long)m * (L + 1) - (long long)m * (m - 1) / 2;
+    return ((L - m) / 2 + kLegBlock) / kLegBlock * kLegBlock;
 }
 
-// lambda_mm of a ring in scaled form: returns the mantissa and sets sc.
-__device__ __forceinline__ double lambda_mm_scaled(double mnorm, int m, double log2s, int &sc)
+// Ring-pair rows of the longitude sums hold two arrays (m >= 0 and m <= 0, or
+// even and odd sums) of 4 lq complex values, the orders of one class m mod 4
+// contiguous: an FFT of a quarter ring yields one class, and its loads and
+// stores are then consecutive.
+__host__ __device__ inline int order_slot(int m, int lq) { return (m & 3) * lq + (m >> 2); }
+
+// The order m of workgroup b (gridDim.x is a multiple of 64).  Workgroups go
+// to the eight XCDs in turn; the eight orders that share the 128-byte lines of
+// every ring row run on one XCD one after the other, so that its L2 serves
+// (merges) their 16-byte reads (writes).
+__device__ __forceinline__ int leg_order(int b)
 {
-    const double e = mnorm + (double)m * log2s;   // log2 |lambda_mm|
-    if (e >= -384.0) {
-        sc = 0;
-        return exp2(e);
+    const int e = ((((b >> 3) >> 3) * 8 + (b & 7)) << 3) + ((b >> 3) & 7);
+    return 32 * (e >> 5) + 4 * (e & 7) + ((e >> 3) & 3);
+}
+static int leg_grid(int L) { return 64 * ((4 * (L / 32 + 1) + 7) / 8); }
+
+// Recurrence tables and coefficients are wave-uniform and read-only while a
+// kernel runs: through the constant address space they are scalar loads.
+#if defined(__HIP_DEVICE_COMPILE__)
+template <class T>
+using uptr = const __attribute__((address_space(4))) T *;
+#else
+template <class T>
+using uptr = const T *;
+#endif
+typedef double d2v __attribute__((ext_vector_type(2)));
+typedef double d4v __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ double2 cmul(double2 a, double2 b)
+{
+    return make_double2(fma(a.x, b.x, -a.y * b.y), fma(a.x, b.y, a.y * b.x));
+}
+__device__ __forceinline__ double2 conj2(double2 a) { return make_double2(a.x, -a.y); }
+__device__ __forceinline__ double2 add2(double2 a, double2 b)
+{
+    return make_double2(a.x + b.x, a.y + b.y);
+}
+__device__ __forceinline__ double2 sub2(double2 a, double2 b)
+{
+    return make_double2(a.x - b.x, a.y - b.y);
+}
+// Roots of unity of a ring: at(u) = e^{i pi u / n} for an integer |u| < 2^31.  The
+// angle in turns, reduced exactly, is the nearest of kRoots table entries plus
+// a remainder of at most half a step (pi / 64 radians), whose sine and cosine
+// are short Taylor sums (truncation below 1e-16): no division and no integer
+// modulo, a fifth of the instructions of sincospi.  The table stands in LDS.
+constexpr int kRoots = 64;
+struct RingRoots {
+    const double2 *roots;
+    double n2, inv;   // 2n, 1/(2n)
+    __device__ __forceinline__ RingRoots(const double2 *table, int n)
+        : roots(table), n2(2.0 * n), inv(1.0 / (2.0 * n)) {}
+    __device__ __forceinline__ double2 at(int u) const
+    {
+        const double ud = (double)u;
+        const double t = fma(-rint(ud * inv), n2, ud) * inv;
+        const double q = rint(t * kRoots);
+        const double x = fma(q, -1.0 / kRoots, t) * 6.283185307179586477;
+        const double x2 = x * x;
+        const double sn =
+            x * fma(x2, fma(x2, fma(x2, -1.0 / 5040.0, 1.0 / 120.0), -1.0 / 6.0), 1.0);
+        const double cs =
+            fma(x2, fma(x2, fma(x2, fma(x2, 1.0 / 40320.0, -1.0 / 720.0), 1.0 / 24.0), -0.5), 1.0);
+        return cmul(roots[(int)q & (kRoots - 1)], make_double2(cs, sn));
     }
-    sc = (int)floor((e + 384.0) / 512.0);          // mantissa in [2^-384, 2^128)
-    return exp2(e - 512.0 * sc);
+};
+// The table into LDS, by threads 0 .. kRoots - 1 (a barrier follows in the caller).
+__device__ __forceinline__ void load_roots(double2 *lds, const double2 *__restrict__ roots)
+{
+    if (threadIdx.x < kRoots) lds[threadIdx.x] = roots[threadIdx.x];
 }
 
-// One step of the l recurrence, lambda_l = A z lambda_{l-1} - B lambda_{l-2},
-// with a rescale while the value is scaled.  Returns the usable value (0 while
-// scaled).
-__device__ __forceinline__ double lambda_step(double A, double B, double z, double &l1, double &l2,
-                                              int &sc)
+// ----------------------------------------------------------- ring FFTs --
+// With z the n = 4k complex samples of a ring pair, the class q = 4a + c of
+// its transform is a length-k transform of the folded samples
+//     Z(4a + c) = sum_{j<k} e^{-2 pi i a j / k} e^{-2 pi i c j / n} sum_t (-i)^{ct} z_{j + tk},
+// done in LDS: on belt rings whose k is a power of two directly, else by
+// Bluestein's chirp transform, a circular convolution of length P = 2^lg >= 2k - 1
+// with b(t) = e^{+pi i t^2 / k}, whose spectrum (times 1/P) is a plan table.  The
+// FFT is radix 8, one butterfly of each pass per thread, decimation in frequency
+// from natural to digit-reversed order, and its inverse back, so no pass
+// reorders.  The first pass (radix 2 or 4 where lg is no multiple of 3) and the
+// last pass of the inverse act on entries t + i P/8, i < 8, of thread t: they
+// run in registers, on the samples as they are loaded and on the results as they
+// are stored.  Against one Goertzel sum per frequency, O(n lcut) per ring, the cap
+// rings cost O(P log P); what bounds the kernels is the latency of their loads
+// and barriers (half of the cycles; FP64 issue is the other half).  LDS entries
+// are padded by one in eight, so that the short-stride passes spread over the
+// banks.
+__host__ __device__ inline int fft_pad(int i) { return i + (i >> 3); }
+static size_t fft_lds_bytes(int lg) { return (size_t)(fft_pad(1 << lg) + kRoots) * sizeof(double2); }
+
+// Four-point transform in place, without twiddles; INV: the inverse.
+template <bool INV>
+__device__ __forceinline__ void dft4(double2 &a0, double2 &a1, double2 &a2, double2 &a3)
 {
-    const double v = fma(A * z, l1, -B * l2);
-    l2 = l1;
-    l1 = v;
-    if (sc < 0) {
-        if (fabs(l1) > kScaleUp) {
-            l1 *= kScaleStep;
-            l2 *= kScaleStep;
-            ++sc;
+    const double2 t0 = add2(a0, a2), t1 = sub2(a0, a2), t2 = add2(a1, a3), d = sub2(a1, a3);
+    const double2 t3 = INV ? make_double2(-d.y, d.x) : make_double2(d.y, -d.x);
+    a0 = add2(t0, t2);
+    a1 = add2(t1, t3);
+    a2 = sub2(t0, t2);
+    a3 = sub2(t1, t3);
+}
+
+// Eight-point transform: frequency f = s + 2r at entry 4s + r.  The inverse
+// takes that order and returns the natural one.
+__device__ __forceinline__ void dft8(double2 e[8])
+{
+    constexpr double h = 0.70710678118654752440;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const double2 d = sub2(e[r], e[r + 4]);
+        e[r] = add2(e[r], e[r + 4]);
+        // times e^{-2 pi i r / 8}
+        e[r + 4] = r == 0 ? d
+                 : r == 1 ? make_double2(h * (d.x + d.y), h * (d.y - d.x))
+                 : r == 2 ? make_double2(d.y, -d.x)
+                          : make_double2(h * (d.y - d.x), -h * (d.x + d.y));
+    }
+    dft4<false>(e[0], e[1], e[2], e[3]);
+    dft4<false>(e[4], e[5], e[6], e[7]);
+}
+__device__ __forceinline__ void idft8(double2 e[8])
+{
+    constexpr double h = 0.70710678118654752440;
+    dft4<true>(e[0], e[1], e[2], e[3]);
+    dft4<true>(e[4], e[5], e[6], e[7]);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const double2 b = e[r + 4];
+        // times e^{+2 pi i r / 8}
+        const double2 d = r == 0 ? b
+                        : r == 1 ? make_double2(h * (b.x - b.y), h * (b.x + b.y))
+                        : r == 2 ? make_double2(-b.y, b.x)
+                                 : make_double2(-h * (b.x + b.y), h * (b.x - b.y));
+        e[r + 4] = sub2(e[r], d);
+        e[r] = add2(e[r], d);
+    }
+}
+
+// Twiddles w^f of entry 4s + r, f = s + 2r, from w; INV: their conjugates.
+template <bool INV>
+__device__ __forceinline__ void twiddle8(double2 e[8], double2 w1)
+{
+    if (INV) w1 = conj2(w1);
+    const double2 w2 = cmul(w1, w1), w3 = cmul(w1, w2), w4 = cmul(w2, w2);
+    e[4] = cmul(e[4], w1);
+    e[1] = cmul(e[1], w2);
+    e[5] = cmul(e[5], w3);
+    e[2] = cmul(e[2], w4);
+    e[6] = cmul(e[6], cmul(w4, w1));
+    e[3] = cmul(e[3], cmul(w4, w2));
+    e[7] = cmul(e[7], cmul(w4, w3));
+}
+
+// The first forward pass, on entries t + i P/8: radix 8, 4 or 2 as lg mod 3 is
+// 0, 2 or 1.  tw[t] = e^{-2 pi i t / Pm}, t < Pm/4, Pm = 2^lgm the plan's longest FFT.
+__device__ __forceinline__ void fft_first(double2 e[8], const double2 *__restrict__ tw, int lg,
+                                          int lgm, int t)
+{
+    const int s8 = (1 << lg) >> 3;
+    if (lg % 3 == 0) {
+        dft8(e);
+        if (s8 > 1) twiddle8<false>(e, tw[t << (lgm - lg)]);
+    } else if (lg % 3 == 2) {   // stride P/4: entries i, i + 2, i + 4, i + 6
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const double2 w1 = tw[(t + i * s8) << (lgm - lg)];
+            const double2 w2 = cmul(w1, w1), w3 = cmul(w1, w2);
+            dft4<false>(e[i], e[i + 2], e[i + 4], e[i + 6]);
+            e[i + 2] = cmul(e[i + 2], w1);
+            e[i + 4] = cmul(e[i + 4], w2);
+            e[i + 6] = cmul(e[i + 6], w3);
         }
-        return sc == 0 ? l1 : 0.0;
+    } else {   // stride P/2: entries i, i + 4
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            // e^{-2 pi i j / P}, the second quarter of the table by -i
+            double2 w = tw[(t + (i & 1) * s8) << (lgm - lg)];
+            if (i >= 2) w = make_double2(w.y, -w.x);
+            const double2 d = sub2(e[i], e[i + 4]);
+            e[i] = add2(e[i], e[i + 4]);
+            e[i + 4] = cmul(d, w);
+        }
     }
-    return v;
 }
 
-// ------------------------------------------------------------ analysis --
+// Its inverse: the last pass of the inverse transform.
+__device__ __forceinline__ void fft_last_inverse(double2 e[8], const double2 *__restrict__ tw,
+                                                 int lg, int lgm, int t)
+{
+    const int s8 = (1 << lg) >> 3;
+    if (lg % 3 == 0) {
+        if (s8 > 1) twiddle8<true>(e, tw[t << (lgm - lg)]);
+        idft8(e);
+    } else if (lg % 3 == 2) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const double2 w1 = conj2(tw[(t + i * s8) << (lgm - lg)]);
+            const double2 w2 = cmul(w1, w1), w3 = cmul(w1, w2);
+            e[i + 2] = cmul(e[i + 2], w1);
+            e[i + 4] = cmul(e[i + 4], w2);
+            e[i + 6] = cmul(e[i + 6], w3);
+            dft4<true>(e[i], e[i + 2], e[i + 4], e[i + 6]);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            double2 w = tw[(t + (i & 1) * s8) << (lgm - lg)];
+            if (i >= 2) w = make_double2(w.y, -w.x);
+            const double2 d = cmul(e[i + 4], conj2(w));
+            e[i + 4] = sub2(e[i], d);
+            e[i] = add2(e[i], d);
+        }
+    }
+}
+
+// The transform of e (entries t + i P/8 of thread t; P = 2^lg >= 8), in LDS z.
+// BLUE: the convolution with the chirp spectrum bh, back in e; else the result
+// stands in z, frequency a at fft_place(a).  Every thread of the workgroup calls
+// it; threads from P/8 on only meet the barriers.  z is free on entry; the
+// caller puts a barrier before it reuses z.
+template <bool BLUE>
+__device__ __forceinline__ void ring_dft(double2 e[8], double2 *z, const double2 *__restrict__ tw,
+                                         const double2 *__restrict__ bh, int lg, int lgm)
+{
+    const int t = (int)threadIdx.x, s8 = (1 << lg) >> 3;
+    const bool on = t < s8;
+    // stride of the pass after the first one
+    int lh = (lg % 3 == 0 ? lg - 3 : lg / 3 * 3) - 3;
+    if (on) fft_first(e, tw, lg, lgm, t);
+    if (lh < 0) {   // P = 8: one thread, one pass
+        if (BLUE && on) {
+#pragma unroll
+            for (int r = 0; r < 8; ++r) e[r] = cmul(e[r], bh[r]);
+            idft8(e);
+        }
+        if (!BLUE && on)
+#pragma unroll
+            for (int r = 0; r < 8; ++r) z[fft_pad(r)] = e[r];
+        __syncthreads();
+        return;
+    }
+    if (on)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) z[fft_pad(t + i * s8)] = e[i];
+    for (; lh >= 0; lh -= 3) {
+        const int h = 1 << lh, j = t & (h - 1), i0 = ((t - j) << 3) + j;
+        double2 w = make_double2(1.0, 0.0);
+        double2 f[8];
+        if (on && lh > 0) w = tw[j << (lgm - lh - 3)];   // (ahead of the barrier)
+        if (BLUE && on && lh == 0)
+#pragma unroll
+            for (int r = 0; r < 8; ++r) f[r] = bh[8 * t + r];
+        __syncthreads();
+        if (on) {
+#pragma unroll
+            for (int r = 0; r < 8; ++r) e[r] = z[fft_pad(i0 + r * h)];
+            dft8(e);
+            if (lh > 0) {
+                twiddle8<false>(e, w);
+            } else if (BLUE) {
+                // the last forward butterflies, the product and the first
+                // inverse ones act on the same eight entries
+#pragma unroll
+                for (int r = 0; r < 8; ++r) e[r] = cmul(e[r], f[r]);
+                idft8(e);
+            }
+#pragma unroll
+            for (int r = 0; r < 8; ++r) z[fft_pad(i0 + r * h)] = e[r];
+        }
+    }
+    if (!BLUE) {
+        __syncthreads();
+        return;
+    }
+    for (lh = 3; lh + 3 <= lg - (lg % 3 == 0 ? 3 : lg % 3); lh += 3) {
+        const int h = 1 << lh, j = t & (h - 1), i0 = ((t - j) << 3) + j;
+        double2 w = make_double2(1.0, 0.0);
+        if (on) w = tw[j << (lgm - lh - 3)];
+        __syncthreads();
+        if (on) {
+#pragma unroll
+            for (int r = 0; r < 8; ++r) e[r] = z[fft_pad(i0 + r * h)];
+            twiddle8<true>(e, w);
+            idft8(e);
+#pragma unroll
+            for (int r = 0; r < 8; ++r) z[fft_pad(i0 + r * h)] = e[r];
+        }
+    }
+    __syncthreads();
+    if (on) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) e[i] = z[fft_pad(t + i * s8)];
+        fft_last_inverse(e, tw, lg, lgm, t);
+    }
+}
+
+// Place of frequency a in the output order of fft_dif.
+__device__ __forceinline__ int fft_place(int a, int lg)
+{
+    int pos = 0;
+    const int b = lg % 3;
+    lg -= b;
+    if (b) {
+        pos = (a & ((1 << b) - 1)) << lg;
+        a >>= b;
+    }
+    while (lg > 0) {
+        lg -= 3;
+        pos += (((a & 1) << 2) | ((a >> 1) & 3)) << lg;
+        a >>= 3;
+    }
+    return pos;
+}
+
+// Chirp spectra, one workgroup per length: b(t) = e^{pi i t^2 / k} for |t| < k,
+// transformed in the order of ring_dft, times 1/P.
+__global__ __launch_bounds__(1024) void k_chirp(const ShtFftRing *__restrict__ list,
+                                                const double2 *__restrict__ tw,
+                                                const double2 *__restrict__ roots,
+                                                double2 *__restrict__ chirp, int lgm)
+{
+    extern __shared__ double2 lds[];
+    double2 *z = lds + kRoots;
+    load_roots(lds, roots);
+    __syncthreads();
+    const ShtFftRing Q = list[blockIdx.x];
+    const RingRoots W(lds, 4 * Q.k);
+    const int P = 1 << Q.lg;
+    double2 e[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int j = (int)threadIdx.x + i * (P >> 3), t = min(j, P - j);
+        // t^2 / k = 4 t^2 / n
+        e[i] = t >= 0 && t < Q.k ? W.at(4 * t * t) : make_double2(0.0, 0.0);
+    }
+    ring_dft<false>(e, z, tw, nullptr, Q.lg, lgm);
+    const double inv = 1.0 / (double)P;
+    for (int i = threadIdx.x; i < P; i += 1024) {
+        const double2 v = z[fft_pad(i)];
+        chirp[Q.chirp + i] = make_double2(v.x * inv, v.y * inv);
+    }
+}
+
+// Workgroup (ring pair of the list, map), which takes the four classes in turn
+// from the pixels it holds in registers.
+template <int T, bool BLUE>
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(2)))
+void k_ring_fwd(const ShtRing *__restrict__ rings,
+                                                const ShtFftRing *__restrict__ list,
+                                                const double2 *__restrict__ tw,
+                                                const double2 *__restrict__ roots,
+                                                const double2 *__restrict__ chirp, int lgm,
+                                                const float *__restrict__ x, long long npix,
+                                                double2 *__restrict__ F, int L, int lq,
+                                                int nnorth)
+{
+    extern __shared__ double2 lds[];
+    double2 *z = lds + kRoots;
+    load_roots(lds, roots);
+    const ShtFftRing Q = list[blockIdx.x];
+    const ShtRing R = rings[Q.ring];
+    const bool equator = Q.ring == nnorth - 1;
+    const float *xa = x + (size_t)blockIdx.y * npix + R.first;
+    const float *xb = x + (size_t)blockIdx.y * npix + rings[2 * nnorth - 2 - Q.ring].first;
+    const int k = Q.k, s8 = (1 << Q.lg) >> 3, t0 = (int)threadIdx.x;
+    constexpr int JN = BLUE ? 4 : 8;   // entries t + i P/8 from 4 on are padding (k <= P/2)
+    float pa[JN][4], pb[JN][4];
+#pragma unroll
+    for (int i = 0; i < JN; ++i) {
+        const int j = t0 + i * s8;
+        const bool in = t0 < s8 && j < k;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            pa[i][t] = in ? xa[j + t * k] : 0.0f;
+            pb[i][t] = in && !equator ? xb[j + t * k] : 0.0f;
+        }
+    }
+    __syncthreads();   // the roots
+    const RingRoots W(lds, R.n);
+    double2 *row = F + ((size_t)blockIdx.y * nnorth + Q.ring) * 8 * lq;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        double2 e[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) e[i] = make_double2(0.0, 0.0);
+#pragma unroll
+        for (int i = 0; i < JN; ++i) {
+            const int j = t0 + i * s8;
+            double2 s[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const double p = (double)pa[i][t], q = (double)pb[i][t];
+                s[t] = make_double2(p + q, equator ? 0.0 : p - q);
+            }
+            double2 v;
+            if (c & 1) {
+                const double2 d0 = sub2(s[0], s[2]), d1 = sub2(s[1], s[3]);
+                v = c == 1 ? make_double2(d0.x + d1.y, d0.y - d1.x)
+                           : make_double2(d0.x - d1.y, d0.y + d1.x);
+            } else {
+                const double2 d0 = add2(s[0], s[2]), d1 = add2(s[1], s[3]);
+                v = c == 0 ? add2(d0, d1) : sub2(d0, d1);
+            }
+            if (BLUE || c) v = cmul(v, W.at(-(BLUE ? 4 * j * j : 0) - 2 * c * j));
+            if (t0 < s8 && j < k) e[i] = v;
+        }
+        ring_dft<BLUE>(e, z, tw, chirp + Q.chirp, Q.lg, lgm);
+        // Z(m) e^{-i m phi_0} of the orders m = q mod n, q = 4a + c, and
+        // Z(-m) e^{i m phi_0} of the orders m = -q mod n; phi_0 = two_o pi / n
+        if (BLUE && R.n <= L) {
+            // several orders per frequency: all threads share them
+            if (t0 < s8)
+#pragma unroll
+                for (int i = 0; i < JN; ++i) {
+                    const int a = t0 + i * s8;
+                    if (a < k) z[fft_pad(a)] = cmul(e[i], W.at(-4 * a * a));
+                }
+            __syncthreads();
+#pragma unroll
+            for (int side = 0; side < 2; ++side) {
+                for (int m = (side ? (4 - c) & 3 : c) + 4 * t0; m <= L; m += 4 * T) {
+                    const int r = m % R.n;
+                    const int a = ((side && r ? R.n - r : r) - c) >> 2;
+                    row[side * 4 * lq + order_slot(m, lq)] =
+                        cmul(z[fft_pad(a)], W.at((side ? m : -m) * R.two_o));
+                }
+            }
+            __syncthreads();
+            continue;
+        }
+#pragma unroll
+        for (int i = 0; i < JN; ++i) {
+            const int a = t0 + i * s8, q = 4 * a + c;
+            if (t0 >= s8 || a >= k || (q > L && R.n - q > L)) continue;
+            const double2 v = BLUE ? cmul(e[i], W.at(-4 * a * a)) : z[fft_pad(fft_place(a, Q.lg))];
+            const double2 w = R.two_o ? W.at(q) : make_double2(1.0, 0.0);
+#pragma unroll
+            for (int side = 0; side < 2; ++side) {
+                // m = q + (multiple of n): e^{-i m phi_0} = +-e^{-i q phi_0}; m = n - q: -e^{-i q phi_0}
+                bool neg = side && q && R.two_o;
+                for (int m = side && q ? R.n - q : q; m <= L; m += R.n) {
+                    const double2 y = cmul(v, conj2(w));
+                    row[side * 4 * lq + order_slot(m, lq)] = neg ? make_double2(-y.x, -y.y) : y;
+                    neg ^= R.two_o != 0;
+                }
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// The inverse: with He(m), Ho(m) the even and odd sums times e^{i m phi_0} and
+// c_m = 1 (m = 0) or 2, the pixels are the real parts of sum_m c_m H(m)
+// e^{2 pi i m j / n}, i.e. the inverse transform of the Hermitian spectrum
+//     S(q) = sum_{m = q mod n, m > 0} H(m) + sum_{m = -q mod n, m > 0} conj H(m)
+// (+ Re H(0) at q = 0), of S = S_e + i S_o for both rings at once.  One
+// workgroup per (ring pair, map) takes the classes 0, 2, 1, 3 in turn and keeps
+// their sums for its pixels in registers.
+template <int T, bool BLUE>
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(2)))
+void k_ring_bwd(const ShtRing *__restrict__ rings, const ShtFftRing *__restrict__ list,
+                const double2 *__restrict__ tw, const double2 *__restrict__ roots,
+                const double2 *__restrict__ chirp, int lgm, const double2 *__restrict__ G,
+                float *out, long long npix, int L, int lq, int nnorth, int accumulate)
+{
+    extern __shared__ double2 lds[];
+    double2 *z = lds + kRoots;
+    load_roots(lds, roots);
+    const ShtFftRing Q = list[blockIdx.x];
+    const ShtRing R = rings[Q.ring];
+    const double2 *ge = G + ((size_t)blockIdx.y * nnorth + Q.ring) * 8 * lq;
+    const double2 *go = ge + 4 * lq;
+    float *oa = out + (size_t)blockIdx.y * npix + R.first;
+    float *ob = out + (size_t)blockIdx.y * npix + rings[2 * nnorth - 2 - Q.ring].first;
+    const bool equator = Q.ring == nnorth - 1;
+    const int k = Q.k, s8 = (1 << Q.lg) >> 3, t0 = (int)threadIdx.x;
+    constexpr int JN = BLUE ? 4 : 8;
+    const RingRoots W(lds, R.n);
+    // short rings, on which several orders fall on one frequency, give each
+    // frequency 2^sl lanes and pass the spectrum through LDS
+    const bool folds = R.n <= 2 * L;
+    int sl = 0;
+    while (sl < 6 && (R.n << sl) < L && (k << (sl + 1)) <= T) ++sl;
+    const int sub = t0 & ((1 << sl) - 1);
+    const bool flip = R.two_o && sl == 0;   // an odd number of ring lengths per step
+    __syncthreads();   // the roots
+    // u_0, then u_0 + u_2; u_0 - u_2; u_1 (u_c the class's share of quarter 0)
+    double2 ya[JN], yb[JN], yc[JN];
+#pragma unroll
+    for (int ci = 0; ci < 4; ++ci) {
+        const int c = ((ci & 1) << 1) | (ci >> 1);   // 0, 2, 1, 3
+        // conj (S_e + i S_o) at q = 4a + c (the inverse transform is the conjugate
+        // of the transform of the conjugate), times the chirp
+        double2 e[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) e[i] = make_double2(0.0, 0.0);
+        if (folds) {
+            for (int a0 = 0; a0 < k; a0 += T >> sl) {
+                const int a = a0 + (t0 >> sl);
+                double2 se = make_double2(0.0, 0.0), so = se;
+                if (a < k) {
+                    const int q = 4 * a + c;
+                    if (q == 0 && sub == 0) {
+                        se.x = ge[0].x;
+                        so.x = go[0].x;
+                    }
+                    // this lane's share of the orders +-q mod n; phi_0 n / pi = two_o, so
+                    // the phase of m + n is (-1)^two_o times that of m
+#pragma unroll
+                    for (int side = 0; side < 2; ++side) {
+                        const int m1 = (side || !q ? R.n - q : q) + sub * R.n;
+                        if (m1 > L) continue;
+                        double2 w = W.at(m1 * R.two_o);
+                        for (int m = m1; m <= L; m += R.n << sl) {
+                            const double2 he = cmul(ge[order_slot(m, lq)], w);
+                            const double2 ho = cmul(go[order_slot(m, lq)], w);
+                            se = add2(se, side ? conj2(he) : he);
+                            so = add2(so, side ? conj2(ho) : ho);
+                            if (flip) w = make_double2(-w.x, -w.y);
+                        }
+                    }
+                }
+                double2 v = make_double2(se.x - so.y, -(se.y + so.x));
+                for (int d = 1; d < 1 << sl; d <<= 1) {
+                    v.x += __shfl_xor(v.x, d);
+                    v.y += __shfl_xor(v.y, d);
+                }
+                if (sub == 0 && a < k) z[fft_pad(a)] = BLUE ? cmul(v, W.at(-4 * a * a)) : v;
+            }
+            __syncthreads();
+            if (t0 < s8)
+#pragma unroll
+                for (int i = 0; i < JN; ++i)
+                    if (t0 + i * s8 < k) e[i] = z[fft_pad(t0 + i * s8)];
+            __syncthreads();
+        } else {
+            // one order at most per frequency: m = q, or m = n - q (conjugate)
+            double2 he[JN], ho[JN];
+#pragma unroll
+            for (int i = 0; i < JN; ++i) {
+                const int a = t0 + i * s8, q = 4 * a + c, m = q <= L ? q : R.n - q;
+                const bool in = t0 < s8 && a < k && m <= L;
+                const int sm = order_slot(in ? m : 0, lq);
+                he[i] = in ? ge[sm] : make_double2(0.0, 0.0);
+                ho[i] = in ? go[sm] : make_double2(0.0, 0.0);
+            }
+#pragma unroll
+            for (int i = 0; i < JN; ++i) {
+                const int a = t0 + i * s8, q = 4 * a + c;
+                const bool up = q <= L;
+                double2 se = he[i], so = ho[i];
+                if (R.two_o) {
+                    const double2 w = W.at(up ? q : R.n - q);
+                    se = cmul(se, w);
+                    so = cmul(so, w);
+                }
+                if (q == 0) se.y = so.y = 0.0;
+                if (!up) {
+                    se = conj2(se);
+                    so = conj2(so);
+                }
+                e[i] = make_double2(se.x - so.y, -(se.y + so.x));
+                if (BLUE) e[i] = cmul(e[i], W.at(-4 * a * a));
+            }
+        }
+        ring_dft<BLUE>(e, z, tw, chirp + Q.chirp, Q.lg, lgm);
+#pragma unroll
+        for (int i = 0; i < JN; ++i) {
+            const int j = t0 + i * s8;
+            if (t0 >= s8 || j >= k) continue;
+            double2 v = BLUE ? e[i] : z[fft_pad(fft_place(j, Q.lg))];
+            if (BLUE || c) v = cmul(v, W.at(-(BLUE ? 4 * j * j : 0) - 2 * c * j));
+            v.y = -v.y;
+            if (ci == 0) {
+                ya[i] = v;
+            } else if (ci == 1) {
+                yb[i] = sub2(ya[i], v);
+                ya[i] = add2(ya[i], v);
+            } else if (ci == 2) {
+                yc[i] = v;
+            } else {
+                // quarters t: sum over c of i^(ct) u_c
+                const double2 s = add2(yc[i], v), d = sub2(yc[i], v);
+                const double2 id = make_double2(-d.y, d.x);
+                const double2 y[4] = {add2(ya[i], s), add2(yb[i], id), sub2(ya[i], s),
+                                      sub2(yb[i], id)};
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const float va = (float)(y[t].x + y[t].y), vb = (float)(y[t].x - y[t].y);
+                    const int p = j + t * k;
+                    oa[p] = accumulate ? oa[p] + va : va;
+                    if (!equator) ob[p] = accumulate ? ob[p] + vb : vb;
+                }
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// --------------------------------------------------- direct ring sums --
+// For quarter rings longer than kShtMaxK that are not a power of two (and all
+// rings under ARKCOS_SHT_NO_FFT).
 // Goertzel: s_j = x_j + 2 cos(w) s_{j-1} - s_{j-2}; after n samples
-// sum_j x_j e^{-i w j} = e^{i w} s_{n-1} - s_{n-2}.  Two samples per step
-// update (s1, s2) in place: s2 <- c s1 + x_j - s2, s1 <- c s2 + x_{j+1} - s1.
-// Ring lengths are multiples of 4, so every staged count is even.  One launch
-// covers frequencies m = m0 + thread + k kShtThreads, k < K.
+// sum_j x_j e^{-i w j} = e^{i w} s_{n-1} - s_{n-2}, for the samples e and o of a
+// ring pair.  Two samples per step update (s1, s2) in place: s2 <- c s1 + x_j -
+// s2, s1 <- c s2 + x_{j+1} - s1.  Ring lengths are multiples of 4, so every
+// staged count is even.  One launch covers frequencies m = m0 + thread + k
+// kShtThreads, k < K.
 template <int K>
 __global__ __launch_bounds__(kShtThreads) void k_sht_dft_fwd(const ShtRing *__restrict__ rings,
                                                              const int *__restrict__ ring_list,
+                                                             const double2 *__restrict__ roots,
                                                              const float *__restrict__ x,
+                                                             long long npix,
                                                              double2 *__restrict__ F, int m0,
-                                                             int L, int nrings)
+                                                             int L, int lq, int nnorth)
 {
-    __shared__ double2 sx[kShtChunk / 2];
+    __shared__ double2 sx[kShtChunk];   // (e, o) of a sample
+    __shared__ double2 rt[kRoots];
+    load_roots(rt, roots);
     const int r = ring_list[blockIdx.x];
     const ShtRing R = rings[r];
-    const float *xr = x + R.first;
-    double c[K], s1[K], s2[K];
+    const bool equator = r == nnorth - 1;
+    const float *xa = x + (size_t)blockIdx.y * npix + R.first;
+    const float *xb = x + (size_t)blockIdx.y * npix + rings[2 * nnorth - 2 - r].first;
+    double c[K], s1[K], s2[K], t1[K], t2[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const int m = m0 + threadIdx.x + k * kShtThreads;
         c[k] = 2.0 * cospi(2.0 * (double)(m % R.n) / (double)R.n);
-        s1[k] = 0.0;
-        s2[k] = 0.0;
+        s1[k] = s2[k] = t1[k] = t2[k] = 0.0;
     }
     for (int j0 = 0; j0 < R.n; j0 += kShtChunk) {
-        const int half = min(kShtChunk, R.n - j0) / 2;
+        const int cnt = min(kShtChunk, R.n - j0);
         __syncthreads();
-        for (int j = threadIdx.x; j < half; j += kShtThreads) {
-            const float2 v = *reinterpret_cast<const float2 *>(xr + j0 + 2 * j);
-            sx[j] = make_double2((double)v.x, (double)v.y);
+        for (int j = threadIdx.x; j < cnt; j += kShtThreads) {
+            const double p = (double)xa[j0 + j];
+            const double q = equator ? 0.0 : (double)xb[j0 + j];
+            sx[j] = make_double2(p + q, equator ? 0.0 : p - q);
         }
         __syncthreads();
-        for (int j = 0; j < half; ++j) {
-            const double2 v = sx[j];
+        for (int j = 0; j < cnt; j += 2) {
+            const double2 v = sx[j], w = sx[j + 1];
 #pragma unroll
             for (int k = 0; k < K; ++k) {
                 s2[k] = fma(c[k], s1[k], v.x - s2[k]);
-                s1[k] = fma(c[k], s2[k], v.y - s1[k]);
+                s1[k] = fma(c[k], s2[k], w.x - s1[k]);
+                t2[k] = fma(c[k], t1[k], v.y - t2[k]);
+                t1[k] = fma(c[k], t2[k], w.y - t1[k]);
             }
         }
     }
+    double2 *row = F + ((size_t)blockIdx.y * nnorth + r) * 8 * lq;
+    const RingRoots W(rt, R.n);
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const int m = m0 + threadIdx.x + k * kShtThreads;
         if (m > L) continue;
         double sw, cw;
         sincospi(2.0 * (double)(m % R.n) / (double)R.n, &sw, &cw);
-        const double xre = cw * s1[k] - s2[k];
-        const double xim = sw * s1[k];
-        // times e^{-i m phi_0}, phi_0 = two_o pi / n
-        const long long q = ((long long)m * R.two_o) % (2LL * R.n);
-        double sp, cp;
-        sincospi((double)q / (double)R.n, &sp, &cp);
-        F[(size_t)m * nrings + r] = make_double2(cp * xre + sp * xim, cp * xim - sp * xre);
-    }
-}
-
-// Partial a_lm of one chunk of northern rings (the equator last): ring r and
-// its mirror 4N-2-r (0-based) have lambda_lm(pi - theta) = (-1)^(l+m)
-// lambda_lm(theta), so they enter through E = F_r + F_mirror (l + m even) and
-// O = F_r - F_mirror (l + m odd); the equator enters once, through E.
-__global__ __launch_bounds__(kShtThreads) void k_sht_leg_fwd(
-    const ShtRing *__restrict__ rings, const double2 *__restrict__ F,
-    const double2 *__restrict__ rec, const double *__restrict__ mnorm,
-    const int *__restrict__ ring_lo, double *__restrict__ part, int L, int nrings, int nnorth,
-    long long nalm)
-{
-    __shared__ double red[kLegCols][kShtThreads + 1];
-    __shared__ double red2[kLegSegs][kLegCols];
-    const int m = blockIdx.y;
-    const int chunk = blockIdx.x;
-    // chunks whose rings all lie below ring_lo[m] contribute nothing (and
-    // k_sht_mul skips their partials)
-    if ((chunk + 1) * kLegChunk <= ring_lo[m]) return;
-    // kLegRings rings per lane: independent recurrences, summed in registers
-    // before the block reduction
-    double2 E[kLegRings], O[kLegRings];
-    double z[kLegRings], l1[kLegRings], l2[kLegRings];
-    int sc[kLegRings];
-#pragma unroll
-    for (int q = 0; q < kLegRings; ++q) {
-        const int i = chunk * kLegChunk + q * kShtThreads + threadIdx.x;
-        const bool act = i < nnorth;
-        const int ii = act ? i : 0;
-        const ShtRing R = rings[ii];
-        const int mir = nrings - 1 - ii;
-        E[q] = make_double2(0.0, 0.0);
-        O[q] = E[q];
-        if (act) {
-            const double2 a = F[(size_t)m * nrings + ii];
-            if (mir == ii) {
-                E[q] = a;
-            } else {
-                const double2 b = F[(size_t)m * nrings + mir];
-                E[q] = make_double2(a.x + b.x, a.y + b.y);
-                O[q] = make_double2(a.x - b.x, a.y - b.y);
-            }
-        }
-        l1[q] = lambda_mm_scaled(mnorm[m], m, R.log2s, sc[q]);
-        l2[q] = 0.0;
-        z[q] = R.z;
-    }
-    const long long base = alm_base(m, L);
-    for (int l0 = m; l0 <= L; l0 += kLegBlock) {
-        double pr[kLegBlock], pim[kLegBlock];
-#pragma unroll
-        for (int k = 0; k < kLegBlock; ++k) {
-            pr[k] = 0.0;
-            pim[k] = 0.0;
-        }
-        bool scaled = false;
-#pragma unroll
-        for (int q = 0; q < kLegRings; ++q) scaled |= sc[q] < 0;
-        if (l0 > m && l0 + kLegBlock - 1 <= L && !__any(scaled)) {
-            // a full block with every lane of the wave unscaled: plain steps,
-            // the block's coefficients loaded together
-            double2 ab[kLegBlock];
-#pragma unroll
-            for (int k = 0; k < kLegBlock; ++k) ab[k] = rec[base + (l0 + k - m)];
-#pragma unroll
-            for (int k = 0; k < kLegBlock; ++k) {
-                const bool odd = ((l0 + k + m) & 1) != 0;
-#pragma unroll
-                for (int q = 0; q < kLegRings; ++q) {
-                    const double v = fma(ab[k].x * z[q], l1[q], -ab[k].y * l2[q]);
-                    l2[q] = l1[q];
-                    l1[q] = v;
-                    const double2 src = odd ? O[q] : E[q];
-                    pr[k] = fma(v, src.x, pr[k]);
-                    pim[k] = fma(v, src.y, pim[k]);
-                }
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < kLegBlock; ++k) {
-                const int l = l0 + k;
-                if (l > L) continue;
-                const bool odd = ((l + m) & 1) != 0;
-#pragma unroll
-                for (int q = 0; q < kLegRings; ++q) {
-                    double v;
-                    if (l == m) {
-                        v = sc[q] == 0 ? l1[q] : 0.0;
-                    } else {
-                        const double2 ab = rec[base + (l - m)];
-                        v = lambda_step(ab.x, ab.y, z[q], l1[q], l2[q], sc[q]);
-                    }
-                    const double2 src = odd ? O[q] : E[q];
-                    pr[k] = fma(v, src.x, pr[k]);
-                    pim[k] = fma(v, src.y, pim[k]);
-                }
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < kLegBlock; ++k) {
-            red[2 * k][threadIdx.x] = pr[k];
-            red[2 * k + 1][threadIdx.x] = pim[k];
-        }
-        __syncthreads();
-        {
-            // column col (degree l0 + col/2, re or im) summed over one segment
-            // of kShtThreads / kLegSegs lanes
-            constexpr int rows = kShtThreads / kLegSegs;
-            const int col = threadIdx.x % kLegCols;
-            const int seg = threadIdx.x / kLegCols;
-            double t = 0.0;
-            for (int q = 0; q < rows; ++q) t += red[col][seg * rows + q];
-            red2[seg][col] = t;
-        }
-        __syncthreads();
-        if (threadIdx.x < kLegCols) {
-            double t = 0.0;
-            for (int sgm = 0; sgm < kLegSegs; ++sgm) t += red2[sgm][threadIdx.x];
-            const int l = l0 + (threadIdx.x >> 1);
-            if (l <= L)
-                part[2 * ((size_t)chunk * nalm + base + (l - m)) + (threadIdx.x & 1)] = t;
-        }
-    }
-}
-
-// a_lm = Omega Khat_l sum over the ring chunks, in chunk order.
-__global__ __launch_bounds__(kShtThreads) void k_sht_mul(const double2 *__restrict__ part,
-                                                         const double *__restrict__ kscale,
-                                                         const int *__restrict__ ring_lo,
-                                                         double2 *__restrict__ alm, int L,
-                                                         int nchunk, long long nalm)
-{
-    const int m = blockIdx.y;
-    const int l = m + blockIdx.x * kShtThreads + threadIdx.x;
-    if (l > L) return;
-    const long long idx = alm_base(m, L) + (l - m);
-    double2 s = make_double2(0.0, 0.0);
-    for (int c = ring_lo[m] / kLegChunk; c < nchunk; ++c) {
-        const double2 p = part[(size_t)c * nalm + idx];
-        s.x += p.x;
-        s.y += p.y;
-    }
-    alm[idx] = make_double2(kscale[l] * s.x, kscale[l] * s.y);
-}
-
-// ----------------------------------------------------------- synthesis --
-// G_r(m) = sum_l a_lm lambda_lm(theta_r) for northern rings and their mirrors,
-// kLegRings rings per lane (independent recurrences sharing the loads of the
-// coefficients), in blocks of kLegBlock degrees: plain steps once every lane
-// of the wave is unscaled, steps with the rescale check before that.
-__global__ __launch_bounds__(kShtThreads) void k_sht_leg_bwd(
-    const ShtRing *__restrict__ rings, const double2 *__restrict__ alm,
-    const double2 *__restrict__ rec, const double *__restrict__ mnorm,
-    const int *__restrict__ ring_lo, double2 *__restrict__ G, int L, int nrings, int nnorth)
-{
-    const int m = blockIdx.y;
-    const int i0 = blockIdx.x * kLegChunk + threadIdx.x;
-    if ((blockIdx.x + 1) * kLegChunk <= ring_lo[m]) {   // every term negligible
-#pragma unroll
-        for (int q = 0; q < kLegRings; ++q) {
-            const int i = i0 + q * kShtThreads;
-            if (i < nnorth) {
-                G[(size_t)m * nrings + i] = make_double2(0.0, 0.0);
-                G[(size_t)m * nrings + (nrings - 1 - i)] = make_double2(0.0, 0.0);
-            }
-        }
-        return;
-    }
-    double z[kLegRings], l1[kLegRings], l2[kLegRings];
-    int sc[kLegRings];
-    double2 ae[kLegRings], ao[kLegRings];   // l + m even, odd
-    const long long base = alm_base(m, L);
-    const double2 a_m = alm[base];
-#pragma unroll
-    for (int q = 0; q < kLegRings; ++q) {
-        const int i = min(i0 + q * kShtThreads, nnorth - 1);
-        const ShtRing R = rings[i];
-        l1[q] = lambda_mm_scaled(mnorm[m], m, R.log2s, sc[q]);
-        l2[q] = 0.0;
-        z[q] = R.z;
-        const double v = sc[q] == 0 ? l1[q] : 0.0;
-        ae[q] = make_double2(v * a_m.x, v * a_m.y);
-        ao[q] = make_double2(0.0, 0.0);
-    }
-    // degrees m+1 .. L in blocks of kLegBlock: plain steps when every lane of
-    // the wave is unscaled, steps with the rescale check otherwise
-    for (int l0 = m + 1; l0 <= L; l0 += kLegBlock) {
-        bool scaled = false;
-#pragma unroll
-        for (int q = 0; q < kLegRings; ++q) scaled |= sc[q] < 0;
-        if (l0 + kLegBlock - 1 <= L && !__any(scaled)) {
-            double2 rb[kLegBlock], ab[kLegBlock];
-#pragma unroll
-            for (int k = 0; k < kLegBlock; ++k) {
-                rb[k] = rec[base + (l0 + k - m)];
-                ab[k] = alm[base + (l0 + k - m)];
-            }
-#pragma unroll
-            for (int k = 0; k < kLegBlock; ++k) {
-                const bool odd = ((l0 + k - m) & 1) != 0;
-#pragma unroll
-                for (int q = 0; q < kLegRings; ++q) {
-                    const double v = fma(rb[k].x * z[q], l1[q], -rb[k].y * l2[q]);
-                    l2[q] = l1[q];
-                    l1[q] = v;
-                    double2 &t = odd ? ao[q] : ae[q];
-                    t.x = fma(v, ab[k].x, t.x);
-                    t.y = fma(v, ab[k].y, t.y);
-                }
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < kLegBlock; ++k) {
-                const int l = l0 + k;
-                if (l > L) continue;
-                const double2 r1 = rec[base + (l - m)];
-                const double2 a = alm[base + (l - m)];
-                const bool odd = ((l - m) & 1) != 0;
-#pragma unroll
-                for (int q = 0; q < kLegRings; ++q) {
-                    const double v = lambda_step(r1.x, r1.y, z[q], l1[q], l2[q], sc[q]);
-                    double2 &t = odd ? ao[q] : ae[q];
-                    t.x = fma(v, a.x, t.x);
-                    t.y = fma(v, a.y, t.y);
-                }
-            }
-        }
-    }
-#pragma unroll
-    for (int q = 0; q < kLegRings; ++q) {
-        const int i = i0 + q * kShtThreads;
-        if (i >= nnorth) continue;
-        const int mir = nrings - 1 - i;
-        G[(size_t)m * nrings + i] = make_double2(ae[q].x + ao[q].x, ae[q].y + ao[q].y);
-        if (mir != i)
-            G[(size_t)m * nrings + mir] = make_double2(ae[q].x - ao[q].x, ae[q].y - ao[q].y);
+        const double2 ph = W.at(-m * R.two_o);   // e^{-i m phi_0}
+        const double2 E = cmul(make_double2(cw * s1[k] - s2[k], sw * s1[k]), ph);
+        const double2 O = cmul(make_double2(cw * t1[k] - t2[k], sw * t1[k]), ph);
+        // Z(m) = E + i O, Z(-m) = conj E + i conj O
+        row[order_slot(m, lq)] = make_double2(E.x - O.y, E.y + O.x);
+        row[4 * lq + order_slot(m, lq)] = make_double2(E.x + O.y, -E.y + O.x);
     }
 }
 
 // y_j = Re sum_m H_m e^{i m a_j}, a_j = 2 pi j / n, H_m = c_m G_r(m) e^{i m phi_0}:
 // with C = sum Re H_m cos(m a) and S = sum Im H_m sin(m a) (Clenshaw, shared
-// coefficient 2 cos a), y_j = C - S and y_{n-j} = C + S.
+// coefficient 2 cos a), y_j = C - S and y_{n-j} = C + S, for the even and odd
+// sums of a ring pair.
 __global__ __launch_bounds__(kShtThreads) void k_sht_dft_bwd(const ShtRing *__restrict__ rings,
                                                              const int *__restrict__ ring_list,
+                                                             const double2 *__restrict__ roots,
                                                              const double2 *__restrict__ G,
-                                                             float *__restrict__ out, int L,
-                                                             int nrings, int accumulate)
+                                                             float *__restrict__ out,
+                                                             long long npix, int L, int lq,
+                                                             int nnorth, int accumulate)
 {
-    extern __shared__ double2 H[];
+    extern __shared__ double2 H[];   // He, then Ho
     const int r = ring_list[blockIdx.x];
     const ShtRing R = rings[r];
+    const double2 *row = G + ((size_t)blockIdx.y * nnorth + r) * 8 * lq;
+    double2 *Ho = H + L + 1;
+    __shared__ double2 rt[kRoots];
+    load_roots(rt, roots);
+    __syncthreads();
+    const RingRoots W(rt, R.n);
     for (int m = threadIdx.x; m <= L; m += kShtThreads) {
-        const double2 g = G[(size_t)m * nrings + r];
-        const long long q = ((long long)m * R.two_o) % (2LL * R.n);
-        double sp, cp;
-        sincospi((double)q / (double)R.n, &sp, &cp);
+        const double2 w = W.at(m * R.two_o);
         const double c = m == 0 ? 1.0 : 2.0;
-        H[m] = make_double2(c * (g.x * cp - g.y * sp), c * (g.x * sp + g.y * cp));
+        const double2 e = cmul(row[order_slot(m, lq)], w);
+        const double2 o = cmul(row[4 * lq + order_slot(m, lq)], w);
+        H[m] = make_double2(c * e.x, c * e.y);
+        Ho[m] = make_double2(c * o.x, c * o.y);
     }
     __syncthreads();
-    float *o = out + R.first;
+    float *oa = out + (size_t)blockIdx.y * npix + R.first;
+    float *ob = out + (size_t)blockIdx.y * npix + rings[2 * nnorth - 2 - r].first;
+    const bool equator = r == nnorth - 1;
     const int npairs = R.n / 2 + 1;     // j = 0 .. n/2
     for (int j0 = threadIdx.x * kShtPairs; j0 < npairs; j0 += kShtThreads * kShtPairs) {
-        double cc[kShtPairs], b1[kShtPairs], b2[kShtPairs], d1[kShtPairs], d2[kShtPairs];
+        double cc[kShtPairs], b1[2][kShtPairs], b2[2][kShtPairs], d1[2][kShtPairs],
+            d2[2][kShtPairs];
 #pragma unroll
         for (int k = 0; k < kShtPairs; ++k) {
             cc[k] = 2.0 * cospi(2.0 * (double)(j0 + k) / (double)R.n);
-            b1[k] = b2[k] = d1[k] = d2[k] = 0.0;
+#pragma unroll
+            for (int p = 0; p < 2; ++p) b1[p][k] = b2[p][k] = d1[p][k] = d2[p][k] = 0.0;
         }
         // b_m = h_m + 2 cos(a) b_{m+1} - b_{m+2} from m = L down, two steps
         // at a time in place (b1 holds the newest term); an odd count starts
         // from b_L = h_L
         int m = L;
         if (((L + 1) & 1) != 0) {
-            const double2 h = H[L];
 #pragma unroll
-            for (int k = 0; k < kShtPairs; ++k) {
-                b1[k] = h.x;
-                d1[k] = h.y;
+            for (int p = 0; p < 2; ++p) {
+                const double2 h = (p ? Ho : H)[L];
+#pragma unroll
+                for (int k = 0; k < kShtPairs; ++k) {
+                    b1[p][k] = h.x;
+                    d1[p][k] = h.y;
+                }
             }
             m = L - 1;
         }
         for (; m > 0; m -= 2) {
-            const double2 ha = H[m];
-            const double2 hb = H[m - 1];
 #pragma unroll
-            for (int k = 0; k < kShtPairs; ++k) {
-                b2[k] = fma(cc[k], b1[k], ha.x - b2[k]);
-                b1[k] = fma(cc[k], b2[k], hb.x - b1[k]);
-                d2[k] = fma(cc[k], d1[k], ha.y - d2[k]);
-                d1[k] = fma(cc[k], d2[k], hb.y - d1[k]);
+            for (int p = 0; p < 2; ++p) {
+                const double2 ha = (p ? Ho : H)[m];
+                const double2 hb = (p ? Ho : H)[m - 1];
+#pragma unroll
+                for (int k = 0; k < kShtPairs; ++k) {
+                    b2[p][k] = fma(cc[k], b1[p][k], ha.x - b2[p][k]);
+                    b1[p][k] = fma(cc[k], b2[p][k], hb.x - b1[p][k]);
+                    d2[p][k] = fma(cc[k], d1[p][k], ha.y - d2[p][k]);
+                    d1[p][k] = fma(cc[k], d2[p][k], hb.y - d1[p][k]);
+                }
             }
         }
 #pragma unroll
@@ -465,158 +842,420 @@ __global__ __launch_bounds__(kShtThreads) void k_sht_dft_bwd(const ShtRing *__re
             if (j >= npairs) continue;
             double sa, ca;
             sincospi(2.0 * (double)j / (double)R.n, &sa, &ca);
-            const double C = b1[k] - b2[k] * ca;     // b_0 - b_1 cos a
-            const double S = d2[k] * sa;             // d_1 sin a
-            const float y0 = (float)(C - S);
-            o[j] = accumulate ? o[j] + y0 : y0;
+            double C[2], S[2];
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                C[p] = b1[p][k] - b2[p][k] * ca;     // b_0 - b_1 cos a
+                S[p] = d2[p][k] * sa;                // d_1 sin a
+            }
             const int jm = j == 0 ? 0 : R.n - j;
-            if (jm != j) {
-                const float y1 = (float)(C + S);
-                o[jm] = accumulate ? o[jm] + y1 : y1;
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                if (t && jm == j) break;
+                const int at = t ? jm : j;
+                const double ye = t ? C[0] + S[0] : C[0] - S[0];
+                const double yo = t ? C[1] + S[1] : C[1] - S[1];
+                const float va = (float)(ye + yo), vb = (float)(ye - yo);
+                oa[at] = accumulate ? oa[at] + va : va;
+                if (!equator) ob[at] = accumulate ? ob[at] + vb : vb;
             }
         }
     }
 }
 
-// ----------------------------------------------------------- belt FFTs --
-// A ring of n = 2M pixels, M a power of two.  The real transform
-// X_m = sum_j x_j e^{-2 pi i m j / n} comes from the complex FFT Z of
-// z_k = x_{2k} + i x_{2k+1} (length M):
-//     X_m = (Z_m + conj Z_{M-m}) / 2 - i e^{-i pi m / M} (Z_m - conj Z_{M-m}) / 2,
-// and the inverse from Z_q = (S_q + conj S_{M-q}) + i e^{i pi q / M} (S_q - conj S_{M-q})
-// for a Hermitian spectrum S (S_{n-m} = conj S_m, zero above lcut < M), whose
-// inverse complex FFT gives z_k = y_{2k} + i y_{2k+1}.  The FFT is radix 2,
-// decimation in time, in place in LDS after a bit-reversed load; tw[t] =
-// e^{-2 pi i t / M} for t < M/2 and hw[m] = e^{-i pi m / M} for m <= M are
-// plan tables.
-
-__device__ __forceinline__ double2 cmul(double2 a, double2 b)
+// ----------------------------------------------------------- Legendre --
+// With c_l = sqrt((l^2 - m^2) / (4 l^2 - 1)), z lambda_l = c_{l+1} lambda_{l+1} +
+// c_l lambda_{l-1}.  The functions p_k = lambda_{m+2k+1} / z are even in z, and
+// both parities follow from them locally (Ishioka 2018):
+//     lambda_{m+2k+1} = z p_k,   lambda_{m+2k} = c_{m+2k+1} p_k + c_{m+2k} p_{k-1}.
+// Applying z twice gives a recurrence in steps of two degrees; scaled by
+// constants nu_k, p_k = nu_k pi_k, it reads pi_{k+1} = (A_k z^2 + B_k) pi_k - pi_{k-1}.
+// So two degrees of a ring pair cost two FMAs of recurrence and four of sums,
+// against three and two per degree of the one-degree recurrence.
+//
+// lambda_mm of a ring times sqrt(2m + 3) (= p_0) in scaled form: returns the
+// mantissa and sets sc.  pnorm[m] is log2 of the normalisation.
+__device__ __forceinline__ double leg_start(double pnorm, int m, double log2s, int &sc)
 {
-    return make_double2(fma(a.x, b.x, -a.y * b.y), fma(a.x, b.y, a.y * b.x));
+    const double e = pnorm + (double)m * log2s;   // log2 p_0
+    if (e >= -384.0) {
+        sc = 0;
+        return exp2(e);
+    }
+    sc = (int)floor((e + 384.0) / 512.0);          // mantissa in [2^-384, 2^128)
+    return exp2(e - 512.0 * sc);
 }
 
-__device__ __forceinline__ double2 conj2(double2 a) { return make_double2(a.x, -a.y); }
-
-// In-place FFT of z (bit-reversed input order), sign -1 (forward) or +1.
-__device__ __forceinline__ void fft_lds(double2 *z, const double2 *__restrict__ tw, int M,
-                                        int logM, bool inverse)
+// Lane exchanges of the reduction below.
+__device__ __forceinline__ double half_swap_add(double a, double b, bool rows16)
 {
-    for (int st = 0; st < logM; ++st) {
-        const int h = 1 << st;
-        for (int b = threadIdx.x; b < (M >> 1); b += kShtThreads) {
-            const int j = b & (h - 1);
-            const int k = ((b >> st) << (st + 1)) + j;
-            double2 w = tw[j << (logM - 1 - st)];
-            if (inverse) w.y = -w.y;
-            const double2 a = z[k];
-            const double2 t = cmul(w, z[k + h]);
-            z[k] = make_double2(a.x + t.x, a.y + t.y);
-            z[k + h] = make_double2(a.x - t.x, a.y - t.y);
+    // 32-lane (16-lane) halves: the lower lanes return the sum of a over both
+    // halves, the upper ones that of b
+    const unsigned long long ua = __double_as_longlong(a), ub = __double_as_longlong(b);
+    typedef unsigned v2u __attribute__((ext_vector_type(2)));
+    v2u lo, hi;
+    if (rows16) {
+        lo = __builtin_amdgcn_permlane16_swap((unsigned)ua, (unsigned)ub, false, false);
+        hi = __builtin_amdgcn_permlane16_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false,
+                                              false);
+    } else {
+        lo = __builtin_amdgcn_permlane32_swap((unsigned)ua, (unsigned)ub, false, false);
+        hi = __builtin_amdgcn_permlane32_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false,
+                                              false);
+    }
+    return __longlong_as_double(((unsigned long long)hi.x << 32) | lo.x) +
+           __longlong_as_double(((unsigned long long)hi.y << 32) | lo.y);
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v)
+{
+    const unsigned long long u = __double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)u, CTRL, 0xF, 0xF, true);
+    const unsigned hi =
+        (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)(u >> 32), CTRL, 0xF, 0xF, true);
+    return __longlong_as_double(((unsigned long long)hi << 32) | lo);
+}
+// Sums of sixteen values over the wave: lane l returns that of v[l >> 2].
+// Each step halves the values a lane carries, so the reduction takes 17 adds
+// instead of 96 and no LDS.
+__device__ __forceinline__ double reduce16(double v[16])
+{
+    const int lane = (int)threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = half_swap_add(v[i], v[i + 8], false);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = half_swap_add(v[i], v[i + 4], true);
+    const bool b3 = (lane & 8) != 0, b2 = (lane & 4) != 0;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+        v[i] = (b3 ? v[i + 2] : v[i]) + dpp_move<0x128>(b3 ? v[i] : v[i + 2]);   // row_ror:8
+    double s = (b2 ? v[1] : v[0]) + dpp_move<0x141>(b2 ? v[0] : v[1]);           // half mirror
+    s += dpp_move<0x4E>(s);
+    s += dpp_move<0xB1>(s);
+    return s;
+}
+
+// Workgroup (order m, chunk of ring pairs, map): the sums S_k = sum pi_k E and
+// T_k = sum pi_k z O over the chunk's ring pairs, with E = (Z(m) + conj Z(-m)) / 2
+// and O = (Z(m) - conj Z(-m)) / 2i.  Chunks count from ring_lo[m], below which
+// no ring contributes; a wave takes 64 R consecutive ring pairs, R per lane.
+// What bounds it is the FP64 rate: six FMAs per ring pair and two degrees, about
+// 5.5 cycles each at 2.4 GHz nominal (measured, all SIMDs busy: the clock
+// falls), 0.43 ms at Nside 2048 and lcut 1500 of the 0.87 ms measured; the
+// reduction over the wave adds half of that at four ring pairs per lane, a
+// quarter at eight.  Loading the next block's coefficients ahead was slower (the
+// copies cost more than the waits).
+template <int R>
+__global__ __launch_bounds__(kShtThreads) __attribute__((amdgpu_waves_per_eu(R == 8 ? 2 : 4)))
+void k_leg_fwd(const ShtRing *__restrict__ rings, const double2 *__restrict__ F,
+               const double2 *__restrict__ ab_all, const double *__restrict__ pnorm,
+               const int *__restrict__ ring_lo, const int *__restrict__ step_base,
+               double *__restrict__ part_all, int L, int lq, int nnorth, int nsteps)
+{
+    __shared__ double ws[kShtThreads / 64][kLegFlush * 16];
+    const int m = leg_order(blockIdx.x);
+    if (m > L) return;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int lane = (int)threadIdx.x & 63;
+    const int i0 = ring_lo[m] + (int)blockIdx.y * R * kShtThreads;
+    if (i0 >= nnorth) return;
+    const int first = i0 + 64 * R * wave;
+    const bool idle = first >= nnorth;   // (wave-uniform)
+    const int steps = leg_steps(m, L);
+    const double2 *ab = ab_all + step_base[m];
+    F += (size_t)blockIdx.z * nnorth * 8 * lq;
+    double *part = part_all + 4 * (((size_t)blockIdx.y * gridDim.z + blockIdx.z) * nsteps + step_base[m]);
+    double z2[R], p1[R], p0[R];
+    double2 E[R], O[R];
+    int sc[R];
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+        const int i = first + 64 * q + lane;
+        const int ii = min(i, nnorth - 1);
+        const ShtRing Rg = rings[ii];
+        const double2 *row = F + (size_t)ii * 8 * lq + order_slot(m, lq);
+        const double2 zp = row[0], zm = row[4 * lq];
+        const double w = i < nnorth ? 0.5 : 0.0, wz = w * Rg.z;
+        E[q] = make_double2(w * (zp.x + zm.x), w * (zp.y - zm.y));
+        O[q] = make_double2(wz * (zp.y + zm.y), wz * (zm.x - zp.x));
+        z2[q] = Rg.z * Rg.z;
+        p0[q] = 0.0;
+        p1[q] = leg_start(pnorm[m], m, Rg.log2s, sc[q]);
+    }
+    int slot = 0, k0 = 0;
+    for (int k = 0; k < steps; k += kLegBlock) {
+        if (idle) {
+            if (lane < 16) ws[wave][slot * 16 + lane] = 0.0;
+        } else {
+            double v[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) v[i] = 0.0;
+            d2v c[kLegBlock];
+#pragma unroll
+            for (int j = 0; j < kLegBlock; ++j) c[j] = ((uptr<d2v>)ab)[k + j];
+            bool scaled = false;
+#pragma unroll
+            for (int q = 0; q < R; ++q) scaled |= sc[q] < 0;
+            if (!__any(scaled)) {
+#pragma unroll
+                for (int j = 0; j < kLegBlock; ++j) {
+#pragma unroll
+                    for (int q = 0; q < R; ++q) {
+                        const double p = p1[q];
+                        v[4 * j] = fma(p, E[q].x, v[4 * j]);
+                        v[4 * j + 1] = fma(p, E[q].y, v[4 * j + 1]);
+                        v[4 * j + 2] = fma(p, O[q].x, v[4 * j + 2]);
+                        v[4 * j + 3] = fma(p, O[q].y, v[4 * j + 3]);
+                        p1[q] = fma(fma(c[j].x, z2[q], c[j].y), p, -p0[q]);
+                        p0[q] = p;
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < kLegBlock; ++j) {
+#pragma unroll
+                    for (int q = 0; q < R; ++q) {
+                        const double p = p1[q];
+                        const double u = sc[q] == 0 ? p : 0.0;
+                        v[4 * j] = fma(u, E[q].x, v[4 * j]);
+                        v[4 * j + 1] = fma(u, E[q].y, v[4 * j + 1]);
+                        v[4 * j + 2] = fma(u, O[q].x, v[4 * j + 2]);
+                        v[4 * j + 3] = fma(u, O[q].y, v[4 * j + 3]);
+                        p1[q] = fma(fma(c[j].x, z2[q], c[j].y), p, -p0[q]);
+                        p0[q] = p;
+                    }
+                }
+                // a block grows a value by less than 2^100, far below the range
+#pragma unroll
+                for (int q = 0; q < R; ++q) {
+                    if (sc[q] < 0 && fabs(p1[q]) > kScaleUp) {
+                        p1[q] *= kScaleStep;
+                        p0[q] *= kScaleStep;
+                        ++sc[q];
+                    }
+                }
+            }
+            const double s = reduce16(v);
+            if ((lane & 3) == 0) ws[wave][slot * 16 + (lane >> 2)] = s;
         }
-        __syncthreads();
+        if (++slot == kLegFlush || k + kLegBlock >= steps) {
+            __syncthreads();
+            for (int e = threadIdx.x; e < slot * 16; e += kShtThreads) {
+                double t = ws[0][e];
+#pragma unroll
+                for (int w = 1; w < kShtThreads / 64; ++w) t += ws[w][e];
+                part[(size_t)k0 * 4 + e] = t;
+            }
+            __syncthreads();
+            k0 += slot * kLegBlock;
+            slot = 0;
+        }
     }
 }
 
-__global__ __launch_bounds__(kShtThreads) void k_sht_fft_fwd(
-    const ShtRing *__restrict__ rings, const int *__restrict__ ring_list,
-    const double2 *__restrict__ tw, const double2 *__restrict__ hw, const float *__restrict__ x,
-    double2 *__restrict__ F, int L, int nrings, int M, int logM)
+// From the sums S_k, T_k (over the ring chunks, in chunk order) the
+// coefficients a_{m+2k} = c_{m+2k+1} nu_k S_k + c_{m+2k} nu_{k-1} S_{k-1} and
+// a_{m+2k+1} = nu_k T_k, times Omega Khat_l, and from these the synthesis
+// coefficients of pi_k (even: De_k = nu_k (a_{m+2k} c_{m+2k+1} + a_{m+2k+2}
+// c_{m+2k+2})) and of z pi_k (odd: Do_k = nu_k a_{m+2k+1}).
+__global__ __launch_bounds__(kShtThreads) void k_sht_mul(
+    const double *__restrict__ part, const double *__restrict__ kscale,
+    const double *__restrict__ nu, const int *__restrict__ ring_lo,
+    const int *__restrict__ step_base, double4 *__restrict__ D, int L, int nnorth, int chunk,
+    int nsteps)
 {
-    extern __shared__ double2 z[];
-    const int r = ring_list[blockIdx.x];
-    const ShtRing R = rings[r];
-    const float *xr = x + R.first;
-    for (int k = threadIdx.x; k < M; k += kShtThreads) {
-        const float2 v = *reinterpret_cast<const float2 *>(xr + 2 * k);
-        z[__brev((unsigned)k) >> (32 - logM)] = make_double2((double)v.x, (double)v.y);
-    }
-    __syncthreads();
-    fft_lds(z, tw, M, logM, false);
-    for (int m = threadIdx.x; m <= L; m += kShtThreads) {
-        const double2 a = z[m & (M - 1)];
-        const double2 b = conj2(z[(M - m) & (M - 1)]);
-        const double2 e = make_double2(0.5 * (a.x + b.x), 0.5 * (a.y + b.y));
-        const double2 d = make_double2(0.5 * (a.x - b.x), 0.5 * (a.y - b.y));
-        // X_m = e - i hw[m] d
-        const double2 hd = cmul(hw[m], d);
-        const double2 X = make_double2(e.x + hd.y, e.y - hd.x);
-        // times e^{-i m phi_0}, phi_0 = two_o pi / n
-        const long long q = ((long long)m * R.two_o) % (2LL * R.n);
-        double sp, cp;
-        sincospi((double)q / (double)R.n, &sp, &cp);
-        F[(size_t)m * nrings + r] = make_double2(cp * X.x + sp * X.y, cp * X.y - sp * X.x);
-    }
-}
-
-__global__ __launch_bounds__(kShtThreads) void k_sht_fft_bwd(
-    const ShtRing *__restrict__ rings, const int *__restrict__ ring_list,
-    const double2 *__restrict__ tw, const double2 *__restrict__ hw, const double2 *__restrict__ G,
-    float *__restrict__ out, int L, int nrings, int M, int logM, int accumulate)
-{
-    extern __shared__ double2 z[];
-    const int r = ring_list[blockIdx.x];
-    const ShtRing R = rings[r];
-    // S_m = G_r(m) e^{i m phi_0} for 1 <= m <= lcut, S_0 = Re G_r(0), else 0
-    auto spec = [&](int m) -> double2 {
-        if (m > L) return make_double2(0.0, 0.0);
-        const double2 g = G[(size_t)m * nrings + r];
-        if (m == 0) return make_double2(g.x, 0.0);
-        const long long q = ((long long)m * R.two_o) % (2LL * R.n);
-        double sp, cp;
-        sincospi((double)q / (double)R.n, &sp, &cp);
-        return make_double2(g.x * cp - g.y * sp, g.x * sp + g.y * cp);
+    const int m = blockIdx.y, map = blockIdx.z;
+    const int k = blockIdx.x * kShtThreads + threadIdx.x;
+    if (k >= leg_steps(m, L)) return;
+    const int base = step_base[m];
+    const int nchunk = (nnorth - ring_lo[m] + chunk - 1) / chunk;
+    auto sums = [&](int kk) {
+        double4 t = make_double4(0.0, 0.0, 0.0, 0.0);
+        if (kk < 0 || m + 2 * kk > L) return t;
+        for (int c = 0; c < nchunk; ++c) {
+            const double4 p = reinterpret_cast<const double4 *>(
+                part)[((size_t)c * gridDim.z + map) * nsteps + base + kk];
+            t.x += p.x;
+            t.y += p.y;
+            t.z += p.z;
+            t.w += p.w;
+        }
+        const double v = nu[base + kk];
+        t.x *= v;
+        t.y *= v;
+        t.z *= v;
+        t.w *= v;
+        return t;
     };
-    for (int qi = threadIdx.x; qi < M; qi += kShtThreads) {
-        const double2 a = spec(qi);
-        const double2 b = conj2(spec(qi == 0 ? M : M - qi));
-        const double2 e = make_double2(a.x + b.x, a.y + b.y);
-        const double2 d = make_double2(a.x - b.x, a.y - b.y);
-        // Z_q = e + i conj(hw[q]) d
-        const double2 hd = cmul(conj2(hw[qi]), d);
-        z[__brev((unsigned)qi) >> (32 - logM)] = make_double2(e.x - hd.y, e.y + hd.x);
-    }
-    __syncthreads();
-    fft_lds(z, tw, M, logM, true);
-    float *o = out + R.first;
-    for (int k = threadIdx.x; k < M; k += kShtThreads) {
-        const double2 v = z[k];
-        float2 y = make_float2((float)v.x, (float)v.y);
-        if (accumulate) {
-            const float2 p = *reinterpret_cast<const float2 *>(o + 2 * k);
-            y.x = p.x + y.x;
-            y.y = p.y + y.y;
+    auto coef = [&](int l) {   // c_l
+        const double dl = l, dm = m;
+        return sqrt((dl * dl - dm * dm) / (4.0 * dl * dl - 1.0));
+    };
+    const double4 sm = sums(k - 1), s0 = sums(k), sp = sums(k + 1);
+    const int l = m + 2 * k;
+    double4 d = make_double4(0.0, 0.0, 0.0, 0.0);
+    if (l <= L) {
+        const double ca = k > 0 ? coef(l) : 0.0, cb = coef(l + 1), cc = coef(l + 2),
+                     cd = coef(l + 3), v = nu[base + k];
+        const double ks0 = kscale[l];
+        d.x = cb * ks0 * (cb * s0.x + ca * sm.x);
+        d.y = cb * ks0 * (cb * s0.y + ca * sm.y);
+        if (l + 2 <= L) {
+            const double ks2 = kscale[l + 2];
+            d.x = fma(cc * ks2, cd * sp.x + cc * s0.x, d.x);
+            d.y = fma(cc * ks2, cd * sp.y + cc * s0.y, d.y);
         }
-        *reinterpret_cast<float2 *>(o + 2 * k) = y;
+        d.x *= v;
+        d.y *= v;
+        if (l + 1 <= L) {
+            d.z = v * kscale[l + 1] * s0.z;
+            d.w = v * kscale[l + 1] * s0.w;
+        }
+    }
+    D[(size_t)map * nsteps + base + k] = d;
+}
+
+// Workgroup (order m, chunk of ring pairs, map): the even and odd sums over l
+// of the chunk's ring pairs, laid out as in k_leg_fwd; rings below ring_lo[m]
+// get zeros.
+template <int R>
+__global__ __launch_bounds__(kShtThreads) __attribute__((amdgpu_waves_per_eu(4)))
+void k_leg_bwd(const ShtRing *__restrict__ rings, const double4 *__restrict__ D_all,
+               const double2 *__restrict__ ab_all, const double *__restrict__ pnorm,
+               const int *__restrict__ ring_lo, const int *__restrict__ step_base,
+               double2 *__restrict__ G, int L, int lq, int nnorth, int nsteps)
+{
+    const int m = leg_order(blockIdx.x);
+    if (m > L) return;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int lane = (int)threadIdx.x & 63;
+    const int lo = ring_lo[m], c0 = (int)blockIdx.y * R * kShtThreads;
+    G += (size_t)blockIdx.z * nnorth * 8 * lq;
+    for (int i = c0 + (int)threadIdx.x; i < min(c0 + R * kShtThreads, lo); i += kShtThreads) {
+        double2 *row = G + (size_t)i * 8 * lq + order_slot(m, lq);
+        row[0] = make_double2(0.0, 0.0);
+        row[4 * lq] = make_double2(0.0, 0.0);
+    }
+    const int first = lo + c0 + 64 * R * wave;
+    if (first >= nnorth) return;
+    const int steps = leg_steps(m, L);
+    const double2 *ab = ab_all + step_base[m];
+    const double4 *D = D_all + (size_t)blockIdx.z * nsteps + step_base[m];
+    double z2[R], p1[R], p0[R];
+    double2 e[R], o[R];
+    int sc[R];
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+        const ShtRing Rg = rings[min(first + 64 * q + lane, nnorth - 1)];
+        z2[q] = Rg.z * Rg.z;
+        p0[q] = 0.0;
+        p1[q] = leg_start(pnorm[m], m, Rg.log2s, sc[q]);
+        e[q] = o[q] = make_double2(0.0, 0.0);
+    }
+    for (int k = 0; k < steps; k += kLegBlock) {
+        d2v c[kLegBlock];
+        d4v d[kLegBlock];
+#pragma unroll
+        for (int j = 0; j < kLegBlock; ++j) {
+            c[j] = ((uptr<d2v>)ab)[k + j];
+            d[j] = ((uptr<d4v>)D)[k + j];
+        }
+        bool scaled = false;
+#pragma unroll
+        for (int q = 0; q < R; ++q) scaled |= sc[q] < 0;
+        if (!__any(scaled)) {
+#pragma unroll
+            for (int j = 0; j < kLegBlock; ++j) {
+#pragma unroll
+                for (int q = 0; q < R; ++q) {
+                    const double p = p1[q];
+                    e[q].x = fma(p, d[j].x, e[q].x);
+                    e[q].y = fma(p, d[j].y, e[q].y);
+                    o[q].x = fma(p, d[j].z, o[q].x);
+                    o[q].y = fma(p, d[j].w, o[q].y);
+                    p1[q] = fma(fma(c[j].x, z2[q], c[j].y), p, -p0[q]);
+                    p0[q] = p;
+                }
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < kLegBlock; ++j) {
+#pragma unroll
+                for (int q = 0; q < R; ++q) {
+                    const double p = p1[q];
+                    const double u = sc[q] == 0 ? p : 0.0;
+                    e[q].x = fma(u, d[j].x, e[q].x);
+                    e[q].y = fma(u, d[j].y, e[q].y);
+                    o[q].x = fma(u, d[j].z, o[q].x);
+                    o[q].y = fma(u, d[j].w, o[q].y);
+                    p1[q] = fma(fma(c[j].x, z2[q], c[j].y), p, -p0[q]);
+                    p0[q] = p;
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < R; ++q) {
+                if (sc[q] < 0 && fabs(p1[q]) > kScaleUp) {
+                    p1[q] *= kScaleStep;
+                    p0[q] *= kScaleStep;
+                    ++sc[q];
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+        const int i = first + 64 * q + lane;
+        if (i >= nnorth) continue;
+        const double z = rings[i].z;
+        double2 *row = G + (size_t)i * 8 * lq + order_slot(m, lq);
+        row[0] = e[q];
+        row[4 * lq] = make_double2(z * o[q].x, z * o[q].y);
     }
 }
 
 // ---------------------------------------------------------------- host --
+// Ring pairs of one FFT launch: those of similar FFT length, so that LDS and
+// threads fit them.
+struct ShtBucket {
+    int first = 0, count = 0;   // entries of the plan's list
+    int lg = 0;                 // log2 of the longest FFT
+    int threads = 0;
+    bool direct = false;
+};
+
 struct Harm {
     int nside = 0;
     int nrings = 0;
     int nnorth = 0;     // northern rings and the equator: 2 Nside
     int lcut = 0;
     int max_batch = 1;
-    int nchunk = 0;     // ring chunks of kShtThreads rings
-    int nchunk_fwd = 0; // ring chunks of the Legendre kernels (kLegChunk rings)
+    int nmaps = 1;      // maps of one pass over the kernels (workspace)
+    int lq = 0;         // orders of one class mod 4, rounded up to whole lines
+    int nchunk = 0;     // most ring chunks of k_leg_fwd
+    int leg_r = 1;      // ring pairs per lane of k_leg_fwd
+    int nsteps = 0;     // recurrence steps of all orders
     int device = -1;
     long long npix = 0;
     long long nalm = 0;
     double omega = 0.0;
     std::vector<double> khat;
     ShtRing *d_rings = nullptr;
-    double2 *d_rec = nullptr;
-    double *d_mnorm = nullptr;
+    double2 *d_ab = nullptr;      // A_k, B_k of every order
+    double *d_nu = nullptr;
+    double *d_pnorm = nullptr;
     double *d_kscale = nullptr;
     int *d_ring_lo = nullptr;     // per m: first northern ring whose terms matter
+    int *d_step_base = nullptr;   // per m: first step
     int *d_dft_rings = nullptr;   // rings of the Goertzel / Clenshaw kernels
-    int *d_fft_rings = nullptr;   // rings of the FFT kernels (belt, n = 2^k > 2 lcut)
-    double2 *d_tw = nullptr;      // FFT tables tw (M/2) and hw (M + 1)
-    double2 *d_hw = nullptr;
-    int n_dft = 0, n_fft = 0, fft_m = 0, fft_log = 0;
-    double2 *d_F = nullptr;       // F, then G: (lcut+1) x nrings
-    double2 *d_part = nullptr;    // nchunk x nalm
-    double2 *d_alm = nullptr;
+    ShtFftRing *d_fft_rings = nullptr;
+    double2 *d_tw = nullptr;
+    double2 *d_roots = nullptr;
+    double2 *d_chirp = nullptr;
+    std::vector<ShtBucket> buckets;
+    int n_dft = 0, n_fft = 0, lgm = 0;
+    double2 *d_F = nullptr;       // nmaps x nnorth rows: Z(m), Z(-m), then even, odd sums
+    double *d_part = nullptr;     // nchunk x nmaps x nsteps x 4
+    double4 *d_D = nullptr;       // nmaps x nsteps
     long long device_bytes = 0;
 };
 
@@ -627,25 +1266,28 @@ static void harm_free(Harm &h)
         (void)hipGetDevice(&cur);
         (void)hipSetDevice(h.device);
         (void)hipDeviceSynchronize();
-        for (void *p : {(void *)h.d_rings, (void *)h.d_rec, (void *)h.d_mnorm, (void *)h.d_kscale,
-                        (void *)h.d_ring_lo, (void *)h.d_dft_rings, (void *)h.d_fft_rings,
-                        (void *)h.d_tw, (void *)h.d_hw, (void *)h.d_F, (void *)h.d_part,
-                        (void *)h.d_alm})
+        for (void *p : {(void *)h.d_rings, (void *)h.d_ab, (void *)h.d_nu, (void *)h.d_pnorm,
+                        (void *)h.d_kscale, (void *)h.d_ring_lo, (void *)h.d_step_base,
+                        (void *)h.d_dft_rings, (void *)h.d_fft_rings, (void *)h.d_tw, (void *)h.d_roots,
+                        (void *)h.d_chirp, (void *)h.d_F, (void *)h.d_part, (void *)h.d_D})
             if (p) (void)hipFree(p);
         (void)hipSetDevice(cur);
     }
     h.d_rings = nullptr;
-    h.d_rec = nullptr;
-    h.d_mnorm = nullptr;
+    h.d_ab = nullptr;
+    h.d_nu = nullptr;
+    h.d_pnorm = nullptr;
     h.d_kscale = nullptr;
     h.d_ring_lo = nullptr;
+    h.d_step_base = nullptr;
     h.d_dft_rings = nullptr;
     h.d_fft_rings = nullptr;
     h.d_tw = nullptr;
-    h.d_hw = nullptr;
+    h.d_roots = nullptr;
+    h.d_chirp = nullptr;
     h.d_F = nullptr;
     h.d_part = nullptr;
-    h.d_alm = nullptr;
+    h.d_D = nullptr;
 }
 
 static int harm_alloc(void **p, size_t bytes, long long *total)
@@ -658,12 +1300,133 @@ static int harm_alloc(void **p, size_t bytes, long long *total)
     return ARKCOS_OK;
 }
 
+template <class T>
+static int harm_upload(T **p, const std::vector<T> &v, long long *total)
+{
+    int rc = harm_alloc((void **)p, v.size() * sizeof(T), total);
+    if (rc) return rc;
+    if (!v.empty())
+        ARKCOS_HIP_CHECK(hipMemcpy(*p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice));
+    return ARKCOS_OK;
+}
+
 static int harm_upload_kernel(Harm &h)
 {
     std::vector<double> ks(h.lcut + 1);
     for (int l = 0; l <= h.lcut; ++l) ks[l] = h.omega * h.khat[l];
     ARKCOS_HIP_CHECK(hipMemcpy(h.d_kscale, ks.data(), ks.size() * sizeof(double),
                                hipMemcpyHostToDevice));
+    return ARKCOS_OK;
+}
+
+#define ARKCOS_RING_KERNEL(name)                                                             \
+    static auto name##_kernel(const ShtBucket &B)                                            \
+    {                                                                                        \
+        switch (B.threads) {                                                                 \
+            case 128: return B.direct ? k_##name<128, false> : k_##name<128, true>;          \
+            case 256: return B.direct ? k_##name<256, false> : k_##name<256, true>;          \
+            case 512: return B.direct ? k_##name<512, false> : k_##name<512, true>;          \
+            default: return B.direct ? k_##name<1024, false> : k_##name<1024, true>;         \
+        }                                                                                    \
+    }
+ARKCOS_RING_KERNEL(ring_fwd)
+ARKCOS_RING_KERNEL(ring_bwd)
+#undef ARKCOS_RING_KERNEL
+
+// Ring pairs by FFT length, and those left to the direct sums.
+static int harm_build_ffts(Harm &h, const std::vector<ShtRing> &rings)
+{
+    // Small maps take the direct sums, npix (lcut + 1) terms each way: the FFT
+    // kernels are a long chain of short passes, whose start-up dominates there
+    // (both ways at Nside 128, lcut 146, 2.9e7 terms: direct 15 us, FFTs 64 us; at
+    // Nside 16: 7 and 50 us; at Nside 256, lcut 269, 2.1e8 terms, eight maps: the
+    // whole call takes 0.38 ms with the FFTs).
+    const bool use_fft = std::getenv("ARKCOS_SHT_NO_FFT") == nullptr &&
+                         (double)h.npix * (h.lcut + 1) > kShtDirectWork;
+    std::vector<int> dft;
+    std::vector<ShtFftRing> list[5], spectra;   // (spectra: one entry per chirped length)
+    long long chirp = 0;
+    std::vector<long long> at((size_t)h.nside + 1, -1);   // chirp spectrum of length k
+    for (int i = 0; i < h.nnorth; ++i) {
+        const int k = rings[i].n / 4;
+        if (!use_fft || k > kShtMaxK) {
+            dft.push_back(i);
+            continue;
+        }
+        ShtFftRing q{};
+        q.ring = i;
+        q.k = k;
+        // the belt rings directly if they can; caps hold few power-of-two rings
+        const bool direct = k == h.nside && k >= 8 && (k & (k - 1)) == 0;
+        q.lg = 3;
+        while ((1 << q.lg) < (direct ? k : 2 * k - 1)) ++q.lg;
+        if (!direct) {
+            if (at[k] < 0) {
+                at[k] = chirp;
+                q.chirp = (int)chirp;
+                chirp += 1LL << q.lg;
+                spectra.push_back(q);
+            }
+            q.chirp = (int)at[k];
+        }
+        h.lgm = std::max(h.lgm, q.lg);
+        // chirped, by FFT length: up to 1024, 2048, 4096, longer; then direct
+        list[direct ? 4 : (q.lg <= 10 ? 0 : q.lg - 10)].push_back(q);
+    }
+    h.lgm = std::max(h.lgm, 5);
+    std::vector<ShtFftRing> all;
+    for (int b = 0; b < 5; ++b) {
+        if (list[b].empty()) continue;
+        ShtBucket B;
+        B.first = (int)all.size();
+        B.count = (int)list[b].size();
+        for (const ShtFftRing &q : list[b]) B.lg = std::max(B.lg, q.lg);
+        B.direct = b == 4;
+        B.threads = std::max(128, (1 << B.lg) / 8);   // a radix-8 butterfly each
+        // longest first (equatorward rings), so that the last workgroups are short
+        std::stable_sort(list[b].begin(), list[b].end(),
+                         [](const ShtFftRing &p, const ShtFftRing &q) { return p.k > q.k; });
+        all.insert(all.end(), list[b].begin(), list[b].end());
+        h.buckets.push_back(B);
+    }
+    h.n_dft = (int)dft.size();
+    h.n_fft = (int)all.size();
+    const int Pm = 1 << h.lgm;
+    std::vector<double2> tw(Pm / 4);
+    for (int t = 0; t < Pm / 4; ++t)
+        tw[t] = make_double2(std::cos(2.0 * M_PI * t / Pm), -std::sin(2.0 * M_PI * t / Pm));
+    int rc;
+    if ((rc = harm_upload(&h.d_dft_rings, dft, &h.device_bytes))) return rc;
+    if ((rc = harm_upload(&h.d_fft_rings, all, &h.device_bytes))) return rc;
+    if ((rc = harm_upload(&h.d_tw, tw, &h.device_bytes))) return rc;
+    std::vector<double2> roots(kRoots);
+    for (int t = 0; t < kRoots; ++t)
+        roots[t] = make_double2(std::cos(2.0 * M_PI * t / kRoots), std::sin(2.0 * M_PI * t / kRoots));
+    if ((rc = harm_upload(&h.d_roots, roots, &h.device_bytes))) return rc;
+    if ((rc = harm_alloc((void **)&h.d_chirp, (size_t)chirp * sizeof(double2), &h.device_bytes)))
+        return rc;
+    const int lds = (int)fft_lds_bytes(h.lgm);
+    ARKCOS_HIP_CHECK(hipFuncSetAttribute((const void *)k_chirp,
+                                         hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+    for (const ShtBucket &B : h.buckets)
+        for (const void *f : {(const void *)ring_fwd_kernel(B), (const void *)ring_bwd_kernel(B)})
+            ARKCOS_HIP_CHECK(
+                hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+    if (h.n_dft > 0)
+        ARKCOS_HIP_CHECK(hipFuncSetAttribute((const void *)k_sht_dft_bwd,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize,
+                                             (int)(2 * (h.lcut + 1) * sizeof(double2))));
+    if (!spectra.empty()) {
+        ShtFftRing *d = nullptr;
+        long long bytes = 0;
+        if ((rc = harm_upload(&d, spectra, &bytes))) return rc;
+        hipLaunchKernelGGL(k_chirp, dim3((unsigned)spectra.size()), dim3(1024), lds, nullptr, d,
+                           h.d_tw, h.d_roots, h.d_chirp, h.lgm);
+        const hipError_t e = hipGetLastError() == hipSuccess ? hipStreamSynchronize(nullptr)
+                                                             : hipErrorLaunchFailure;
+        (void)hipFree(d);
+        ARKCOS_HIP_CHECK(e);
+    }
     return ARKCOS_OK;
 }
 
@@ -681,52 +1444,65 @@ static int harm_build(Harm &h)
         rings[i].two_o = g.two_o;
         rings[i].pad = 0;
     }
-    // recurrence coefficients A = a_lm, B = a_lm b_lm, and log2 of the
-    // lambda_mm normalisation sqrt((2m+1)!!/(4 pi (2m)!!))
-    std::vector<double2> rec((size_t)h.nalm);
-    std::vector<double> mnorm(L + 1);
+    // Recurrence tables.  With l = m + 2k + 1, z^2 p_k = c_{l+1} c_{l+2} p_{k+1} +
+    // (c_{l+1}^2 + c_l^2) p_k + c_l c_{l-1} p_{k-1}; nu_{k+1} = nu_{k-1} c_l c_{l-1} /
+    // (c_{l+1} c_{l+2}) makes the last coefficient 1.
+    std::vector<int> step_base(L + 2, 0);
+    for (int m = 0; m <= L; ++m) step_base[m + 1] = step_base[m] + leg_steps(m, L);
+    h.nsteps = step_base[L + 1];
+    std::vector<double2> ab((size_t)h.nsteps, make_double2(0.0, 0.0));
+    std::vector<double> nu((size_t)h.nsteps, 0.0), pnorm(L + 1), c2(L + 8);
     double acc = -std::log2(4.0 * M_PI);
     for (int m = 0; m <= L; ++m) {
         if (m > 0) acc += std::log2((2.0 * m + 1.0) / (2.0 * m));
-        mnorm[m] = 0.5 * acc;
-        const long long base = alm_base(m, L);
-        rec[base] = make_double2(0.0, 0.0);
-        for (int l = m + 1; l <= L; ++l) {
-            const double dl = l, dm = m;
-            const double a = std::sqrt((4.0 * dl * dl - 1.0) / (dl * dl - dm * dm));
-            const double b = std::sqrt(((dl - 1.0) * (dl - 1.0) - dm * dm) /
-                                       (4.0 * (dl - 1.0) * (dl - 1.0) - 1.0));
-            rec[base + (l - m)] = make_double2(a, a * b);
+        pnorm[m] = 0.5 * (acc + std::log2(2.0 * m + 3.0));
+        for (int l = m; l <= L + 5; ++l)   // c_l^2
+            c2[l] = ((double)l - m) * ((double)l + m) / (4.0 * l * l - 1.0);
+        double v0 = 1.0, v1 = 1.0;   // nu_k, nu_{k+1}
+        const int base = step_base[m];
+        for (int k = 0; m + 2 * k <= L; ++k) {
+            const int l = m + 2 * k + 1;
+            const double g = std::sqrt(c2[l + 1] * c2[l + 2]);
+            const double A = v0 / (v1 * g);
+            ab[base + k] = make_double2(A, -(c2[l + 1] + c2[l]) * A);
+            nu[base + k] = v0;
+            // nu_{k+2} = nu_k c_{l+2} c_{l+1} / (c_{l+3} c_{l+4})
+            const double next = v0 * g / std::sqrt(c2[l + 3] * c2[l + 4]);
+            v0 = v1;
+            v1 = next;
         }
     }
     // Per order m, the first northern ring (rings run from the pole to the
-    // equator, sin theta increasing) on which some lambda_lm, l <= lcut,
-    // exceeds 2^-394: below it every term is negligible and the Legendre
-    // kernels skip the ring.  For fixed l and m, |lambda_lm| grows with
-    // sin theta until the oscillatory range, so the rings that matter are a
-    // suffix and a bisection finds its start.
+    // equator, sin theta increasing) on which some p_k exceeds 2^-394: below it
+    // every term is negligible and the Legendre kernels skip the ring.  For
+    // fixed l and m, |lambda_lm| grows with sin theta until the oscillatory
+    // range, so the rings that matter are a suffix and a bisection finds its
+    // start.
     std::vector<int> ring_lo(L + 1, 0);
     auto matters = [&](int i, int m) {
         const ShtRing &Rg = rings[i];
-        double e = mnorm[m] + m * Rg.log2s;      // log2 |lambda_mm|
+        const double e = pnorm[m] + m * Rg.log2s;      // log2 p_0
         if (e > -394.0) return true;
-        double scale = std::floor(e);               // |lambda| = v1 2^scale
+        double scale = std::floor(e);               // |pi_k| = v1 2^scale
         double v1 = std::exp2(e - scale);
         double v2 = 0.0;
-        const long long base = alm_base(m, L);
-        for (int l = m + 1; l <= L; ++l) {
-            const double2 ab = rec[base + (l - m)];
-            const double v = ab.x * Rg.z * v1 - ab.y * v2;
+        const int base = step_base[m];
+        const double z2 = Rg.z * Rg.z;
+        for (int k = 0; m + 2 * k <= L; ++k) {
+            const double v = (ab[base + k].x * z2 + ab[base + k].y) * v1 - v2;
             v2 = v1;
             v1 = v;
-            if (std::fabs(v1) > 0x1p200 || (std::fabs(v1) < 0x1p-200 && v1 != 0.0)) {
-                int k = 0;
-                std::frexp(v1, &k);
-                v1 = std::ldexp(v1, -k);
-                v2 = std::ldexp(v2, -k);
-                scale += k;
+            const double av = std::fabs(v1);
+            if (av > 0x1p200 || (av < 0x1p-200 && v1 != 0.0)) {
+                int ex = 0;
+                std::frexp(v1, &ex);
+                v1 = std::ldexp(v1, -ex);
+                v2 = std::ldexp(v2, -ex);
+                scale += ex;
             }
-            if (v1 != 0.0 && std::log2(std::fabs(v1)) + scale > -394.0) return true;
+            // (log2 |v1| <= 200 after the rescale)
+            if (scale > -594.0 && v1 != 0.0 && std::log2(std::fabs(v1)) + scale > -394.0)
+                return true;
         }
         return false;
     };
@@ -742,105 +1518,52 @@ static int harm_build(Harm &h)
         }
         ring_lo[m] = lo;
     }
-    // Belt rings take the FFT when their length n = 4 Nside is a power of two,
-    // n/2 fits the LDS (complex FP64) and lcut < n/2; the others Goertzel.
-    std::vector<int> dft_rings, fft_rings;
-    {
-        const int n = 4 * h.nside;
-        const bool pow2 = (n & (n - 1)) == 0;
-        const int M = n / 2;
-        const bool fft = pow2 && M >= 2 && M <= kShtFftMaxM && L < M &&
-                         std::getenv("ARKCOS_SHT_NO_FFT") == nullptr;
-        for (int i = 0; i < h.nrings; ++i) {
-            if (fft && rings[i].n == n) fft_rings.push_back(i); else dft_rings.push_back(i);
-        }
-        if (fft) {
-            h.fft_m = M;
-            h.fft_log = 0;
-            while ((1 << h.fft_log) < M) ++h.fft_log;
-        }
-    }
-    h.n_dft = (int)dft_rings.size();
-    h.n_fft = (int)fft_rings.size();
+    h.lq = ((L >> 2) + 8) & ~7;
+    // maps that pass through the kernels together: small maps fill the chip only
+    // as a group, and a group's rows stay below 512 MB
+    const size_t rows = (size_t)h.nnorth * 8 * h.lq * sizeof(double2);
+    h.nmaps = (int)std::max<size_t>(1, std::min<size_t>({(size_t)h.max_batch, 64, (512u << 20) / rows}));
     ARKCOS_HIP_CHECK(hipGetDevice(&h.device));
     int rc;
-    if ((rc = harm_alloc((void **)&h.d_rings, rings.size() * sizeof(ShtRing), &h.device_bytes)))
-        return rc;
-    if ((rc = harm_alloc((void **)&h.d_rec, rec.size() * sizeof(double2), &h.device_bytes)))
-        return rc;
-    if ((rc = harm_alloc((void **)&h.d_mnorm, mnorm.size() * sizeof(double), &h.device_bytes)))
-        return rc;
+    if ((rc = harm_upload(&h.d_rings, rings, &h.device_bytes))) return rc;
+    if ((rc = harm_upload(&h.d_ab, ab, &h.device_bytes))) return rc;
+    if ((rc = harm_upload(&h.d_nu, nu, &h.device_bytes))) return rc;
+    if ((rc = harm_upload(&h.d_pnorm, pnorm, &h.device_bytes))) return rc;
     if ((rc = harm_alloc((void **)&h.d_kscale, (L + 1) * sizeof(double), &h.device_bytes)))
         return rc;
-    if ((rc = harm_alloc((void **)&h.d_ring_lo, (L + 1) * sizeof(int), &h.device_bytes)))
-        return rc;
-    if ((rc = harm_alloc((void **)&h.d_dft_rings, dft_rings.size() * sizeof(int), &h.device_bytes)))
-        return rc;
-    if ((rc = harm_alloc((void **)&h.d_fft_rings, fft_rings.size() * sizeof(int), &h.device_bytes)))
-        return rc;
-    if (h.n_fft > 0) {
-        const int M = h.fft_m;
-        std::vector<double2> tw(M / 2 > 0 ? M / 2 : 1), hw(M + 1);
-        for (int t = 0; t < M / 2; ++t)
-            tw[t] = make_double2(std::cos(2.0 * M_PI * t / M), -std::sin(2.0 * M_PI * t / M));
-        for (int m = 0; m <= M; ++m)
-            hw[m] = make_double2(std::cos(M_PI * m / M), -std::sin(M_PI * m / M));
-        if ((rc = harm_alloc((void **)&h.d_tw, tw.size() * sizeof(double2), &h.device_bytes)))
-            return rc;
-        if ((rc = harm_alloc((void **)&h.d_hw, hw.size() * sizeof(double2), &h.device_bytes)))
-            return rc;
-        ARKCOS_HIP_CHECK(hipMemcpy(h.d_tw, tw.data(), tw.size() * sizeof(double2),
-                                   hipMemcpyHostToDevice));
-        ARKCOS_HIP_CHECK(hipMemcpy(h.d_hw, hw.data(), hw.size() * sizeof(double2),
-                                   hipMemcpyHostToDevice));
-        const size_t lds = (size_t)M * sizeof(double2);
-        ARKCOS_HIP_CHECK(hipFuncSetAttribute((const void *)k_sht_fft_fwd,
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        ARKCOS_HIP_CHECK(hipFuncSetAttribute((const void *)k_sht_fft_bwd,
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    }
-    if (!dft_rings.empty())
-        ARKCOS_HIP_CHECK(hipMemcpy(h.d_dft_rings, dft_rings.data(), dft_rings.size() * sizeof(int),
-                                   hipMemcpyHostToDevice));
-    if (!fft_rings.empty())
-        ARKCOS_HIP_CHECK(hipMemcpy(h.d_fft_rings, fft_rings.data(), fft_rings.size() * sizeof(int),
-                                   hipMemcpyHostToDevice));
-    if ((rc = harm_alloc((void **)&h.d_F, (size_t)(L + 1) * h.nrings * sizeof(double2),
+    if ((rc = harm_upload(&h.d_ring_lo, ring_lo, &h.device_bytes))) return rc;
+    if ((rc = harm_upload(&h.d_step_base, step_base, &h.device_bytes))) return rc;
+    if ((rc = harm_build_ffts(h, rings))) return rc;
+    if ((rc = harm_alloc((void **)&h.d_F, (size_t)h.nmaps * rows, &h.device_bytes))) return rc;
+    if ((rc = harm_alloc((void **)&h.d_part,
+                         (size_t)h.nchunk * h.nmaps * h.nsteps * 4 * sizeof(double),
                          &h.device_bytes)))
         return rc;
-    if ((rc = harm_alloc((void **)&h.d_part, (size_t)h.nchunk_fwd * h.nalm * sizeof(double2),
+    if ((rc = harm_alloc((void **)&h.d_D, (size_t)h.nmaps * h.nsteps * sizeof(double4),
                          &h.device_bytes)))
         return rc;
-    if ((rc = harm_alloc((void **)&h.d_alm, (size_t)h.nalm * sizeof(double2), &h.device_bytes)))
-        return rc;
-    ARKCOS_HIP_CHECK(hipMemcpy(h.d_rings, rings.data(), rings.size() * sizeof(ShtRing),
-                               hipMemcpyHostToDevice));
-    ARKCOS_HIP_CHECK(hipMemcpy(h.d_rec, rec.data(), rec.size() * sizeof(double2),
-                               hipMemcpyHostToDevice));
-    ARKCOS_HIP_CHECK(hipMemcpy(h.d_mnorm, mnorm.data(), mnorm.size() * sizeof(double),
-                               hipMemcpyHostToDevice));
-    ARKCOS_HIP_CHECK(hipMemcpy(h.d_ring_lo, ring_lo.data(), ring_lo.size() * sizeof(int),
-                               hipMemcpyHostToDevice));
     return harm_upload_kernel(h);
 }
 
-// The five kernels for one map.
-static int harm_launch(const Harm &h, const float *in, float *out, int accumulate, hipStream_t s)
+// The kernels for nb <= nmaps maps.
+static int harm_launch(const Harm &h, const float *in, float *out, int nb, int accumulate,
+                       hipStream_t s)
 {
     const int L = h.lcut;
-    const size_t fft_lds = (size_t)h.fft_m * sizeof(double2);
-    if (h.n_fft > 0)
-        hipLaunchKernelGGL(k_sht_fft_fwd, dim3(h.n_fft), dim3(kShtThreads), fft_lds, s, h.d_rings,
-                           h.d_fft_rings, h.d_tw, h.d_hw, in, h.d_F, L, h.nrings, h.fft_m,
-                           h.fft_log);
+    for (const ShtBucket &B : h.buckets) {
+        hipLaunchKernelGGL(ring_fwd_kernel(B), dim3(B.count, nb), dim3(B.threads), fft_lds_bytes(B.lg), s, h.d_rings,
+                           h.d_fft_rings + B.first, h.d_tw, h.d_roots, h.d_chirp, h.lgm,
+                           in, h.npix, h.d_F, L, h.lq, h.nnorth);
+    }
     // frequencies per thread, kShtMaxFreq per launch
     for (int m0 = 0, left = (L + kShtThreads) / kShtThreads; h.n_dft > 0 && left > 0;
          m0 += kShtMaxFreq * kShtThreads, left -= kShtMaxFreq) {
         switch (std::min(left, kShtMaxFreq)) {
 #define ARKCOS_DFT_CASE(K)                                                                   \
     case K:                                                                                  \
-        hipLaunchKernelGGL(k_sht_dft_fwd<K>, dim3(h.n_dft), dim3(kShtThreads), 0, s,        \
-                           h.d_rings, h.d_dft_rings, in, h.d_F, m0, L, h.nrings);            \
+        hipLaunchKernelGGL(k_sht_dft_fwd<K>, dim3(h.n_dft, nb), dim3(kShtThreads), 0, s,    \
+                           h.d_rings, h.d_dft_rings, h.d_roots, in, h.npix, h.d_F, m0, L, \
+                           h.lq, h.nnorth);                                                       \
         break;
             ARKCOS_DFT_CASE(1) ARKCOS_DFT_CASE(2) ARKCOS_DFT_CASE(3) ARKCOS_DFT_CASE(4)
             ARKCOS_DFT_CASE(5) ARKCOS_DFT_CASE(6) ARKCOS_DFT_CASE(7)
@@ -848,21 +1571,28 @@ static int harm_launch(const Harm &h, const float *in, float *out, int accumulat
 #undef ARKCOS_DFT_CASE
         }
     }
-    hipLaunchKernelGGL(k_sht_leg_fwd, dim3(h.nchunk_fwd, L + 1), dim3(kShtThreads), 0, s, h.d_rings,
-                       h.d_F, h.d_rec, h.d_mnorm, h.d_ring_lo, (double *)h.d_part, L, h.nrings,
-                       h.nnorth, h.nalm);
-    hipLaunchKernelGGL(k_sht_mul, dim3((L + kShtThreads) / kShtThreads, L + 1), dim3(kShtThreads),
-                       0, s, h.d_part, h.d_kscale, h.d_ring_lo, h.d_alm, L, h.nchunk_fwd, h.nalm);
-    hipLaunchKernelGGL(k_sht_leg_bwd, dim3(h.nchunk_fwd, L + 1), dim3(kShtThreads), 0, s, h.d_rings,
-                       h.d_alm, h.d_rec, h.d_mnorm, h.d_ring_lo, h.d_F, L, h.nrings, h.nnorth);
+    auto lf = h.leg_r == 1 ? k_leg_fwd<1> : (h.leg_r == 2 ? k_leg_fwd<2> : k_leg_fwd<kLegFwdRings>);
+    auto lb = h.leg_r == 1 ? k_leg_bwd<1> : (h.leg_r == 2 ? k_leg_bwd<2> : k_leg_bwd<kLegBwdRings>);
+    const int cf = kShtThreads * h.leg_r;
+    const int cb = kShtThreads * std::min(h.leg_r, kLegBwdRings);
+    hipLaunchKernelGGL(lf, dim3(leg_grid(L), (h.nnorth + cf - 1) / cf, nb), dim3(kShtThreads), 0, s,
+                       h.d_rings, h.d_F, h.d_ab, h.d_pnorm, h.d_ring_lo, h.d_step_base, h.d_part,
+                       L, h.lq, h.nnorth, h.nsteps);
+    hipLaunchKernelGGL(k_sht_mul, dim3((leg_steps(0, L) + kShtThreads - 1) / kShtThreads, L + 1, nb),
+                       dim3(kShtThreads), 0, s, h.d_part, h.d_kscale, h.d_nu, h.d_ring_lo,
+                       h.d_step_base, h.d_D, L, h.nnorth, cf, h.nsteps);
+    hipLaunchKernelGGL(lb, dim3(leg_grid(L), (h.nnorth + cb - 1) / cb, nb), dim3(kShtThreads), 0, s,
+                       h.d_rings, h.d_D, h.d_ab, h.d_pnorm, h.d_ring_lo, h.d_step_base, h.d_F, L,
+                       h.lq, h.nnorth, h.nsteps);
+    for (const ShtBucket &B : h.buckets) {
+        hipLaunchKernelGGL(ring_bwd_kernel(B), dim3(B.count, nb), dim3(B.threads), fft_lds_bytes(B.lg), s,
+                           h.d_rings, h.d_fft_rings + B.first, h.d_tw, h.d_roots, h.d_chirp,
+                           h.lgm, h.d_F, out, h.npix, L, h.lq, h.nnorth, accumulate);
+    }
     if (h.n_dft > 0)
-        hipLaunchKernelGGL(k_sht_dft_bwd, dim3(h.n_dft), dim3(kShtThreads),
-                           (size_t)(L + 1) * sizeof(double2), s, h.d_rings, h.d_dft_rings, h.d_F,
-                           out, L, h.nrings, accumulate);
-    if (h.n_fft > 0)
-        hipLaunchKernelGGL(k_sht_fft_bwd, dim3(h.n_fft), dim3(kShtThreads), fft_lds, s, h.d_rings,
-                           h.d_fft_rings, h.d_tw, h.d_hw, h.d_F, out, L, h.nrings, h.fft_m,
-                           h.fft_log, accumulate);
+        hipLaunchKernelGGL(k_sht_dft_bwd, dim3(h.n_dft, nb), dim3(kShtThreads),
+                           (size_t)2 * (L + 1) * sizeof(double2), s, h.d_rings, h.d_dft_rings,
+                           h.d_roots, h.d_F, out, h.npix, L, h.lq, h.nnorth, accumulate);
     ARKCOS_HIP_CHECK(hipGetLastError());
     return ARKCOS_OK;
 }
@@ -900,9 +1630,12 @@ int arkcos_harm_create(int nside, int lcut, const double *khat, int max_batch,
     h->max_batch = max_batch;
     h->npix = 12LL * nside * nside;
     h->omega = 4.0 * M_PI / (double)h->npix;
-    h->nalm = alm_base(lcut + 1, lcut);
-    h->nchunk = (h->nnorth + kShtThreads - 1) / kShtThreads;
-    h->nchunk_fwd = (h->nnorth + kLegChunk - 1) / kLegChunk;
+    h->nalm = (long long)(lcut + 1) * (lcut + 2) / 2;
+    // more ring pairs per lane share the coefficients and the reduction; small
+    // maps need the waves instead (at 600 ring pairs two per lane run 6 % faster
+    // than four, at 4096 eight 4 % faster than four)
+    h->leg_r = h->nnorth >= 1024 ? kLegFwdRings : (h->nnorth >= 512 ? 2 : 1);
+    h->nchunk = (h->nnorth + kShtThreads * h->leg_r - 1) / (kShtThreads * h->leg_r);
     int rc;
     try {
         h->khat.assign(khat, khat + lcut + 1);
@@ -968,9 +1701,9 @@ int arkcos_harm_convolve(arkcos_harm_t harm, const float *d_in, float *d_out, in
     if (accumulate != 0 && accumulate != 1) return fail(ARKCOS_EINVAL, "accumulate must be 0 or 1");
     if (overlap(d_in, d_out, h->npix * nbatch))
         return fail(ARKCOS_EINVAL, "d_in and d_out overlap");
-    for (int b = 0; b < nbatch; ++b) {
+    for (int b = 0; b < nbatch; b += h->nmaps) {
         int rc = harm_launch(*h, d_in + (size_t)b * h->npix, d_out + (size_t)b * h->npix,
-                             accumulate, (hipStream_t)stream);
+                             std::min(h->nmaps, nbatch - b), accumulate, (hipStream_t)stream);
         if (rc) return rc;
     }
     return ARKCOS_OK;

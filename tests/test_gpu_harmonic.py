@@ -73,6 +73,35 @@ def test_harmonic_fft_and_goertzel_paths_agree(monkeypatch):
     assert rel_rms(to_host(acc) - 0.25, to_host(y_dft)) <= 1e-6
 
 
+# Sums in FP64, rounded to FP32 once: at most half an ulp, 2^-24, of each pixel.
+@pytest.mark.parametrize("nside,lcut,nb", [
+    (100, 600, 2),     # rings shorter and longer than lcut, chirp transforms of 8 .. 256
+    (171, 200, 1),     # belt of no power of two
+    (256, 100, 1),     # belt rings transformed directly, short l range
+    (260, 700, 3)])    # more than one wave of ring pairs per order, several maps
+def test_harmonic_ring_ffts(nside, lcut, nb):
+    khat = _khat(lcut, nside)
+    x = W.white_noise(nside, 77, nbatch=nb)
+    log("harmonic ring FFTs Nside %d lcut %d" % (nside, lcut))
+    y = to_host(_A().Harm(nside, khat, max_batch=nb).convolve(to_dev(x)))
+    for b in range(nb):
+        err = rel_rms(y[b], O.harmonic(nside, khat, x[b].astype(np.float32).astype(np.float64)))
+        log("harmonic ring FFTs rel rms %.3e" % err)
+        assert err <= 2.0 ** -24
+
+
+@pytest.mark.parametrize("nside,lcut", [(1025, 64), (2100, 33)])
+def test_harmonic_long_ring_ffts(monkeypatch, nside, lcut):
+    """The longest chirp transforms (4096 and 8192) against the direct sums."""
+    khat = _khat(lcut, 5)
+    x = to_dev(W.white_noise(nside, 6))
+    log("harmonic long ring FFTs Nside %d" % nside)
+    y = to_host(_A().Harm(nside, khat).convolve(x))
+    monkeypatch.setenv("ARKCOS_SHT_NO_FFT", "1")
+    ref = to_host(_A().Harm(nside, khat).convolve(x))
+    assert rel_rms(y, ref) <= 2.0 ** -24
+
+
 def test_harmonic_batch_and_accumulate():
     import torch
     nside, lcut = 16, 40

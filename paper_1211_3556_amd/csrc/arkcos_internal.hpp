@@ -360,6 +360,8 @@ struct Plan {
     int occ_gen = 0;
     int occ_kc = 0;                     // and of the two knot-gradient kernels
     int occ_kg = 0;
+    int occ_km = 0;                     // several-map form of the general one (0: not used),
+    int knot_maps = 1;                  // and its maps per item
     long long device_bytes = 0;
 
     DevPlanView view() const;

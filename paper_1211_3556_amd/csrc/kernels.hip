@@ -517,17 +517,15 @@ __device__ __forceinline__ float node_coord(float d2, const UCoef &uc)
     return d * p;
 }
 
-// One staged position per thread: source position c0 + e of ring s and its
+// One staged position e per thread: source position c0 + e of ring s and its
 // reflection, four quarter turns each, on ring s (a, c) and its mirror (b, d).
-// Threads at or past cn load nothing: positions past the chunk are never
-// read.  Loads address their ring by 32-bit byte offsets shared between a
-// ring and its mirror (the ring's base stays in scalar registers).
+// Positions at or past cn load nothing.  Loads address their ring by 32-bit byte
+// offsets shared between a ring and its mirror (the ring's base stays in scalar registers).
 template <int SIDE>
 __device__ __forceinline__ void prefetch16(const float *src, const float *srcm, int n_s,
-                                           int two_o_s, int c0, int cn, float4 &a, float4 &b,
-                                           float4 &c, float4 &d)
+                                           int two_o_s, int c0, int cn, int e, float4 &a,
+                                           float4 &b, float4 &c, float4 &d)
 {
-    const int e = threadIdx.x;
     if (e >= cn) return;
     // byte offsets in the ring: jd of position c0 + e (-n_s < c0 + e < 2 n_s),
     // jr of its reflection qs - 2o_s - jd (-n_s < . < n_s), and their quarter turns
@@ -576,7 +574,8 @@ template <int SIDE = 0>
 __device__ __forceinline__ void prefetch_chunk(const float *in, const GenChunk &c, float4 &a,
                                                float4 &b, float4 &d2, float4 &d)
 {
-    prefetch16<SIDE>(in + c.first, in + c.first_m, c.n, c.two_o, c.c0, c.cn, a, b, d2, d);
+    prefetch16<SIDE>(in + c.first, in + c.first_m, c.n, c.two_o, c.c0, c.cn, (int)threadIdx.x, a,
+                     b, d2, d);
     mask_sources(c.mask, a, b, d2, d);
 }
 
@@ -1410,15 +1409,16 @@ __device__ __forceinline__ void knot_candidates16(const DevPairD &pd, const Node
 // 2^lp lanes per pixel taking every 2^lp-th candidate).  A lane holds g at the
 // sixteen output images of its pixel (zero where a ring-range plan writes no
 // output, and for the reflected images at a fixed point of the reflection).
-// Workgroups take the items blockIdx.x, blockIdx.x + gridDim.x, ... and bin
-// into one histogram per wave.
+// An item is a share of a tile's chunks (one of nsplit) on one map.  Workgroups take
+// the items blockIdx.x, blockIdx.x + gridDim.x, ... and bin into one histogram
+// per wave.
 // One instantiation per angle mode (AM), so that only that mode's FP64 series
 // constants occupy registers.
 constexpr int kGenWaves = kGenThreads / 64;
 template <int AM>
 __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(4)))
 void k_knot_gen(const DevPlanView *__restrict__ views, const float *__restrict__ g,
-                const float *__restrict__ x, int nmaps, double *__restrict__ partials)
+                const float *__restrict__ x, int nmaps, int nsplit, double *__restrict__ partials)
 {
     extern __shared__ __align__(16) double hists[];
     const DevPlanView P = cst(views)[0];
@@ -1428,10 +1428,11 @@ void k_knot_gen(const DevPlanView *__restrict__ views, const float *__restrict__
     double *hist = hists + (threadIdx.x >> 6) * hstride;   // this wave's own bins
     __syncthreads();
     const NodeMapD nm(P);
-    const int nitems = P.ngtiles2 * nmaps;
+    const int nitems = P.ngtiles2 * nmaps * nsplit;
     for (int item = blockIdx.x; item < nitems; item += gridDim.x) {
-        const int ti = item / nmaps;
-        const int map = item - ti * nmaps;
+        const int part = item % nsplit;
+        const int ti = item / nsplit / nmaps;
+        const int map = item / nsplit - ti * nmaps;
         const DevTile2 *Tp = P.gtiles2 + ti;
         const int nr = cst(Tp)->nr;
         const int kPart = kGenThreads / nr;
@@ -1468,8 +1469,9 @@ void k_knot_gen(const DevPlanView *__restrict__ views, const float *__restrict__
                 gv[12 + q] = (refl && gs_ok) ? gsm[jb + q * qr] : 0.0f;
             }
         }
-        const cptr<GenChunk> C = cst(P.gchunks) + cst(Tp)->c_begin;
-        const int nch = cst(Tp)->nchunks;
+        const int ch0 = cst(Tp)->nchunks * part / nsplit;
+        const int nch = cst(Tp)->nchunks * (part + 1) / nsplit - ch0;
+        const cptr<GenChunk> C = cst(P.gchunks) + cst(Tp)->c_begin + ch0;
         float4 pa, pb, pc, pd4;
         GenChunk ch{};
         if (nch > 0) {
@@ -1518,26 +1520,268 @@ void k_knot_gen(const DevPlanView *__restrict__ views, const float *__restrict__
     write_partials<kGenWaves>(hists, hstride, P.ntab,
                               partials + ((size_t)P.nkpart_circ + blockIdx.x) * P.ntab);
 }
+
+// ----------------------------------- general rings: per pair, several maps --
+// As k_knot_gen, for calls of kKnotMapsMin maps or more.
+// The sums C(pixel, candidate) = sum of g x over the sixteen images of the pair
+// run on the matrix cores, as v_mfma_f32_4x4x1_16b_f32: block b of a wave takes
+// the pixels 4b .. 4b + 3 (their g at image K is the A operand: lane l holds pixel
+// l) and four consecutive source positions (their x at image K is the B operand:
+// lane 4b + j reads position j of the block's four), and lane 4b + j receives
+// C(4b + i, j), i = 0..3, after sixteen products.  So a lane reads 64 bytes of LDS
+// for four pairs instead of one, and the pairs of up to kKnotMaps maps, whose
+// node coordinate is the same, are summed (in FP64 over the maps) before it is
+// evaluated once.  The price is the union of the four pixels' windows, about six
+// candidates more per row.  Nside 1024, 30 arcmin, 256 knots: 1804 -> 1400 us for
+// eight maps and 3 % of a training step for three; with one or two maps k_knot_gen
+// is the faster one (a step of one map 890 against 1090 us), hence kKnotMapsMin.
+// It waits on LDS and on the FP64 chains most of the time (two waves per SIMD:
+// the sixteen g of four maps take 64 registers); two maps per item at four
+// waves took 1390 to 1570 us.
+constexpr int kKnotMaps = 4;
+constexpr int kKnotMapsMin = 3;
+typedef float kn_v4f __attribute__((ext_vector_type(4)));
+
+// One wave over a staged chunk: `cnt` steps of this lane's block from position
+// p0 on, of which it takes every nsub-th, starting at `skew` and wrapping around
+// (neighbouring blocks, whose candidates at the same step have nearly the same
+// separation, then add into different bins); T the wave's largest count.
+// m: numerator of (pixel 4b, candidate lane & 3) at p0; ms, mj its changes per
+// step and per pixel.  wlo, whi: windows of the block's pixels relative to p0 + (lane & 3).
+template <bool LONG, int AM>
+__device__ __forceinline__ void knot_steps(const DevPairD &pd, const NodeMapD &nm, int m, int ms,
+                                           int mj, const float4 *stage, int p0, int cnt, int skew,
+                                           int T, const float (&gv)[kKnotMaps][16], int nv,
+                                           const int wlo[4], const int whi[4], int nsub,
+                                           int cn, double *hist)
+{
+    for (int t = 0; t < T; ++t) {
+        int tt = t + skew;
+        tt = tt >= cnt ? tt - cnt : tt;
+        tt = t < cnt ? tt : 0;
+        const int pos = p0 + 4 * nsub * tt;
+        const bool on = t < cnt && pos < cn;
+        const float4 *sp = stage + min(pos, kGenStage - 1);
+        double c[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int mp = 0; mp < kKnotMaps; ++mp) {
+            if (mp >= nv) break;
+            // four chains, so that a product does not wait for the one before
+            float4 v[4];
+            kn_v4f d[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                v[q] = sp[(4 * mp + q) * kGenStage];
+                d[q] = kn_v4f{0.0f, 0.0f, 0.0f, 0.0f};
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                d[q] = __builtin_amdgcn_mfma_f32_4x4x1f32(gv[mp][4 * q], v[q].x, d[q], 0, 0, 0);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                d[q] = __builtin_amdgcn_mfma_f32_4x4x1f32(gv[mp][4 * q + 1], v[q].y, d[q], 0, 0, 0);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                d[q] = __builtin_amdgcn_mfma_f32_4x4x1f32(gv[mp][4 * q + 2], v[q].z, d[q], 0, 0, 0);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                d[q] = __builtin_amdgcn_mfma_f32_4x4x1f32(gv[mp][4 * q + 3], v[q].w, d[q], 0, 0, 0);
+            const kn_v4f e = (d[0] + d[1]) + (d[2] + d[3]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) c[i] += (double)e[i];
+        }
+        const int mt = m - __mul24(tt, ms);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            bool use = on && c[i] != 0.0;
+            use = use && 4 * nsub * tt >= wlo[i] && 4 * nsub * tt <= whi[i];
+            if (use) {
+                int node;
+                double frac;
+                if (pair_node_knot<LONG, AM>(pd, nm, mt + i * mj, node, frac)) {
+                    atomicAdd(&hist[node], (1.0 - frac) * c[i]);
+                    atomicAdd(&hist[node + 1], frac * c[i]);
+                }
+            }
+        }
+    }
+}
+
+// Pairs whose output ring is general, over the general gather's tiles and
+// staged chunks (1, 2 or 4 adjacent rings sharing each staged source chunk), for
+// groups of nmg <= kKnotMaps maps.  A wave takes 64 pixels of one ring; the waves that a
+// ring has beyond its pixels share the steps.  A lane holds g at the sixteen
+// output images of its pixel (zero where a ring-range plan writes no output, and
+// for the reflected images at a fixed point of the reflection).
+// Workgroups take the items blockIdx.x, blockIdx.x + gridDim.x, ... and bin
+// into one histogram per wave.
+// One instantiation per angle mode (AM), so that only that mode's FP64 series
+// constants occupy registers.
+template <int AM>
+__global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(2)))
+void k_knot_maps(const DevPlanView *__restrict__ views, const float *__restrict__ g,
+                const float *__restrict__ x, int nmaps, int nmg, int nsplit,
+                double *__restrict__ partials)
+{
+    extern __shared__ __align__(16) double hists[];
+    const DevPlanView P = cst(views)[0];
+    const int hstride = hist_stride(P.ntab);
+    float4 *stage = reinterpret_cast<float4 *>(hists + kGenWaves * hstride);
+    for (int i = threadIdx.x; i < kGenWaves * hstride; i += blockDim.x) hists[i] = 0.0;
+    const int lane = (int)threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    double *hist = hists + wave * hstride;   // this wave's own bins
+    __syncthreads();
+    const NodeMapD nm(P);
+    const int ngroups = (nmaps + nmg - 1) / nmg;
+    const int nitems = P.ngtiles2 * ngroups * nsplit;
+    // longest tiles first, every other round of workgroups in reverse
+    const int nwg = (int)gridDim.x, wg = (int)blockIdx.x;
+    for (int r0 = 0, rev = 0; r0 < nitems; r0 += nwg, rev ^= 1) {
+        const int item = r0 + (rev ? nwg - 1 - wg : wg);
+        if (item >= nitems) continue;
+        const int ti = item / (ngroups * nsplit);
+        const int gs = item - ti * ngroups * nsplit;
+        const int map0 = gs / nsplit * nmg;
+        const int part = gs - gs / nsplit * nsplit;
+        const int nv = min(nmg, nmaps - map0);
+        const DevTile2 *Tp = P.gtiles2 + ti;
+        const int per = kGenWaves / cst(Tp)->nr;   // waves of a ring
+        const int h = wave / per;
+        const GenRing my = cst(Tp->q)[h];
+        const int len = my.len;
+        // pixel blocks of 64 and the waves that share each of them
+        const int nblk = max(1, (len + 63) >> 6);
+        const int nsub = per / nblk;               // >= 1: len <= 64 per
+        const int blk = (wave - h * per) % nblk, sub = (wave - h * per) / nblk;
+        const bool busy = 64 * blk < len && sub < nsub;   // (wave-uniform)
+        const int px = 64 * blk + lane;
+        const int rn = my.r;
+        const int rs = P.nrings - 1 - rn;
+        const DevRing R = cst(P.rings)[rn];
+        const int qr = R.n >> 2;
+        const bool active = busy && px < len;
+        const int j = cst(Tp)->j0 + min(px, max(len - 1, 0));
+        const int jb = qr - R.two_o - j;
+        const bool gn_ok = active && (my.flags & kTileSkipNorth) == 0;
+        const bool gs_ok = active && rs != rn && (my.flags & kTileSkipSouth) == 0;
+        const bool refl = jb != j && jb != qr;
+        float gv[kKnotMaps][16];
+#pragma unroll
+        for (int mp = 0; mp < kKnotMaps; ++mp) {
+            const float *gm = g + (size_t)(map0 + min(mp, nv - 1)) * P.npix;
+            const float *gn = gm + R.first;
+            const float *gsm = gm + cst(P.rings)[rs].first;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                gv[mp][q] = gn_ok ? gn[j + q * qr] : 0.0f;
+                gv[mp][4 + q] = gs_ok ? gsm[j + q * qr] : 0.0f;
+                gv[mp][8 + q] = (refl && gn_ok) ? gn[jb + q * qr] : 0.0f;
+                gv[mp][12 + q] = (refl && gs_ok) ? gsm[jb + q * qr] : 0.0f;
+            }
+        }
+        // this item's share of the tile's chunks
+        const int ch0 = cst(Tp)->nchunks * part / nsplit;
+        const int nch = cst(Tp)->nchunks * (part + 1) / nsplit - ch0;
+        const cptr<GenChunk> C = cst(P.gchunks) + cst(Tp)->c_begin + ch0;
+        // staging: this thread's position of maps m2 and m2 + 2, loaded a chunk ahead
+        const int m2 = (int)threadIdx.x >> 8, e2 = (int)threadIdx.x & 255;
+        float4 pv[kKnotMaps / 2][4];
+        auto load = [&](const GenChunk &c) {
+#pragma unroll
+            for (int r = 0; r < kKnotMaps / 2; ++r) {
+                pv[r][0] = pv[r][1] = pv[r][2] = pv[r][3] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                if (2 * r + m2 >= nv) continue;
+                const float *in = x + (size_t)(map0 + 2 * r + m2) * P.npix;
+                prefetch16<0>(in + c.first, in + c.first_m, c.n, c.two_o, c.c0, c.cn, e2,
+                              pv[r][0], pv[r][1], pv[r][2], pv[r][3]);
+                mask_sources(c.mask, pv[r][0], pv[r][1], pv[r][2], pv[r][3]);
+            }
+        };
+        GenChunk nx{};
+        if (nch > 0) {
+            nx = C[0];
+            load(nx);
+        }
+        for (int k = 0; k < nch; ++k) {
+            const GenChunk ch = nx;
+            nx = C[min(k + 1, nch - 1)];
+            const int rows = (ch.cn + 3) & ~3;   // a multiple of four, zero past the chunk
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < kKnotMaps / 2; ++r)
+                if (2 * r + m2 < nv && e2 < rows)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        stage[(4 * (2 * r + m2) + q) * kGenStage + e2] = pv[r][q];
+            __syncthreads();
+            if (k + 1 < nch) load(nx);
+            if (busy && ch.s >= my.s_lo && ch.s <= my.s_hi) {
+                const int kk = my.pb + ch.s - my.s_lo;
+                const DevPair pp = cst(P.pairs)[kk];
+                const DevPairD pd = cst(P.pairs_d)[kk];
+                int lo, hi;
+                pair_window(pp, ch.n, j, lo, hi);
+                // the union of the block's windows, in positions of the chunk
+                const int glo = __builtin_amdgcn_mov_dpp(lo, 0x00, 0xF, 0xF, true) - ch.c0;
+                const int ghi = __builtin_amdgcn_mov_dpp(hi, 0xFF, 0xF, 0xF, true) - ch.c0;
+                const int a0 = max(glo, 0) & ~3, a1 = min(ghi, ch.cn - 1);
+                const int all = a1 >= max(glo, 0) ? ((a1 - a0) >> 2) + 1 : 0;
+                // this wave's steps sub, sub + nsub, ... of the block
+                const int cnt = all > sub ? (all - sub - 1) / nsub + 1 : 0;
+                const int T = wave_max(cnt);
+                const int b = lane >> 2;
+                const int skew = cnt > 0 ? b % cnt : 0;
+                const int p0 = a0 + 4 * sub + (lane & 3);
+                // numerator of the block's first pixel; the others follow at 2 n_s
+                const int m0 = lon_numerator(lon_base(cst(Tp)->j0 + 64 * blk + 4 * b, R.two_o, ch.n),
+                                             ch.c0 + p0, ch.two_o, R.n);
+                const int at = ch.c0 + p0;
+                const int wlo[4] = {__builtin_amdgcn_mov_dpp(lo, 0x00, 0xF, 0xF, true) - at,
+                                    __builtin_amdgcn_mov_dpp(lo, 0x55, 0xF, 0xF, true) - at,
+                                    __builtin_amdgcn_mov_dpp(lo, 0xAA, 0xF, 0xF, true) - at,
+                                    __builtin_amdgcn_mov_dpp(lo, 0xFF, 0xF, 0xF, true) - at};
+                const int whi[4] = {__builtin_amdgcn_mov_dpp(hi, 0x00, 0xF, 0xF, true) - at,
+                                    __builtin_amdgcn_mov_dpp(hi, 0x55, 0xF, 0xF, true) - at,
+                                    __builtin_amdgcn_mov_dpp(hi, 0xAA, 0xF, 0xF, true) - at,
+                                    __builtin_amdgcn_mov_dpp(hi, 0xFF, 0xF, 0xF, true) - at};
+                if (pp.mode & kPairLongSin)
+                    knot_steps<true, AM>(pd, nm, m0, 8 * nsub * R.n, 2 * ch.n, stage, p0, cnt, skew,
+                                         T, gv, nv, wlo, whi, nsub, ch.cn, hist);
+                else
+                    knot_steps<false, AM>(pd, nm, m0, 8 * nsub * R.n, 2 * ch.n, stage, p0, cnt, skew,
+                                          T, gv, nv, wlo, whi, nsub, ch.cn, hist);
+            }
+        }
+    }
+    __syncthreads();
+    write_partials<kGenWaves>(hists, hstride, P.ntab,
+                              partials + ((size_t)P.nkpart_circ + blockIdx.x) * P.ntab);
+}
+
 // Fixed-order reduction of the per-workgroup partials, scaled by Omega: a
-// block of kReduceWaves waves covers 64 knots, wave w sums rows w, w + kReduceWaves, ...,
-// and the wave sums are added in wave order.
-constexpr int kReduceWaves = 16;
-__global__ __launch_bounds__(64 * kReduceWaves) void k_knot_reduce(
+// block of kReduceRows x kReduceKnots threads covers kReduceKnots knots (128 bytes of
+// a row), thread row w sums rows w, w + kReduceRows, ..., and the thread rows are
+// added in order.  The loads' latency bounds it: 64 thread rows and ntab/16 blocks
+// took the 1800 rows of Nside 1024 with 256 knots from 44 us (16 rows, ntab/64
+// blocks) to 13 us.
+constexpr int kReduceKnots = 16, kReduceRows = 64;
+__global__ __launch_bounds__(kReduceKnots *kReduceRows) void k_knot_reduce(
     const double *__restrict__ partials, int nblocks, int ntab, double omega,
     float *__restrict__ gk)
 {
-    __shared__ double red[kReduceWaves][64];
-    const int lane = threadIdx.x & 63;
-    const int w = threadIdx.x >> 6;
-    const int k = blockIdx.x * 64 + lane;
+    __shared__ double red[kReduceRows][kReduceKnots];
+    const int c = threadIdx.x % kReduceKnots;
+    const int w = threadIdx.x / kReduceKnots;
+    const int k = blockIdx.x * kReduceKnots + c;
     double s = 0.0;
     if (k < ntab)
-        for (int b = w; b < nblocks; b += kReduceWaves) s += partials[(size_t)b * ntab + k];
-    red[w][lane] = s;
+        for (int b = w; b < nblocks; b += kReduceRows) s += partials[(size_t)b * ntab + k];
+    red[w][c] = s;
     __syncthreads();
     if (w == 0 && k < ntab) {
         double t = 0.0;
-        for (int i = 0; i < kReduceWaves; ++i) t += red[i][lane];
+        for (int i = 0; i < kReduceRows; ++i) t += red[i][c];
         gk[k] = (float)(omega * t);
     }
 }
@@ -1598,13 +1842,35 @@ static size_t knot_circ_lds(int ntab)
     return knot_hist_bytes(ntab) + (size_t)kGroupRings * kKnotSeg * sizeof(float) +
            (size_t)kKnotWaves * kKnotXW * sizeof(float);
 }
-static size_t knot_gen_lds(int ntab)
+static size_t knot_gen_lds(int ntab, int nmg)
 {
     return (size_t)kGenWaves * hist_stride(ntab) * sizeof(double) +
-           (size_t)4 * kGenStage * sizeof(float4);
+           (size_t)4 * nmg * kGenStage * sizeof(float4);
 }
 
-
+// Launch of the general rings' knot gradient for nmaps maps.  Fewer items than
+// resident workgroups leave CUs idle and make the longest tile the time, so
+// the chunks of a tile are split between up to kKnotSplit items until every resident
+// workgroup has kKnotItems (Nside 128, 5 degrees, two maps, 72 tiles x maps: 144 us unsplit,
+// 31 us split; with four items per workgroup calls that have enough tiles
+// anyway, Nside 1024 and one map, got 3 % slower).
+constexpr int kKnotSplit = 16;
+constexpr int kKnotItems = 2;
+struct KnotLaunch {
+    int nmg, split, grid;   // maps per item (0: k_knot_gen), shares of a tile, workgroups
+};
+static KnotLaunch knot_launch(const Plan &p, int nmaps)
+{
+    KnotLaunch k{};
+    k.nmg = p.occ_km > 0 && nmaps >= kKnotMapsMin ? p.knot_maps : 0;
+    const long long room = (long long)(k.nmg ? p.occ_km : p.occ_kg) * p.cus;
+    const int per = std::max(1, k.nmg);
+    const long long items = (long long)p.gtiles2.size() * ((nmaps + per - 1) / per);
+    if (items == 0) return k;
+    k.split = (int)std::min<long long>(kKnotSplit, (kKnotItems * room + items - 1) / items);
+    k.grid = (int)std::min(room, items * k.split);
+    return k;
+}
 
 int prepare_launches(Plan &p)
 {
@@ -1613,19 +1879,28 @@ int prepare_launches(Plan &p)
     int rc;
     if ((rc = occupancy(p.circ_form ? k_circ_mfma : k_circ, circ_lds(), &p.occ_circ))) return rc;
     if ((rc = occupancy(k_general, gen_lds(p.desc.ntab), &p.occ_gen, kGenThreads))) return rc;
+    size_t lds = 0;
+    if ((rc = device_lds_limit(p.device, &lds))) return rc;
     p.grid_kc = p.grid_kg = 0;
     if ((p.desc.flags & ARKCOS_PLAN_LEARNABLE) && p.desc.ntab <= ARKCOS_MAX_GRAD_NTAB) {
         if ((rc = occupancy(k_knot_circ, knot_circ_lds(p.desc.ntab), &p.occ_kc))) return rc;
         // (the three angle-mode instantiations have the same resource limits)
-        if ((rc = occupancy(k_knot_gen<0>, knot_gen_lds(p.desc.ntab), &p.occ_kg, kGenThreads)))
+        if ((rc = occupancy(k_knot_gen<0>, knot_gen_lds(p.desc.ntab, 1), &p.occ_kg, kGenThreads)))
+            return rc;
+        p.occ_km = 0;
+        p.knot_maps = kKnotMaps;
+        while (p.knot_maps >= kKnotMapsMin && knot_gen_lds(p.desc.ntab, p.knot_maps) > lds)
+            --p.knot_maps;
+        if (p.desc.max_batch >= kKnotMapsMin && p.knot_maps >= kKnotMapsMin &&
+            (rc = occupancy(k_knot_maps<0>, knot_gen_lds(p.desc.ntab, p.knot_maps), &p.occ_km,
+                            kGenThreads)))
             return rc;
         // one partial row per resident workgroup of each knot kernel, and no
         // more workgroups than work items
         const long long mb = std::max(1, p.desc.max_batch);
         p.grid_kc = (int)std::min<long long>((long long)p.occ_kc * p.cus,
                                              (long long)p.kctiles.size() * mb);
-        p.grid_kg = (int)std::min<long long>((long long)p.occ_kg * p.cus,
-                                             (long long)p.gtiles2.size() * mb);
+        for (int nb = 1; nb <= mb; ++nb) p.grid_kg = std::max(p.grid_kg, knot_launch(p, nb).grid);
     }
     p.grid = std::max(1, p.grid_kc + p.grid_kg);
     return ARKCOS_OK;
@@ -1699,8 +1974,8 @@ int launch_build_knotw(const Plan &p, hipStream_t s)
     return ARKCOS_OK;
 }
 
-// Circulant rings by correlation, general rings per pair; every partial row
-// is written (the grids are the rows reserved at plan creation), then reduced.
+// Circulant rings by correlation, general rings per pair; every workgroup writes its
+// partial row (plan creation reserves the rows of the largest grids), then reduced.
 static int launch_knot(const Plan &p, const float *g, const float *x, float *gk, int nbatch,
                        hipStream_t s, double *kpart)
 {
@@ -1708,15 +1983,22 @@ static int launch_knot(const Plan &p, const float *g, const float *x, float *gk,
     if (p.grid_kc > 0)
         hipLaunchKernelGGL(k_knot_circ, dim3(p.grid_kc), dim3(kThreads), knot_circ_lds(ntab), s,
                            (const DevPlanView *)p.d_view, g, x, nbatch, kpart);
-    if (p.grid_kg > 0) {
+    const KnotLaunch k = knot_launch(p, nbatch);
+    if (k.grid > 0 && k.nmg > 0) {
+        auto kg = p.angle_mode == 0 ? k_knot_maps<0>
+                                    : (p.angle_mode == 1 ? k_knot_maps<1> : k_knot_maps<2>);
+        hipLaunchKernelGGL(kg, dim3(k.grid), dim3(kGenThreads), knot_gen_lds(ntab, k.nmg), s,
+                           (const DevPlanView *)p.d_view, g, x, nbatch, k.nmg, k.split, kpart);
+    } else if (k.grid > 0) {
         auto kg = p.angle_mode == 0 ? k_knot_gen<0>
                                     : (p.angle_mode == 1 ? k_knot_gen<1> : k_knot_gen<2>);
-        hipLaunchKernelGGL(kg, dim3(p.grid_kg), dim3(kGenThreads), knot_gen_lds(ntab), s,
-                           (const DevPlanView *)p.d_view, g, x, nbatch, kpart);
+        hipLaunchKernelGGL(kg, dim3(k.grid), dim3(kGenThreads), knot_gen_lds(ntab, 1), s,
+                           (const DevPlanView *)p.d_view, g, x, nbatch, k.split, kpart);
     }
     ARKCOS_HIP_CHECK(hipGetLastError());
-    hipLaunchKernelGGL(k_knot_reduce, dim3((ntab + 63) / 64), dim3(64 * kReduceWaves), 0, s,
-                       kpart, p.grid_kc + p.grid_kg, ntab, p.omega, gk);
+    hipLaunchKernelGGL(k_knot_reduce, dim3((ntab + kReduceKnots - 1) / kReduceKnots),
+                       dim3(kReduceKnots * kReduceRows), 0, s,
+                       kpart, p.grid_kc + k.grid, ntab, p.omega, gk);
     ARKCOS_HIP_CHECK(hipGetLastError());
     return ARKCOS_OK;
 }

@@ -49,6 +49,30 @@ def test_gradients_full_maps(nside, nb, tc_deg, nk):
     assert np.array_equal(to_host(gx2), gx)
 
 
+@pytest.mark.parametrize("nside,tc_deg,nk", [(16, 74.7, 33), (40, 7.0, 257), (100, 3.31, 64),
+                                             (16, 0.5, 16)])
+def test_knot_gradient_map_groups(nside, tc_deg, nk):
+    """The knot gradient of plans for 1, 2 and 6 maps (groups of one, two and four,
+    the last one partial, and the tiles' chunks split between workgroups) called
+    with every number of maps up to their limit."""
+    A = _A()
+    tc = np.radians(tc_deg)
+    assert_tie_free(nside, tc)
+    x = W.white_noise(nside, 610, nbatch=6)
+    g = W.white_noise(nside, 710, nbatch=6)
+    each = np.stack([O.knot_grad(nside, tc, nk, x[b], g[b]) for b in range(6)])
+    for mb in (1, 2, 6):
+        plan = A.Plan(nside, tc, ntab=nk, max_batch=mb, learnable=True)
+        plan.set_knots(to_dev(W.gaussian_profile_knots(tc / 3, tc, nk)))
+        for nb in range(1, mb + 1):
+            _, gk = plan.backward(to_dev(g[:nb]), to_dev(x[:nb]), want_map=False,
+                                  want_knots=True)
+            _sync()
+            ref = each[:nb].sum(axis=0)
+            assert np.max(np.abs(to_host(gk) - ref)) <= 1e-5 * np.abs(ref).max(), (mb, nb)
+            assert rel_rms(to_host(gk), ref) <= 1e-6, (mb, nb)
+
+
 def test_autograd_function_and_loss():
     """The torch.autograd.Function path on the c5 loss L = sum (conv(x) - t)^2 at
     a reduced Nside: gradients match the oracle's."""

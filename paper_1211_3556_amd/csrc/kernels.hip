@@ -354,6 +354,55 @@ __device__ __forceinline__ void circ_rows(const DevPlanView &P, const DevTile &T
 //    of u, so short rows waste a larger share of the products: the plan takes
 //    this form when its rows average at least kCircMfmaTaps taps.
 template <bool MF>
+__device__ __forceinline__ void circ_tile(const DevPlanView &P, const DevTile &T, const float *in,
+                                          float *out, float *xs, float *wls, int buf_floats)
+{
+    const int lane = (int)threadIdx.x & 63;
+    const int wave = (int)threadIdx.x >> 6;
+    const DevGroup G = cst(P.groups)[T.r];
+    const int n = cst(P.rings)[G.r0].n;
+    double acc[4][4];
+    circ_rows<MF>(P, T, G, n, in, xs, wls, buf_floats, acc);
+    if (MF) {
+        // ring lane >> 4, pixels 256 w + 64 q + 4 (lane & 15) + c (T.len is
+        // a multiple of 4)
+        const int r = lane >> 4;
+        if (r < G.nr) {
+            float *o = out + cst(P.rings)[G.r0 + r].first + T.j0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int px = kCircWavePix * wave + 64 * q + 4 * (lane & 15);
+                if (px < T.len) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) o[px + c] = (float)acc[q][c];
+                }
+            }
+        }
+    } else if (4 * (int)threadIdx.x < T.len) {   // T.len is a multiple of 4
+#pragma unroll
+        for (int r = 0; r < kGroupRings; ++r) {
+            if (r < G.nr) {
+                float *o = out + cst(P.rings)[G.r0 + r].first + T.j0 + 4 * threadIdx.x;
+#pragma unroll
+                for (int i = 0; i < kCircPix; ++i) o[i] = (float)acc[r][i];
+            }
+        }
+    }
+}
+
+// Zeroes the tap quads around both weight buffers (rows fill only the middle).
+__device__ __forceinline__ void circ_zero_ends(float *wls)
+{
+    if ((int)threadIdx.x < kCircWRow) {
+        const int e = (int)threadIdx.x;
+        wls[e] = 0.0f;
+        wls[kCircWBuf - kCircWRow + e] = 0.0f;
+        wls[kCircWBuf + e] = 0.0f;
+        wls[2 * kCircWBuf - kCircWRow + e] = 0.0f;
+    }
+}
+
+template <bool MF>
 __device__ __forceinline__ void circ_gather(const DevPlanView *__restrict__ views,
                                             const int2 *__restrict__ tile_map, int ntiles,
                                             const MapIO &io, int nmaps, int buf_floats,
@@ -362,16 +411,7 @@ __device__ __forceinline__ void circ_gather(const DevPlanView *__restrict__ view
     extern __shared__ __align__(16) float xs[];
     float *wls = xs + 2 * buf_floats;      // two weight buffers of kCircWBuf floats
     __shared__ int s_item;
-    // the zero tap quads around both weight buffers (rows fill only the middle)
-    if ((int)threadIdx.x < kCircWRow) {
-        const int e = (int)threadIdx.x;
-        wls[e] = 0.0f;
-        wls[kCircWBuf - kCircWRow + e] = 0.0f;
-        wls[kCircWBuf + e] = 0.0f;
-        wls[2 * kCircWBuf - kCircWRow + e] = 0.0f;
-    }
-    const int lane = (int)threadIdx.x & 63;
-    const int wave = (int)threadIdx.x >> 6;
+    circ_zero_ends(wls);
     const int nitems = ntiles * nmaps;
     for (;;) {
         const int item = next_item(counter, &s_item);
@@ -382,37 +422,8 @@ __device__ __forceinline__ void circ_gather(const DevPlanView *__restrict__ view
         const int lt = tile_map ? cst(tile_map)[ti].y : ti;
         const DevPlanView P = cst(views)[pi];
         const DevTile T = cst(P.ctiles)[lt];
-        const DevGroup G = cst(P.groups)[T.r];
-        const int n = cst(P.rings)[G.r0].n;
-        const float *in = io.in[pi] + (size_t)map * P.npix;
-        float *out = io.out[pi] + (size_t)map * P.npix;
-        double acc[4][4];
-        circ_rows<MF>(P, T, G, n, in, xs, wls, buf_floats, acc);
-        if (MF) {
-            // ring lane >> 4, pixels 256 w + 64 q + 4 (lane & 15) + c (T.len is
-            // a multiple of 4)
-            const int r = lane >> 4;
-            if (r < G.nr) {
-                float *o = out + cst(P.rings)[G.r0 + r].first + T.j0;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int px = kCircWavePix * wave + 64 * q + 4 * (lane & 15);
-                    if (px < T.len) {
-#pragma unroll
-                        for (int c = 0; c < 4; ++c) o[px + c] = (float)acc[q][c];
-                    }
-                }
-            }
-        } else if (4 * (int)threadIdx.x < T.len) {   // T.len is a multiple of 4
-#pragma unroll
-            for (int r = 0; r < kGroupRings; ++r) {
-                if (r < G.nr) {
-                    float *o = out + cst(P.rings)[G.r0 + r].first + T.j0 + 4 * threadIdx.x;
-#pragma unroll
-                    for (int i = 0; i < kCircPix; ++i) o[i] = (float)acc[r][i];
-                }
-            }
-        }
+        circ_tile<MF>(P, T, io.in[pi] + (size_t)map * P.npix, io.out[pi] + (size_t)map * P.npix,
+                      xs, wls, buf_floats);
     }
 }
 
@@ -949,6 +960,45 @@ void k_general(const DevPlanView *__restrict__ views, const int2 *__restrict__ t
             gen_tile_variant<true>(P, tab, stage, Tp, in, out);
         else
             gen_tile_variant<false>(P, tab, stage, Tp, in, out);
+    }
+}
+
+// Both gathers of one plan in one launch, a workgroup per (tile, map) in the
+// order of the tile lists, the general tiles (the longer ones) first.  A small
+// call is bound by the length of one tile's chain of rows, not by the chip: here
+// the two chains run side by side, with no queue to reset and one launch instead
+// of three.  Against k_circ and k_general one after the other: Nside 64, 6 degrees 53 -> 27 us;
+// Nside 256, 100 arcmin 80 -> 45; Nside 512, 90 arcmin 165 -> 146, two maps 243 -> 219.
+// Calls of more than kBothRounds rounds of resident workgroups keep the
+// persistent kernels: there every workgroup's own load of the table and the
+// circulant tiles' four waves in eight-wave workgroups cost more (Nside 512, 30 arcmin,
+// four maps, 3332 tiles: 134 against 138 us; Nside 1024, 30 arcmin, 2700: 235 against 259;
+// Nside 2048, 10 arcmin: 398 against 546).
+constexpr int kBothRounds = 4;
+template <bool MF>
+__global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(4)))
+void k_both(const DevPlanView *__restrict__ views, const float *in, float *out, int ngen, int nmaps,
+            int tab_floats, int buf_floats)
+{
+    extern __shared__ __align__(16) float lds[];
+    const DevPlanView P = cst(views)[0];
+    const bool gen = (int)blockIdx.x < ngen;
+    const int item = (int)blockIdx.x - (gen ? 0 : ngen);
+    const int ti = item / nmaps;
+    const size_t at = (size_t)(item - ti * nmaps) * P.npix;
+    if (gen) {
+        load_table(lds, P.table, P.ntab);
+        if (threadIdx.x < 2) lds[P.ntab + threadIdx.x] = 0.0f;
+        float4 *stage = reinterpret_cast<float4 *>(lds + tab_floats);
+        if (P.biased)
+            gen_tile_variant<true>(P, lds, stage, P.gtiles2 + ti, in + at, out + at);
+        else
+            gen_tile_variant<false>(P, lds, stage, P.gtiles2 + ti, in + at, out + at);
+    } else if ((int)threadIdx.x < kThreads) {   // (the barriers count the waves that are left)
+        float *wls = lds + 2 * buf_floats;
+        circ_zero_ends(wls);
+        const DevTile T = cst(P.ctiles)[ti];
+        circ_tile<MF>(P, T, in + at, out + at, lds, wls, buf_floats);
     }
 }
 
@@ -1829,6 +1879,7 @@ static size_t gen_lds(int ntab)
 {
     return (size_t)(gen_tab_floats(ntab) + 16 * kGenStage) * sizeof(float);
 }
+static size_t both_lds(int ntab) { return std::max(circ_lds(), gen_lds(ntab)); }
 // FP64 histogram (16-byte aligned), then the staged g and x of a circulant
 // knot tile, or the general stage.
 static size_t knot_hist_bytes(int ntab)
@@ -1881,6 +1932,11 @@ int prepare_launches(Plan &p)
     if ((rc = occupancy(k_general, gen_lds(p.desc.ntab), &p.occ_gen, kGenThreads))) return rc;
     size_t lds = 0;
     if ((rc = device_lds_limit(p.device, &lds))) return rc;
+    p.occ_both = 0;
+    if (!p.ctiles.empty() && !p.gtiles2.empty() &&
+        (rc = occupancy(p.circ_form ? k_both<true> : k_both<false>, both_lds(p.desc.ntab),
+                        &p.occ_both, kGenThreads)))
+        return rc;
     p.grid_kc = p.grid_kg = 0;
     if ((p.desc.flags & ARKCOS_PLAN_LEARNABLE) && p.desc.ntab <= ARKCOS_MAX_GRAD_NTAB) {
         if ((rc = occupancy(k_knot_circ, knot_circ_lds(p.desc.ntab), &p.occ_kc))) return rc;
@@ -1946,9 +2002,18 @@ int launch_forward(const Plan &p, const float *in, float *out, int nbatch, hipSt
     io.in[0] = in;
     io.out[0] = out;
     if (!counter) counter = p.d_counter;
-    hipLaunchKernelGGL(k_reset_counters, dim3(1), dim3(64), 0, s, counter);
     const int nct = (parts & ARKCOS_PART_CIRCULANT) ? (int)p.ctiles.size() : 0;
     const int ngt = (parts & ARKCOS_PART_GENERAL) ? (int)p.gtiles2.size() : 0;
+    const long long items = (long long)(nct + ngt) * nbatch;
+    if (nct > 0 && ngt > 0 && items <= (long long)kBothRounds * p.occ_both * p.cus) {
+        hipLaunchKernelGGL(p.circ_form ? k_both<true> : k_both<false>, dim3((unsigned)items),
+                           dim3(kGenThreads), both_lds(p.desc.ntab), s,
+                           (const DevPlanView *)p.d_view, in, out, ngt * nbatch, nbatch,
+                           gen_tab_floats(p.desc.ntab), circ_buf_floats());
+        ARKCOS_HIP_CHECK(hipGetLastError());
+        return ARKCOS_OK;
+    }
+    hipLaunchKernelGGL(k_reset_counters, dim3(1), dim3(64), 0, s, counter);
     if (nct > 0) {
         const int grid = std::max(1, std::min(nct * nbatch, p.occ_circ * p.cus));
         hipLaunchKernelGGL(p.circ_form ? k_circ_mfma : k_circ, dim3(grid), dim3(kThreads),

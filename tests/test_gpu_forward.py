@@ -226,6 +226,23 @@ def test_map_batches():
     assert rel_rms(yb[7], O.convolve(nside, tc, k, xb[7])) <= REL_RMS_TOL
 
 
+@pytest.mark.parametrize("nside,tc_deg,nb", [(64, 6.0, 60), (32, 30.3, 200)])
+def test_one_launch_equals_persistent_kernels(nside, tc_deg, nb):
+    """Calls of few (tile, map) items run both gathers in one launch, larger ones
+    as two persistent kernels: a map alone equals the same map in a large
+    batch bit for bit (vector and matrix form of the circulant rows)."""
+    tc = np.radians(tc_deg)
+    assert_tie_free(nside, tc)
+    k = W.gaussian_profile_knots(tc / 3, tc, 500)
+    xs = W.white_noise(nside, 41, nbatch=nb)
+    plan = _A().Plan(nside, tc, k, max_batch=nb)
+    ys = _conv_gpu(plan, xs)
+    for b in (0, 1, nb // 2, nb - 1):
+        assert np.array_equal(_conv_gpu(plan, xs[b]), ys[b]), b
+    assert np.array_equal(_conv_gpu(plan, xs[5:8]), ys[5:8])
+    assert rel_rms(ys[nb - 1], O.convolve(nside, tc, k, xs[nb - 1])) <= REL_RMS_TOL
+
+
 @pytest.mark.parametrize("nside,tc_deg", [(64, 6.0), (100, 3.31), (16, 74.7)])
 def test_parts_compose_to_full_convolution(nside, tc_deg):
     """The circulant and general gathers write disjoint rings: running them

@@ -140,7 +140,8 @@ struct DevTile2 {
     GenRing q[kGenMaxRings];
     int c_begin;
     int nchunks;
-    int pad[2];
+    int wide;      // the gather takes the matrix-core form
+    int pad;
 };
 static_assert(sizeof(DevTile2) == 128, "DevTile2 layout");
 // One staged chunk of a general tile: unwrapped positions c0 .. c0 + cn - 1
@@ -185,6 +186,12 @@ constexpr int kGenPixelsDefault = 128;
 constexpr int kGenQuadWindowDefault = 64;
 constexpr int kGenPairWindowDefault = 200;
 constexpr int kGenStage = 248;       // with a 16384-node table two workgroups fit a CU
+// General tiles of one or two rings whose rows average this many candidates run
+// their products on the matrix cores, 128 / nr pixels of each ring per tile.  Below,
+// the union of sixteen pixels' windows costs more than the products save: sixteen maps of
+// 5-30 arcmin in one call took 18.4 ms with 72 or more and 19.6 ms with 56; with 72
+// instead of 96, Nside 256 and 1000 arcmin went from 1630 to 1115 us.
+constexpr int kGenWideWindow = 72;
 constexpr int kMaxMaps = 32;
 // Circulant knot-gradient tiles: kKnotSeg pixels of a ring group.
 constexpr int kKnotSeg = 512;
@@ -313,7 +320,7 @@ struct Plan {
     int tile_source = 0;              // 0 defaults, 1 tuning cache, 2 descriptor
     // the general northern rings in order, for the general-gather tiling:
     // ring, pixels of its half-quadrant, tile flags, widest row window
-    std::vector<int> gen_ring, gen_lanes, gen_flags;
+    std::vector<int> gen_ring, gen_lanes, gen_flags, gen_wflags;
     std::vector<double> gen_wmax;
     std::vector<double> ring_cost;    // candidates per output pixel of each ring
     // Source rings read by the gathers (0-based, inclusive; all if src_hi < 0).

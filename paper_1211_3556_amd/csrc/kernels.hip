@@ -34,6 +34,7 @@
 #include <algorithm>
 #include <cstdint>
 #include <string>
+#include <type_traits>
 
 #include "arkcos_internal.hpp"
 
@@ -882,6 +883,272 @@ __device__ __forceinline__ void gen_tile2(const DevPlanView &P, const float *tab
     }
 }
 
+// ------------------------------------------------ general gather, wide rows --
+// Tiles whose rows average kGenWideWindow candidates or more.  There k_general is
+// bound by the sixteen FMAs of a candidate and its 64 bytes of LDS reads on top
+// of the weight; here the products run on the matrix cores as
+// v_mfma_f32_16x16x4f32 (FP32 in and out), which takes half the cycles of the
+// FMAs and reads 256 bytes of LDS per wave instead of 4096.  A wave takes sixteen
+// pixels of one ring: lane l evaluates the weight of pixel l & 15 and candidate l >> 4
+// of four consecutive source positions (A[pixel][candidate]), reads image l & 15 of
+// that position (B[candidate][image]) and receives D[4 (l >> 4) + c][l & 15], c = 0..3, the
+// sums of four pixels and one image.  The price is the union of the sixteen
+// pixels' windows, about eighteen candidates more per row.  A ring's waves beyond
+// its groups of sixteen pixels share the steps of a group.  Every instruction of a
+// step issues on the vector ALUs or the matrix cores, which do not overlap in one
+// SIMD, and they are busy all of the time: hence the untested middle of a row and the
+// form for rows beyond the break of a biased grid.  Nside 2048, 240 arcmin: 75 -> 66 ms
+// (105.5 -> 97.4 ms with the circulant rows); Nside 1024, 300 arcmin: 11.04 -> 10.28 ms.
+//
+// A zero weight still multiplies the staged value, so a NaN or an infinity
+// would reach pixels outside whose disc it lies: a tile that stages one returns
+// false before it writes, and runs in the vector form.
+constexpr int kWideFlush = 16;   // steps (64 FP32 terms) between moves into FP64
+
+// Whether every candidate of a row lies beyond the break of a biased grid (by
+// half a coarse node): its smallest separation, at m = 0, does.  Wave-uniform.
+template <bool LONG, int AM>
+__device__ __forceinline__ bool beyond_break(const DevPair &pp, const GenConst<AM> &gc)
+{
+    const float u = LONG ? node_coord<AM>(pp.A, gc.ucf)
+                         : (AM == 0 ? __builtin_amdgcn_sqrtf(pp.sq[0])
+                                    : node_coord<AM>(pp.sq[0], gc.ucf));
+    return __builtin_amdgcn_readfirstlane(fmaf(u, gc.br, gc.bc) >= 0.5f) != 0;
+}
+
+// T steps of one wave in a staged chunk, of which [h, e) lie inside every pixel's
+// window (no test there).  COARSE: every candidate of the row lies beyond
+// the break of a biased grid (the row's smallest separation does), as most rows of
+// a wide cut do, and needs no choice between the table's two pieces.
+template <bool LONG, int AM, bool INTM, bool BIAS, bool COARSE>
+__device__ __forceinline__ void wide_steps(const DevPair &pp, const GenConst<AM> &gc,
+                                           const float *tab, int m, int dm, int jv, int width,
+                                           int jstep, int sp, int sstep, int h, int e, int T,
+                                           double acc[4])
+{
+    const float A = LONG ? vreg(pp.A) : 0.0f;
+    const float B = LONG ? vreg(pp.B) : 0.0f;
+    const float xscale = LONG ? vreg(pp.xscale) : 0.0f;
+    const float q0 = LONG ? 0.0f : vreg(pp.sq[0]);
+    const float q1 = LONG ? 0.0f : vreg(pp.sq[1]);
+    const float q2 = LONG ? 0.0f : vreg(pp.sq[2]);
+    const float q3 = LONG ? 0.0f : vreg(pp.sq[3]);
+    const float q4 = (LONG || AM != 0) ? 0.0f : vreg(pp.sq[4]);
+    const UCoef &ucf = gc.ucf;
+    const float ms = LONG ? 1.0f : pp.mscale;
+    float mf = (float)m * ms;
+    const float dmf = vreg((float)dm * ms);
+    int mi = m;
+    const int dmi = vreg(dm);
+    const float mcut_f = vreg((float)pp.mcut * ms);
+    const unsigned mcut_u = (unsigned)vreg(pp.mcut);
+    typedef __attribute__((address_space(3))) const float lds_float;
+    const int tab_b = (int)(size_t)(lds_float *)tab;
+    const int tab_cb = BIAS ? vreg(tab_b + 4 * gc.kb) : tab_b;
+    const float zslot = COARSE ? gc.zslot - (float)gc.kb : gc.zslot;
+    const int js = vreg(jstep), ss = vreg(sstep);
+    circ_v4f d = {0.0f, 0.0f, 0.0f, 0.0f};
+    auto step = [&](auto check) {
+        constexpr bool CHECK = decltype(check)::value;
+        const float x = *(lds_float *)(size_t)sp;
+        float u0;
+        if (LONG) {
+            const float xx = (INTM ? (float)mi : mf) * xscale;
+            const float sx = sin_series(xx);
+            u0 = node_coord<AM>(fmaf(B, sx * sx, A), ucf);
+        } else if (AM == 0) {
+            const float y = mf * mf;
+            u0 = __builtin_amdgcn_sqrtf(fmaf(fmaf(fmaf(fmaf(y, q4, q3), y, q2), y, q1), y, q0));
+        } else {
+            const float y = mf * mf;
+            u0 = node_coord<AM>(fmaf(fmaf(fmaf(y, q3, q2), y, q1), y, q0), ucf);
+        }
+        const float v = BIAS ? fmaf(u0, gc.br, gc.bc) : 0.0f;
+        const bool coarse = BIAS && (COARSE || v >= 0.0f);
+        float uc = coarse ? v : u0;
+        int tb = coarse ? tab_cb : tab_b;
+        if (CHECK) {
+            bool keep = INTM ? (unsigned)mi + mcut_u <= 2u * mcut_u : fabsf(mf) <= mcut_f;
+            // (the union of whole-ring windows meets a source pixel twice)
+            if (LONG) keep = keep && (unsigned)jv <= (unsigned)width;
+            uc = keep ? uc : zslot;
+            if (BIAS && !COARSE) tb = keep ? tb : tab_b;
+        }
+        const int node = (int)uc;
+        const float frac = __builtin_amdgcn_fractf(uc);
+        lds_float *kp = (lds_float *)(size_t)(tb + 4 * node);
+        const float k0 = kp[0];
+        const float k1 = kp[1];
+        const float w = fmaf(frac, k1 - k0, k0);
+        d = __builtin_amdgcn_mfma_f32_16x16x4f32(w, x, d, 0, 0, 0);
+        sp += ss;
+        if (LONG) jv += js;
+        if (INTM)
+            mi -= dmi;
+        else
+            mf -= dmf;
+    };
+    auto flush = [&]() {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[c] += (double)d[c];
+        d = circ_v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    };
+    // the tested steps before and after the middle (one copy of the loop)
+#pragma unroll 1
+    for (int part = 0; part < 2; ++part) {
+        int n = part ? T - e : h;
+#pragma unroll 1
+        while (n > 0) {
+            const int k = min(n, kWideFlush);
+#pragma unroll 1
+            for (int t = 0; t < k; ++t) step(std::true_type{});
+            flush();
+            n -= k;
+        }
+        if (part) break;
+        n = e - h;
+#pragma unroll 1
+        while (n > 0) {
+            const int k = min(n, kWideFlush);
+#pragma unroll 1
+            for (int t = 0; t < k; ++t) step(std::false_type{});
+            flush();
+            n -= k;
+        }
+    }
+}
+
+// Zero for a finite v, NaN otherwise.
+__device__ __forceinline__ float nan_unless_finite(const float4 &v)
+{
+    return fmaf(0.0f, v.x, fmaf(0.0f, v.y, fmaf(0.0f, v.z, 0.0f * v.w)));
+}
+
+// 1 + the last chunk of a tile that staged a NaN or an infinity.
+__device__ __forceinline__ int &wide_bad()
+{
+    __shared__ int s_bad;
+    return s_bad;
+}
+
+template <bool LONG, int AM, bool INTM, bool BIAS>
+__device__ __forceinline__ bool gen_tile_wide(const DevPlanView &P, const float *tab, float4 *stage,
+                                              const DevTile2 *Tp, const float *in, float *out)
+{
+    int &s_bad = wide_bad();
+    const int lane = (int)threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int per = kGenThreads / 64 / cst(Tp)->nr;   // waves of a ring
+    const int h = wave / per, wv = wave - h * per;
+    const GenRing my = cst(Tp->q)[h];
+    const int rn = my.r, rs = P.nrings - 1 - rn;
+    const DevRing R = cst(P.rings)[rn];
+    // sixteen-pixel groups (at most one per wave) and the waves that share each
+    const int ngr = max(1, (my.len + 15) >> 4);
+    int ls = 0;   // a group's waves: 2^ls
+    while ((2 * ngr << ls) <= per) ++ls;
+    const int nsub = 1 << ls;
+    const int grp = wv % ngr, sub = wv / ngr;
+    const bool busy = my.len > 0 && sub < nsub;   // (wave-uniform)
+    const int p0 = 16 * grp;
+    const int j = cst(Tp)->j0 + min(p0 + (lane & 15), max(my.len - 1, 0));
+    const GenConst<AM> gc(P);
+    const cptr<GenChunk> C = cst(P.gchunks) + cst(Tp)->c_begin;
+    const int nch = cst(Tp)->nchunks;
+    float4 pa, pb, pc, pd;
+    GenChunk ch{};
+    auto load = [&](const GenChunk &c) {
+        pa = pb = pc = pd = make_float4(0.0f, 0.0f, 0.0f, 0.0f);   // rows past the chunk
+        prefetch_chunk<0>(in, c, pa, pb, pc, pd);
+    };
+    if (nch > 0) {
+        ch = C[0];
+        load(ch);
+    }
+    if (threadIdx.x == 0) s_bad = 0;
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    typedef __attribute__((address_space(3))) const float lds_float;
+    const int stage_b = (int)(size_t)(lds_float *)(const float *)stage;
+    for (int k = 0; k < nch; ++k) {
+        const GenChunk nx = C[min(k + 1, nch - 1)];
+        const int rows = (ch.cn + 3) & ~3;
+        __syncthreads();      // the previous chunk is no longer read
+        if ((int)threadIdx.x < rows) {
+            stage[threadIdx.x] = pa;
+            stage[kGenStage + threadIdx.x] = pb;
+            stage[2 * kGenStage + threadIdx.x] = pc;
+            stage[3 * kGenStage + threadIdx.x] = pd;
+        }
+        const float z = (nan_unless_finite(pa) + nan_unless_finite(pb)) +
+                        (nan_unless_finite(pc) + nan_unless_finite(pd));
+        if (__any(z != 0.0f) && lane == 0) s_bad = k + 1;
+        __syncthreads();
+        if (s_bad == k + 1) return false;
+        if (k + 1 < nch) load(nx);
+        if (busy && ch.s >= my.s_lo && ch.s <= my.s_hi) {
+            const DevPair pp = cst(P.pairs)[my.pb + ch.s - my.s_lo];
+            int lo, hi;
+            pair_window(pp, ch.n, j, lo, hi);
+            // windows move up with the pixel: the group's union
+            const int glo = __builtin_amdgcn_readlane(lo, 0);
+            const int ghi = __builtin_amdgcn_readlane(hi, 15);
+            const int a0 = max(glo - ch.c0, 0), a1 = min(ghi - ch.c0, ch.cn - 1);
+            const int all = a1 >= a0 ? (a1 - a0 + 4) >> 2 : 0;   // steps of the group
+            const int T = all > sub ? ((all - sub - 1) >> ls) + 1 : 0;
+            // inside the staged rows, whose length is a multiple of four; what a
+            // pixel meets outside its window has weight zero
+            const int s0 = min(a0, rows - 4 * all) + 4 * sub;
+            // steps inside the window of every pixel of the group (one position in from
+            // the ends, which are widened for the centre's rounding)
+            const int cl = __builtin_amdgcn_readlane(lo, 15) + 1 - ch.c0;
+            const int cr = min(__builtin_amdgcn_readlane(hi, 0) - 1 - ch.c0, ch.cn - 1);
+            const int h = min(max((cl - s0 + 4 * nsub - 1) >> (ls + 2), 0), T);
+            const int e = min(max(((cr - 3 - s0) >> (ls + 2)) + 1, h), T);
+            const int sl = s0 + (lane >> 4);
+            const int jq = ch.c0 + sl;
+            const int m0 = lon_numerator(lon_base(j, R.two_o, ch.n), jq, ch.two_o, R.n);
+            const int sp = stage_b + 16 * (((lane >> 2) & 3) * kGenStage + sl) + 4 * (lane & 3);
+            const int dm = 8 * nsub * R.n;
+            if (T > 0 && BIAS && beyond_break<LONG, AM>(pp, gc)) {
+                wide_steps<LONG, AM, INTM, BIAS, BIAS>(pp, gc, tab, m0, dm, jq - lo, hi - lo,
+                                                       4 * nsub, sp, 64 * nsub, h, e, T, acc);
+            } else if (T > 0) {
+                wide_steps<LONG, AM, INTM, BIAS, false>(pp, gc, tab, m0, dm, jq - lo, hi - lo,
+                                                        4 * nsub, sp, 64 * nsub, h, e, T, acc);
+            }
+        }
+        ch = nx;
+    }
+    // the other waves' shares, in order (both barriers for every wave: the parts of
+    // a tile may differ in nsub)
+    __syncthreads();
+    if (busy && sub > 0) {
+        double *part = reinterpret_cast<double *>(stage);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) part[((wave - 1) * 4 + c) * 64 + lane] = acc[c];
+    }
+    __syncthreads();
+    if (!busy || sub > 0) return true;
+    for (int u = 1; u < nsub; ++u)
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            acc[c] += reinterpret_cast<const double *>(stage)[((wave + u * ngr - 1) * 4 + c) * 64 +
+                                                             lane];
+    // image (lane & 15) of the pixels 4 (lane >> 4) + c: quarter turn (lane & 3) of the
+    // pixel or its reflection (lane & 8), on the ring or its mirror (lane & 4)
+    const bool south = (lane & 4) != 0, refl = (lane & 8) != 0;
+    const int qr = R.n >> 2;
+    if ((my.flags & (south ? kTileSkipSouth : kTileSkipNorth)) || (south && rs == rn)) return true;
+    float *o = out + cst(P.rings)[south ? rs : rn].first + (lane & 3) * qr;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const int p = p0 + 4 * (lane >> 4) + c;
+        const int jp = cst(Tp)->j0 + p, jb = qr - R.two_o - jp;
+        if (p < my.len && !(refl && (jb == jp || jb == qr))) o[refl ? jb : jp] = (float)acc[c];
+    }
+    return true;
+}
+
 // The candidate-loop form of a tile: sine series, angle series and numerator
 // type from the tile and plan, the node-grid map from BIAS.
 template <bool BIAS>
@@ -896,6 +1163,21 @@ __device__ __forceinline__ void gen_tile_variant(const DevPlanView &P, const flo
         if (q.len > 0) skip_all &= q.flags;
     }
     const bool lg = (fl & kTileLongSin) != 0;
+    if (cst(Tp)->wide) {
+        bool done = false;
+        switch (P.angle_mode * 3 + ((fl & kTileIntM) ? 2 : (lg ? 1 : 0))) {
+            case 0: done = gen_tile_wide<false, 0, false, BIAS>(P, tab, stage, Tp, in, out); break;
+            case 1: done = gen_tile_wide<true, 0, false, BIAS>(P, tab, stage, Tp, in, out); break;
+            case 2: done = gen_tile_wide<true, 0, true, BIAS>(P, tab, stage, Tp, in, out); break;
+            case 3: done = gen_tile_wide<false, 1, false, BIAS>(P, tab, stage, Tp, in, out); break;
+            case 4: done = gen_tile_wide<true, 1, false, BIAS>(P, tab, stage, Tp, in, out); break;
+            case 5: done = gen_tile_wide<true, 1, true, BIAS>(P, tab, stage, Tp, in, out); break;
+            case 6: done = gen_tile_wide<false, 2, false, BIAS>(P, tab, stage, Tp, in, out); break;
+            case 7: done = gen_tile_wide<true, 2, false, BIAS>(P, tab, stage, Tp, in, out); break;
+            default: done = gen_tile_wide<true, 2, true, BIAS>(P, tab, stage, Tp, in, out); break;
+        }
+        if (done) return;
+    }
     if (fl & kTileIntM) {   // wide windows on large rings (long sine implied)
         switch (P.angle_mode) {
             case 0: gen_tile2<true, 0, true, BIAS, 0>(P, tab, stage, Tp, in, out); break;

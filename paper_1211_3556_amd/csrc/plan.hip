@@ -279,7 +279,6 @@ static void build_gen_chunks(Plan &P)
 // tuner can re-tile a plan without rebuilding it.
 void build_gen_tiles(Plan &P)
 {
-    const int seg = P.tiles.gen_pixels;
     const double quad_max = P.tiles.gen_quad_window;   // -1: never
     const double pair_max = P.tiles.gen_pair_window;
     const std::vector<int> &gring = P.gen_ring, &glanes = P.gen_lanes, &gflags = P.gen_flags;
@@ -307,19 +306,31 @@ void build_gen_tiles(Plan &P)
     for (size_t g = 0; g < gring.size();) {
         const int nr = run_of(g, 4, 0) ? 4 : (run_of(g, 2, 1) ? 2 : 1);
         int lanes = 0;
-        for (int i = 0; i < nr; ++i) lanes = std::max(lanes, glanes[g + i]);
+        double rows = 0.0, cands = 0.0;   // of a pixel of each ring
+        int skip = kTileSkipNorth | kTileSkipSouth;
+        for (int i = 0; i < nr; ++i) {
+            lanes = std::max(lanes, glanes[g + i]);
+            const DevRing &dr = P.dev_rings[gring[g + i]];
+            rows += dr.pair_end - dr.pair_begin;
+            cands += P.ring_cost[gring[g + i]];
+            skip &= gflags[g + i];
+        }
+        // (tiles that write one side only have a vector form at half the cost)
+        const bool wide = nr <= 2 && !skip && cands >= kGenWideWindow * rows;
+        const int seg = wide ? std::min(P.tiles.gen_pixels, kGenLanes / nr) : P.tiles.gen_pixels;
         for (int j0 = 0; j0 < lanes; j0 += seg) {
             DevTile2 t{};
             double c = 1.0;
             t.nr = nr;
             t.j0 = j0;
+            t.wide = wide;
             t.s_first = 0x7fffffff;
             t.s_last = -1;
             for (int h = 0; h < kGenMaxRings; ++h) {
                 GenRing &q = t.q[h];
                 q.r = h < nr ? gring[g + h] : gring[g];
                 q.len = h < nr ? std::max(0, std::min(seg, glanes[g + h] - j0)) : 0;
-                q.flags = h < nr ? gflags[g + h] : 0;
+                q.flags = h < nr ? (wide ? P.gen_wflags : gflags)[g + h] : 0;
                 q.s_lo = 0;
                 q.s_hi = -1;
                 if (q.len > 0) {
@@ -542,6 +553,7 @@ static int build_plan(Plan &P)
     P.gen_ring.clear();
     P.gen_lanes.clear();
     P.gen_flags.clear();
+    P.gen_wflags.clear();
     P.gen_wmax.clear();
     for (int r = 0; r <= P.nrings - 1 - r; ++r) {
         if (!general[r]) continue;
@@ -553,6 +565,7 @@ static int build_plan(Plan &P)
         // runs past a lane's window (at most 64 lanes per pixel, +4 for the
         // spread of windows across a wave)
         int flags = force_int_m ? (kTileIntM | kTileLongSin) : 0;
+        int wflags = 0;
         if (!in_range(r)) flags |= kTileSkipNorth;
         if (!in_range(rm)) flags |= kTileSkipSouth;
         for (int k = P.dev_rings[r].pair_begin; k < P.dev_rings[r].pair_end; ++k) {
@@ -560,6 +573,9 @@ static int build_plan(Plan &P)
             if (pp.mode & kPairLongSin) flags |= kTileLongSin;
             const double W = (pp.mode & kPairWhole) ? 0.5 * P.rings[pp.s].n + 1.0 : pp.w + 1.0;
             if (2.0 * P.rings[r].n * (W + 70.0) >= 16777216.0) flags |= kTileIntM | kTileLongSin;
+            // (wide tiles: the union of sixteen pixels' windows, pixel spacing n_s / n_r)
+            if (2.0 * P.rings[r].n * (W + 70.0) + 32.0 * P.rings[pp.s].n >= 16777216.0)
+                wflags |= kTileIntM | kTileLongSin;
         }
         for (int j0 = 0; j0 < lanes; j0 += kGenLanes) {
             DevTile t{};
@@ -579,6 +595,7 @@ static int build_plan(Plan &P)
         P.gen_ring.push_back(r);
         P.gen_lanes.push_back(lanes);
         P.gen_flags.push_back(flags);
+        P.gen_wflags.push_back(flags | wflags);
         P.gen_wmax.push_back(wmax);
     }
     sort_by_cost(P.gtiles, cost);

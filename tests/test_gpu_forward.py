@@ -243,6 +243,44 @@ def test_one_launch_equals_persistent_kernels(nside, tc_deg, nb):
     assert rel_rms(ys[nb - 1], O.convolve(nside, tc, k, xs[nb - 1])) <= REL_RMS_TOL
 
 
+@pytest.mark.parametrize("nside,tc_deg,biased", [(64, 74.7, False), (64, 60.1, True),
+                                                 (96, 40.3, True), (150, 27.7, False)])
+def test_wide_rows(nside, tc_deg, biased):
+    """Rows wide enough for the matrix-core form of the general gather: whole rings,
+    both sine forms, both node grids, the angle series and short last segments
+    (the table falls to zero at the cut, so that lattice ties there do not count).
+    A NaN and an infinity reach the pixels whose disc they lie in, and none beyond
+    the pixels next to those."""
+    A = _A()
+    tc = np.radians(tc_deg)
+    ntab = 700
+    kw = {}
+    nodes = None
+    theta = np.linspace(0.0, tc, ntab)
+    if biased:
+        kw["theta_break"], kw["k_break"] = A.paper_bias(tc, ntab)
+        nodes = theta = O.biased_nodes(tc, ntab)
+    k = W.gaussian_profile_at(tc / 2, theta) * (1.0 - theta / tc)
+    x = W.white_noise(nside, 47)
+    plan = A.Plan(nside, tc, k, **kw)
+    y = _conv_gpu(plan, x)
+    pix = np.unique(np.random.default_rng(3).integers(0, 12 * nside ** 2, 300))
+    ref = O.convolve(nside, tc, k, x, nodes=nodes, pixels=pix)
+    assert rel_rms(y[pix], ref) <= REL_RMS_TOL
+    bad = np.array(x)
+    at = [2 * 3 * 4 + 5, 2 * nside * (nside - 1) + 7]   # near the pole, first belt ring
+    bad[at] = np.nan, np.inf
+    yb = _conv_gpu(plan, bad)[pix]
+    delta = np.zeros(x.shape)
+    delta[at] = 1.0
+    step = 2.0 / nside
+    inner = O.convolve(nside, tc - step, np.ones(16), delta, pixels=pix) != 0
+    outer = O.convolve(nside, tc + step, np.ones(16), delta, pixels=pix) != 0
+    assert inner.any() and not np.any(np.isfinite(yb[inner]))
+    assert (~outer).any() and np.all(np.isfinite(yb[~outer]))
+    assert rel_rms(yb[~outer], ref[~outer]) <= REL_RMS_TOL
+
+
 @pytest.mark.parametrize("nside,tc_deg", [(64, 6.0), (100, 3.31), (16, 74.7)])
 def test_parts_compose_to_full_convolution(nside, tc_deg):
     """The circulant and general gathers write disjoint rings: running them

@@ -394,8 +394,8 @@ def main() -> int:
         nalm = (L + 1) * (L + 2) // 2
         # algorithmic FP64 FLOP: belt rings of power-of-two length 4 Nside by
         # real FFTs (complex FFT of half the length, 5 M log2 M each way),
-        # the other rings by Goertzel and Clenshaw (3 per pixel and m each
-        # way); Legendre recurrence 4 plus 2 (analysis) or 4 (synthesis) per
+        # the other rings by direct sums (3 per pixel and m each way, a
+        # nominal count that the cap rings' FFTs undercut); Legendre recurrence 4 plus 2 (analysis) or 4 (synthesis) per
         # (l, m, northern ring)
         nb = 4 * s.nside
         M = nb // 2

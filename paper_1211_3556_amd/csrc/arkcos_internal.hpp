@@ -372,6 +372,7 @@ struct Plan {
     int knot_maps = 1;                  // and its maps per item
     long long device_bytes = 0;
 
+    bool wide_tiles = false;            // some general tile takes the matrix-core form
     DevPlanView view() const;
 };
 
@@ -380,6 +381,7 @@ struct Batch {
     std::vector<int2> cmap;             // circulant tiles of all plans: (plan, tile), those of
                                         // vector-form plans first, each part longest first
     int ncirc_valu = 0;                 // tiles of vector-form plans at the front of cmap
+    bool wide_tiles = false;            // some plan's general tiles take the matrix-core form
     std::vector<int2> gmap;             // general tiles of all plans
     int2 *d_cmap = nullptr;
     int2 *d_gmap = nullptr;

@@ -188,6 +188,7 @@ int arkcos_batch_create(const arkcos_plan_t *plans, int nmaps, arkcos_batch_t *o
         B->plans.push_back(P);
         B->max_ntab = std::max(B->max_ntab, P->desc.ntab);
         B->max_taps = std::max(B->max_taps, P->max_taps);
+        B->wide_tiles = B->wide_tiles || P->wide_tiles;
         views.push_back(P->view());
         for (int t = 0; t < (int)P->ctiles.size(); ++t) {
             (P->circ_form ? cmap_m : B->cmap).push_back(make_int2(k, t));

@@ -1151,7 +1151,7 @@ __device__ __forceinline__ bool gen_tile_wide(const DevPlanView &P, const float 
 
 // The candidate-loop form of a tile: sine series, angle series and numerator
 // type from the tile and plan, the node-grid map from BIAS.
-template <bool BIAS>
+template <bool BIAS, bool WIDE>
 __device__ __forceinline__ void gen_tile_variant(const DevPlanView &P, const float *tab,
                                                  float4 *stage, const DevTile2 *Tp,
                                                  const float *in, float *out)
@@ -1163,7 +1163,7 @@ __device__ __forceinline__ void gen_tile_variant(const DevPlanView &P, const flo
         if (q.len > 0) skip_all &= q.flags;
     }
     const bool lg = (fl & kTileLongSin) != 0;
-    if (cst(Tp)->wide) {
+    if (WIDE && cst(Tp)->wide) {
         bool done = false;
         switch (P.angle_mode * 3 + ((fl & kTileIntM) ? 2 : (lg ? 1 : 0))) {
             case 0: done = gen_tile_wide<false, 0, false, BIAS>(P, tab, stage, Tp, in, out); break;
@@ -1212,6 +1212,9 @@ __device__ __forceinline__ void gen_tile_variant(const DevPlanView &P, const flo
 // segment) x maps.  LDS: the node table of the current plan followed by two
 // zero entries (the slot of candidates outside the disc), then the stage.
 // The loads of the next chunk are in flight while the current one is used.
+// WIDE: some tile takes the matrix-core form (its registers cost launches without
+// one 1 %: Nside 2048, 20 arcmin, 1002 against 1009 us).
+template <bool WIDE>
 __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(4)))
 void k_general(const DevPlanView *__restrict__ views, const int2 *__restrict__ tile_map,
                int ntiles, MapIO io, int nmaps, int tab_floats, unsigned int *counter)
@@ -1239,9 +1242,9 @@ void k_general(const DevPlanView *__restrict__ views, const int2 *__restrict__ t
         const float *in = io.in[pi] + (size_t)map * P.npix;
         float *out = io.out[pi] + (size_t)map * P.npix;
         if (P.biased)
-            gen_tile_variant<true>(P, tab, stage, Tp, in, out);
+            gen_tile_variant<true, WIDE>(P, tab, stage, Tp, in, out);
         else
-            gen_tile_variant<false>(P, tab, stage, Tp, in, out);
+            gen_tile_variant<false, WIDE>(P, tab, stage, Tp, in, out);
     }
 }
 
@@ -1257,7 +1260,7 @@ void k_general(const DevPlanView *__restrict__ views, const int2 *__restrict__ t
 // four maps, 3332 tiles: 134 against 138 us; Nside 1024, 30 arcmin, 2700: 235 against 259;
 // Nside 2048, 10 arcmin: 398 against 546).
 constexpr int kBothRounds = 4;
-template <bool MF>
+template <bool MF, bool WIDE>
 __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(4)))
 void k_both(const DevPlanView *__restrict__ views, const float *in, float *out, int ngen, int nmaps,
             int tab_floats, int buf_floats)
@@ -1273,9 +1276,9 @@ void k_both(const DevPlanView *__restrict__ views, const float *in, float *out, 
         if (threadIdx.x < 2) lds[P.ntab + threadIdx.x] = 0.0f;
         float4 *stage = reinterpret_cast<float4 *>(lds + tab_floats);
         if (P.biased)
-            gen_tile_variant<true>(P, lds, stage, P.gtiles2 + ti, in + at, out + at);
+            gen_tile_variant<true, WIDE>(P, lds, stage, P.gtiles2 + ti, in + at, out + at);
         else
-            gen_tile_variant<false>(P, lds, stage, P.gtiles2 + ti, in + at, out + at);
+            gen_tile_variant<false, WIDE>(P, lds, stage, P.gtiles2 + ti, in + at, out + at);
     } else if ((int)threadIdx.x < kThreads) {   // (the barriers count the waves that are left)
         float *wls = lds + 2 * buf_floats;
         circ_zero_ends(wls);
@@ -2205,19 +2208,29 @@ static KnotLaunch knot_launch(const Plan &p, int nmaps)
     return k;
 }
 
+static auto both_kernel(bool mfma, bool wide) -> decltype(&k_both<true, true>)
+{
+    if (wide) return mfma ? k_both<true, true> : k_both<false, true>;
+    return mfma ? k_both<true, false> : k_both<false, false>;
+}
+
 int prepare_launches(Plan &p)
 {
     ARKCOS_HIP_CHECK(hipDeviceGetAttribute(&p.cus, hipDeviceAttributeMultiprocessorCount,
                                            p.device));
     int rc;
     if ((rc = occupancy(p.circ_form ? k_circ_mfma : k_circ, circ_lds(), &p.occ_circ))) return rc;
-    if ((rc = occupancy(k_general, gen_lds(p.desc.ntab), &p.occ_gen, kGenThreads))) return rc;
+    // (both forms: the tuner may re-tile the plan; two workgroups per CU either way)
+    if ((rc = occupancy(k_general<true>, gen_lds(p.desc.ntab), &p.occ_gen, kGenThreads))) return rc;
+    if ((rc = occupancy(k_general<false>, gen_lds(p.desc.ntab), &p.occ_gen, kGenThreads))) return rc;
     size_t lds = 0;
     if ((rc = device_lds_limit(p.device, &lds))) return rc;
     p.occ_both = 0;
     if (!p.ctiles.empty() && !p.gtiles2.empty() &&
-        (rc = occupancy(p.circ_form ? k_both<true> : k_both<false>, both_lds(p.desc.ntab),
-                        &p.occ_both, kGenThreads)))
+        ((rc = occupancy(both_kernel(p.circ_form, true), both_lds(p.desc.ntab), &p.occ_both,
+                         kGenThreads)) ||
+         (rc = occupancy(both_kernel(p.circ_form, false), both_lds(p.desc.ntab), &p.occ_both,
+                         kGenThreads))))
         return rc;
     p.grid_kc = p.grid_kg = 0;
     if ((p.desc.flags & ARKCOS_PLAN_LEARNABLE) && p.desc.ntab <= ARKCOS_MAX_GRAD_NTAB) {
@@ -2251,7 +2264,9 @@ int prepare_batch(Batch &b)
     int occ_c = 0, occ_m = 0, occ_g = 0, rc;
     if ((rc = occupancy(k_circ, circ_lds(), &occ_c))) return rc;
     if ((rc = occupancy(k_circ_mfma, circ_lds(), &occ_m))) return rc;
-    if ((rc = occupancy(k_general, gen_lds(b.max_ntab), &occ_g, kGenThreads))) return rc;
+    if ((rc = occupancy(b.wide_tiles ? k_general<true> : k_general<false>, gen_lds(b.max_ntab), &occ_g,
+                        kGenThreads)))
+        return rc;
     b.grid_circ = std::max(1, std::min(b.ncirc_valu, occ_c * b.cus));
     b.grid_circ_mfma = std::max(1, std::min((int)b.cmap.size() - b.ncirc_valu, occ_m * b.cus));
     b.grid_gen = std::max(1, std::min((int)b.gmap.size(), occ_g * b.cus));
@@ -2288,7 +2303,7 @@ int launch_forward(const Plan &p, const float *in, float *out, int nbatch, hipSt
     const int ngt = (parts & ARKCOS_PART_GENERAL) ? (int)p.gtiles2.size() : 0;
     const long long items = (long long)(nct + ngt) * nbatch;
     if (nct > 0 && ngt > 0 && items <= (long long)kBothRounds * p.occ_both * p.cus) {
-        hipLaunchKernelGGL(p.circ_form ? k_both<true> : k_both<false>, dim3((unsigned)items),
+        hipLaunchKernelGGL(both_kernel(p.circ_form, p.wide_tiles), dim3((unsigned)items),
                            dim3(kGenThreads), both_lds(p.desc.ntab), s,
                            (const DevPlanView *)p.d_view, in, out, ngt * nbatch, nbatch,
                            gen_tab_floats(p.desc.ntab), circ_buf_floats());
@@ -2304,7 +2319,8 @@ int launch_forward(const Plan &p, const float *in, float *out, int nbatch, hipSt
     }
     if (ngt > 0) {
         const int grid = std::max(1, std::min(ngt * nbatch, p.occ_gen * p.cus));
-        hipLaunchKernelGGL(k_general, dim3(grid), dim3(kGenThreads), gen_lds(p.desc.ntab), s,
+        hipLaunchKernelGGL(p.wide_tiles ? k_general<true> : k_general<false>, dim3(grid),
+                           dim3(kGenThreads), gen_lds(p.desc.ntab), s,
                            (const DevPlanView *)p.d_view, (const int2 *)nullptr, ngt, io, nbatch,
                            gen_tab_floats(p.desc.ntab), counter + 1);
     }
@@ -2415,7 +2431,8 @@ int launch_batch(const Batch &b, const float *const *in, float *const *out, hipS
                            (const DevPlanView *)b.d_views, (const int2 *)b.d_cmap + b.ncirc_valu,
                            ncm, io, 1, circ_buf_floats(), b.d_counter + 2);
     if (!b.gmap.empty() && (parts & ARKCOS_PART_GENERAL))
-        hipLaunchKernelGGL(k_general, dim3(b.grid_gen), dim3(kGenThreads), gen_lds(b.max_ntab), s,
+        hipLaunchKernelGGL(b.wide_tiles ? k_general<true> : k_general<false>, dim3(b.grid_gen),
+                           dim3(kGenThreads), gen_lds(b.max_ntab), s,
                            (const DevPlanView *)b.d_views, (const int2 *)b.d_gmap,
                            (int)b.gmap.size(), io, 1, gen_tab_floats(b.max_ntab), b.d_counter + 1);
     ARKCOS_HIP_CHECK(hipGetLastError());

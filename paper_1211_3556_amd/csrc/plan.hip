@@ -353,6 +353,8 @@ void build_gen_tiles(Plan &P)
         }
         g += nr;
     }
+    P.wide_tiles = false;
+    for (const DevTile2 &t : P.gtiles2) P.wide_tiles = P.wide_tiles || t.wide;
     sort_by_cost(P.gtiles2, cost);
     P.gtile2_cost = cost;
     build_gen_chunks(P);

@@ -459,9 +459,10 @@ int arkcos_tune(const arkcos_plan_desc *desc, int reps, const char *cache_path,
  * arkcos_harm_create: Nside 1..ARKCOS_MAX_NSIDE, lcut 0..ARKCOS_MAX_LCUT
  * (EUNSUPPORTED above), khat host FP64 of lcut+1 values (copied), max_batch
  * >= 1.  Allocates device memory on the current device (synchronously):
- * longitude sums (lcut+1) x 2 Nside ring pairs (even and odd parts, complex
- * FP64) of the maps that pass together (512 MB at most beyond the first), per-chunk
- * partial coefficients, recurrence tables and chirp spectra.  EINVAL, ENOMEM, EDEVICE.
+ * a workspace per map of longitude sums, (lcut+1) x 2 Nside ring pairs (even and
+ * odd parts, complex FP64), and per-chunk partial coefficients; as many maps pass
+ * together as fit 512 MB of it, at least one.  Then recurrence tables and chirp
+ * spectra (up to 360 MB at Nside 4096 and above).  EINVAL, ENOMEM, EDEVICE.
  */
 int arkcos_harm_create(int nside, int lcut, const double *khat, int max_batch,
                        arkcos_harm_t *out);

@@ -1520,9 +1520,12 @@ static int harm_build(Harm &h)
     }
     h.lq = ((L >> 2) + 8) & ~7;
     // maps that pass through the kernels together: small maps fill the chip only
-    // as a group, and a group's rows stay below 512 MB
+    // as a group, and a group's workspace (rows, partial sums and coefficients, of
+    // which the last two grow as lcut^2 at any Nside) stays below 512 MB
     const size_t rows = (size_t)h.nnorth * 8 * h.lq * sizeof(double2);
-    h.nmaps = (int)std::max<size_t>(1, std::min<size_t>({(size_t)h.max_batch, 64, (512u << 20) / rows}));
+    const size_t coefs = (size_t)(h.nchunk + 1) * h.nsteps * sizeof(double4);
+    h.nmaps = (int)std::max<size_t>(
+        1, std::min<size_t>({(size_t)h.max_batch, 64, (512u << 20) / (rows + coefs)}));
     ARKCOS_HIP_CHECK(hipGetDevice(&h.device));
     int rc;
     if ((rc = harm_upload(&h.d_rings, rings, &h.device_bytes))) return rc;

@@ -102,6 +102,18 @@ def test_harmonic_long_ring_ffts(monkeypatch, nside, lcut):
     assert rel_rms(y, ref) <= 2.0 ** -24
 
 
+@pytest.mark.parametrize("nside,lcut", [(8, 4095), (64, 4095), (64, 2000), (256, 300)])
+def test_harmonic_workspace_bound(nside, lcut):
+    """The workspace of the maps that pass together is 512 MB at most beyond one
+    map's, coefficients (which grow as lcut^2 at any Nside) included."""
+    A = _A()
+    log("harmonic workspace Nside %d lcut %d" % (nside, lcut))
+    khat = np.ones(lcut + 1)
+    one = A.Harm(nside, khat).info()["device_bytes"]
+    many = A.Harm(nside, khat, max_batch=64).info()["device_bytes"]
+    assert one <= many <= one + (512 << 20)
+
+
 def test_harmonic_batch_and_accumulate():
     import torch
     nside, lcut = 16, 40

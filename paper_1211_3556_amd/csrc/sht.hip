@@ -17,7 +17,7 @@
 //  1. k_ring_fwd      per ring pair: the longitude sums of z = e + i o,
 //                     Z(m) = sum_j z_j e^{-i m phi_j} for m = -lcut .. lcut,
 //                     by FFTs of a quarter of the ring (k_sht_dft_fwd, direct
-//                     sums, for the rings the FFT does not reach);
+//                     sums, at low lcut and on small maps);
 //  2. k_leg_fwd       per (m, chunk of ring pairs): Legendre functions by a
 //                     two-degree recurrence, times E(m) and O(m), reduced over
 //                     the rings into per-chunk partial sums;
@@ -72,10 +72,8 @@ struct ShtFftRing {
 };
 
 constexpr int kShtThreads = 256;
-constexpr int kShtChunk = 2048;     // samples of a ring pair staged per pass (FP64)
-constexpr int kShtMaxFreq = 8;      // frequencies per thread and pass in k_sht_dft_fwd
-constexpr int kShtPairs = 2;        // pixel pairs per thread in k_sht_dft_bwd
-constexpr double kShtDirectWork = 6e7;   // pixels x orders up to which rings are summed directly
+constexpr int kShtMaxPairs = 4;     // pairs of orders per thread and pass in k_sht_dft_fwd
+constexpr double kShtDirectWork = 6e7;   // pixels x orders up to which every ring is summed directly
 constexpr int kShtMaxK = 4096;      // longest quarter ring the FFTs take
 constexpr int kLegBlock = 4;        // recurrence steps (two degrees each) per reduction
 constexpr int kLegFwdRings = 8;     // ring pairs per lane of k_leg_fwd on large maps
@@ -694,24 +692,26 @@ void k_ring_bwd(const ShtRing *__restrict__ rings, const ShtFftRing *__restrict_
 }
 
 // --------------------------------------------------- direct ring sums --
-// For quarter rings longer than kShtMaxK that are not a power of two (and all
-// rings under ARKCOS_SHT_NO_FFT).
-// Goertzel: s_j = x_j + 2 cos(w) s_{j-1} - s_{j-2}; after n samples
-// sum_j x_j e^{-i w j} = e^{i w} s_{n-1} - s_{n-2}, for the samples e and o of a
-// ring pair.  Two samples per step update (s1, s2) in place: s2 <- c s1 + x_j -
-// s2, s1 <- c s2 + x_{j+1} - s1.  Ring lengths are multiples of 4, so every
-// staged count is even.  One launch covers frequencies m = m0 + thread + k
-// kShtThreads, k < K.
+// For rings on which the FFTs are the longer way (see ring_direct).  With the folds of
+// the FFTs, real for each of e and o: a_0 = s_0 + s_1 + s_2 + s_3 and a_2 = s_0 - s_1 +
+// s_2 - s_3 for the classes 0 and 2, p = s_0 - s_2 and q = s_1 - s_3 for the classes
+// 1 (p - i q) and 3 (p + i q), s_t the samples of quarter t.  Goertzel on the k samples of a
+// fold: s_j = x_j + 2 cos(w) s_{j-1} - s_{j-2}, and sum_j x_j e^{-i w j} =
+// e^{-i w (k-1)} (s_{k-1} - e^{-i w} s_{k-2}).  Two samples per step update (s1, s2) in
+// place: s2 <- c s1 + x_j - s2, s1 <- c s2 + x_{j+1} - s1.  A thread takes the orders 2p and
+// 2p + 1, six real sums of length n/4 (against four of length n without the folds), for K
+// values of p; waves past lcut only stage.  One launch covers p = p0 .. p0 + K kShtThreads - 1.
+// FP64 issue bounds it.
 template <int K>
 __global__ __launch_bounds__(kShtThreads) void k_sht_dft_fwd(const ShtRing *__restrict__ rings,
                                                              const int *__restrict__ ring_list,
                                                              const double2 *__restrict__ roots,
                                                              const float *__restrict__ x,
                                                              long long npix,
-                                                             double2 *__restrict__ F, int m0,
+                                                             double2 *__restrict__ F, int p0,
                                                              int L, int lq, int nnorth)
 {
-    __shared__ double2 sx[kShtChunk];   // (e, o) of a sample
+    __shared__ double2 sx[4 * kShtThreads];   // a_0, a_2, p, q of a sample, each (e, o)
     __shared__ double2 rt[kRoots];
     load_roots(rt, roots);
     const int r = ring_list[blockIdx.x];
@@ -719,54 +719,123 @@ __global__ __launch_bounds__(kShtThreads) void k_sht_dft_fwd(const ShtRing *__re
     const bool equator = r == nnorth - 1;
     const float *xa = x + (size_t)blockIdx.y * npix + R.first;
     const float *xb = x + (size_t)blockIdx.y * npix + rings[2 * nnorth - 2 - r].first;
-    double c[K], s1[K], s2[K], t1[K], t2[K];
+    const int k = R.n >> 2;
+    const int first = p0 + K * ((int)threadIdx.x & ~63);
+    const int pl = first + ((int)threadIdx.x & 63);   // p = pl + 64 i: all of one parity
+    const bool busy = __builtin_amdgcn_readfirstlane(2 * first) <= L;
+    // state of the even order (e, o) and of the odd one (p e, p o, q e, q o)
+    double ce[K], co[K], s1[K][6], s2[K][6];
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const int m = m0 + threadIdx.x + k * kShtThreads;
-        c[k] = 2.0 * cospi(2.0 * (double)(m % R.n) / (double)R.n);
-        s1[k] = s2[k] = t1[k] = t2[k] = 0.0;
+    for (int i = 0; i < K; ++i) {
+        const int m = 2 * (pl + 64 * i);
+        ce[i] = 2.0 * cospi(2.0 * (double)(m % R.n) / (double)R.n);
+        co[i] = 2.0 * cospi(2.0 * (double)((m + 1) % R.n) / (double)R.n);
+#pragma unroll
+        for (int f = 0; f < 6; ++f) s1[i][f] = s2[i][f] = 0.0;
     }
-    for (int j0 = 0; j0 < R.n; j0 += kShtChunk) {
-        const int cnt = min(kShtChunk, R.n - j0);
+    float va[4], vb[4];
+    auto load = [&](int j0) {
+        const int j = j0 + (int)threadIdx.x;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            va[t] = j < k ? xa[j + t * k] : 0.0f;
+            vb[t] = j < k && !equator ? xb[j + t * k] : 0.0f;
+        }
+    };
+    load(0);
+    for (int j0 = 0; j0 < k; j0 += kShtThreads) {
         __syncthreads();
-        for (int j = threadIdx.x; j < cnt; j += kShtThreads) {
-            const double p = (double)xa[j0 + j];
-            const double q = equator ? 0.0 : (double)xb[j0 + j];
-            sx[j] = make_double2(p + q, equator ? 0.0 : p - q);
+        {
+            double e[4], o[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                e[t] = (double)va[t] + (double)vb[t];
+                o[t] = equator ? 0.0 : (double)va[t] - (double)vb[t];
+            }
+            double2 *d = sx + 4 * threadIdx.x;
+            d[0] = make_double2((e[0] + e[2]) + (e[1] + e[3]), (o[0] + o[2]) + (o[1] + o[3]));
+            d[1] = make_double2((e[0] + e[2]) - (e[1] + e[3]), (o[0] + o[2]) - (o[1] + o[3]));
+            d[2] = make_double2(e[0] - e[2], o[0] - o[2]);
+            d[3] = make_double2(e[1] - e[3], o[1] - o[3]);
         }
         __syncthreads();
-        for (int j = 0; j < cnt; j += 2) {
-            const double2 v = sx[j], w = sx[j + 1];
+        if (j0 + kShtThreads < k) load(j0 + kShtThreads);
+        if (!busy) continue;
+        const int cnt = min(kShtThreads, k - j0);
+        const double2 *u = sx + (pl & 1), *w = sx + 2;
+        int j = 0;
+        for (; j + 1 < cnt; j += 2, u += 8, w += 8) {
+            const double2 ua = u[0], pa = w[0], qa = w[1], ub = u[4], pb = w[4], qb = w[5];
 #pragma unroll
-            for (int k = 0; k < K; ++k) {
-                s2[k] = fma(c[k], s1[k], v.x - s2[k]);
-                s1[k] = fma(c[k], s2[k], w.x - s1[k]);
-                t2[k] = fma(c[k], t1[k], v.y - t2[k]);
-                t1[k] = fma(c[k], t2[k], w.y - t1[k]);
+            for (int i = 0; i < K; ++i) {
+                const double fa[6] = {ua.x, ua.y, pa.x, pa.y, qa.x, qa.y};
+                const double fb[6] = {ub.x, ub.y, pb.x, pb.y, qb.x, qb.y};
+#pragma unroll
+                for (int f = 0; f < 6; ++f) {
+                    const double c = f < 2 ? ce[i] : co[i];
+                    s2[i][f] = fma(c, s1[i][f], fa[f] - s2[i][f]);
+                    s1[i][f] = fma(c, s2[i][f], fb[f] - s1[i][f]);
+                }
+            }
+        }
+        if (j < cnt) {   // the last sample of an odd k
+            const double2 ua = u[0], pa = w[0], qa = w[1];
+#pragma unroll
+            for (int i = 0; i < K; ++i) {
+                const double fa[6] = {ua.x, ua.y, pa.x, pa.y, qa.x, qa.y};
+#pragma unroll
+                for (int f = 0; f < 6; ++f) {
+                    const double v = fma(f < 2 ? ce[i] : co[i], s1[i][f], fa[f] - s2[i][f]);
+                    s2[i][f] = s1[i][f];
+                    s1[i][f] = v;
+                }
             }
         }
     }
+    if (!busy) return;
     double2 *row = F + ((size_t)blockIdx.y * nnorth + r) * 8 * lq;
     const RingRoots W(rt, R.n);
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const int m = m0 + threadIdx.x + k * kShtThreads;
-        if (m > L) continue;
-        double sw, cw;
-        sincospi(2.0 * (double)(m % R.n) / (double)R.n, &sw, &cw);
-        const double2 ph = W.at(-m * R.two_o);   // e^{-i m phi_0}
-        const double2 E = cmul(make_double2(cw * s1[k] - s2[k], sw * s1[k]), ph);
-        const double2 O = cmul(make_double2(cw * t1[k] - t2[k], sw * t1[k]), ph);
-        // Z(m) = E + i O, Z(-m) = conj E + i conj O
-        row[order_slot(m, lq)] = make_double2(E.x - O.y, E.y + O.x);
-        row[4 * lq + order_slot(m, lq)] = make_double2(E.x + O.y, -E.y + O.x);
+    for (int i = 0; i < K; ++i) {
+#pragma unroll
+        for (int d = 0; d < 2; ++d) {
+            const int m = 2 * (pl + 64 * i) + d;
+            if (m > L) continue;
+            double sw, cw;
+            sincospi(2.0 * (double)(m % R.n) / (double)R.n, &sw, &cw);
+            // s_{k-1} - e^{-i w} s_{k-2} of a real fold
+            auto tail = [&](int f) {
+                return make_double2(s1[i][f] - cw * s2[i][f], sw * s2[i][f]);
+            };
+            double2 E, O;
+            if (d == 0) {
+                E = tail(0);
+                O = tail(1);
+            } else {
+                const double2 pe = tail(2), po = tail(3), qe = tail(4), qo = tail(5);
+                const double g = (m & 3) == 1 ? 1.0 : -1.0;   // p -+ i q
+                E = make_double2(fma(g, qe.y, pe.x), fma(-g, qe.x, pe.y));
+                O = make_double2(fma(g, qo.y, po.x), fma(-g, qo.x, po.y));
+            }
+            const double2 ph = W.at(-m * (2 * (k - 1) + R.two_o));   // and e^{-i m phi_0}
+            E = cmul(E, ph);
+            O = cmul(O, ph);
+            // Z(m) = E + i O, Z(-m) = conj E + i conj O
+            row[order_slot(m, lq)] = make_double2(E.x - O.y, E.y + O.x);
+            row[4 * lq + order_slot(m, lq)] = make_double2(E.x + O.y, -E.y + O.x);
+        }
     }
 }
 
-// y_j = Re sum_m H_m e^{i m a_j}, a_j = 2 pi j / n, H_m = c_m G_r(m) e^{i m phi_0}:
-// with C = sum Re H_m cos(m a) and S = sum Im H_m sin(m a) (Clenshaw, shared
-// coefficient 2 cos a), y_j = C - S and y_{n-j} = C + S, for the even and odd
-// sums of a ring pair.
+// The inverse, y_j = Re sum_m H_m e^{i m a_j}, a_j = 2 pi j / n, H_m = c_m G_r(m) e^{i m phi_0}
+// of either ring, by classes: with u_c = sum_{m = c mod 4} H_m e^{i m a_j} the pixels of the
+// four quarters are y_{j + tk} = Re sum_c i^{ct} u_c.  u_c is e^{i c a_j} times a sum in steps
+// of b = 4 a_j = 2 pi j / k, from the real Clenshaw sums C = sum h cos, S = sum h sin of the real and
+// imaginary parts (shared coefficient 2 cos b); at k - j the cosines are the same and the sines
+// change sign.  So a thread obtains sixteen pixels of the two rings from sixteen
+// sums of lcut / 4 terms.  FP64 issue bounds it.
+__host__ __device__ inline int dft_groups(int L) { return (L >> 2) + 1; }
+static size_t dft_bwd_lds(int L) { return (size_t)8 * dft_groups(L) * sizeof(double2); }
 __global__ __launch_bounds__(kShtThreads) void k_sht_dft_bwd(const ShtRing *__restrict__ rings,
                                                              const int *__restrict__ ring_list,
                                                              const double2 *__restrict__ roots,
@@ -775,89 +844,96 @@ __global__ __launch_bounds__(kShtThreads) void k_sht_dft_bwd(const ShtRing *__re
                                                              long long npix, int L, int lq,
                                                              int nnorth, int accumulate)
 {
-    extern __shared__ double2 H[];   // He, then Ho
+    extern __shared__ double2 H[];   // northern ring, then its mirror, zero past lcut
     const int r = ring_list[blockIdx.x];
     const ShtRing R = rings[r];
     const double2 *row = G + ((size_t)blockIdx.y * nnorth + r) * 8 * lq;
-    double2 *Ho = H + L + 1;
+    const int A = dft_groups(L), k = R.n >> 2;
     __shared__ double2 rt[kRoots];
     load_roots(rt, roots);
     __syncthreads();
     const RingRoots W(rt, R.n);
-    for (int m = threadIdx.x; m <= L; m += kShtThreads) {
-        const double2 w = W.at(m * R.two_o);
-        const double c = m == 0 ? 1.0 : 2.0;
-        const double2 e = cmul(row[order_slot(m, lq)], w);
-        const double2 o = cmul(row[4 * lq + order_slot(m, lq)], w);
-        H[m] = make_double2(c * e.x, c * e.y);
-        Ho[m] = make_double2(c * o.x, c * o.y);
+    for (int m = threadIdx.x; m < 4 * A; m += kShtThreads) {
+        double2 hn = make_double2(0.0, 0.0), hs = hn;
+        if (m <= L) {
+            const double2 w = W.at(m * R.two_o);
+            const double c = m == 0 ? 1.0 : 2.0;
+            const double2 e = cmul(row[order_slot(m, lq)], w);
+            const double2 o = cmul(row[4 * lq + order_slot(m, lq)], w);
+            hn = make_double2(c * (e.x + o.x), c * (e.y + o.y));
+            hs = make_double2(c * (e.x - o.x), c * (e.y - o.y));
+        }
+        H[m] = hn;
+        H[4 * A + m] = hs;
     }
     __syncthreads();
     float *oa = out + (size_t)blockIdx.y * npix + R.first;
     float *ob = out + (size_t)blockIdx.y * npix + rings[2 * nnorth - 2 - r].first;
     const bool equator = r == nnorth - 1;
-    const int npairs = R.n / 2 + 1;     // j = 0 .. n/2
-    for (int j0 = threadIdx.x * kShtPairs; j0 < npairs; j0 += kShtThreads * kShtPairs) {
-        double cc[kShtPairs], b1[2][kShtPairs], b2[2][kShtPairs], d1[2][kShtPairs],
-            d2[2][kShtPairs];
+    for (int j = threadIdx.x; j <= k >> 1; j += kShtThreads) {
+        double sb, cb;
+        sincospi(2.0 * (double)j / (double)k, &sb, &cb);
+        const double cc = 2.0 * cb;
+        // b_a = h_a + 2 cos(b) b_{a+1} - b_{a+2} from a = A - 1 down to 1, two steps at
+        // a time in place (b1 holds the newest term); an odd count starts from b_{A-1} = h_{A-1}
+        double b1[4][4], b2[4][4];   // class; real and imaginary part, north and south
+        const bool odd = (A & 1) == 0;
 #pragma unroll
-        for (int k = 0; k < kShtPairs; ++k) {
-            cc[k] = 2.0 * cospi(2.0 * (double)(j0 + k) / (double)R.n);
-#pragma unroll
-            for (int p = 0; p < 2; ++p) b1[p][k] = b2[p][k] = d1[p][k] = d2[p][k] = 0.0;
+        for (int c = 0; c < 4; ++c) {
+            const double2 hn = H[4 * (A - 1) + c], hs = H[4 * A + 4 * (A - 1) + c];
+            b1[c][0] = odd ? hn.x : 0.0;
+            b1[c][1] = odd ? hn.y : 0.0;
+            b1[c][2] = odd ? hs.x : 0.0;
+            b1[c][3] = odd ? hs.y : 0.0;
+            b2[c][0] = b2[c][1] = b2[c][2] = b2[c][3] = 0.0;
         }
-        // b_m = h_m + 2 cos(a) b_{m+1} - b_{m+2} from m = L down, two steps
-        // at a time in place (b1 holds the newest term); an odd count starts
-        // from b_L = h_L
-        int m = L;
-        if (((L + 1) & 1) != 0) {
+        for (int a = odd ? A - 2 : A - 1; a > 1; a -= 2) {
 #pragma unroll
-            for (int p = 0; p < 2; ++p) {
-                const double2 h = (p ? Ho : H)[L];
+            for (int c = 0; c < 4; ++c) {
+                const double2 na = H[4 * a + c], nb = H[4 * a - 4 + c];
+                const double2 sa = H[4 * A + 4 * a + c], sb2 = H[4 * A + 4 * a - 4 + c];
+                const double ha[4] = {na.x, na.y, sa.x, sa.y};
+                const double hb[4] = {nb.x, nb.y, sb2.x, sb2.y};
 #pragma unroll
-                for (int k = 0; k < kShtPairs; ++k) {
-                    b1[p][k] = h.x;
-                    d1[p][k] = h.y;
-                }
-            }
-            m = L - 1;
-        }
-        for (; m > 0; m -= 2) {
-#pragma unroll
-            for (int p = 0; p < 2; ++p) {
-                const double2 ha = (p ? Ho : H)[m];
-                const double2 hb = (p ? Ho : H)[m - 1];
-#pragma unroll
-                for (int k = 0; k < kShtPairs; ++k) {
-                    b2[p][k] = fma(cc[k], b1[p][k], ha.x - b2[p][k]);
-                    b1[p][k] = fma(cc[k], b2[p][k], hb.x - b1[p][k]);
-                    d2[p][k] = fma(cc[k], d1[p][k], ha.y - d2[p][k]);
-                    d1[p][k] = fma(cc[k], d2[p][k], hb.y - d1[p][k]);
+                for (int f = 0; f < 4; ++f) {
+                    b2[c][f] = fma(cc, b1[c][f], ha[f] - b2[c][f]);
+                    b1[c][f] = fma(cc, b2[c][f], hb[f] - b1[c][f]);
                 }
             }
         }
 #pragma unroll
-        for (int k = 0; k < kShtPairs; ++k) {
-            const int j = j0 + k;
-            if (j >= npairs) continue;
-            double sa, ca;
-            sincospi(2.0 * (double)j / (double)R.n, &sa, &ca);
-            double C[2], S[2];
+        for (int side = 0; side < 2; ++side) {   // pixels j + tk, then k - j + tk
+            const int jj = side ? k - j : j;
+            if (side && (j == 0 || jj == j)) break;
+            double re[2][4], im[2][4];
 #pragma unroll
-            for (int p = 0; p < 2; ++p) {
-                C[p] = b1[p][k] - b2[p][k] * ca;     // b_0 - b_1 cos a
-                S[p] = d2[p][k] * sa;                // d_1 sin a
+            for (int c = 0; c < 4; ++c) {
+                const double2 w = W.at(2 * c * jj);
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {   // north, south
+                    const double2 h0 = H[4 * A * h + c];
+                    const double Cr = fma(b1[c][2 * h], cb, h0.x - b2[c][2 * h]);
+                    const double Ci = fma(b1[c][2 * h + 1], cb, h0.y - b2[c][2 * h + 1]);
+                    const double s = side ? -sb : sb;
+                    const double2 u =
+                        cmul(make_double2(fma(-s, b1[c][2 * h + 1], Cr), fma(s, b1[c][2 * h], Ci)), w);
+                    re[h][c] = u.x;
+                    im[h][c] = u.y;
+                }
             }
-            const int jm = j == 0 ? 0 : R.n - j;
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                if (t && jm == j) break;
-                const int at = t ? jm : j;
-                const double ye = t ? C[0] + S[0] : C[0] - S[0];
-                const double yo = t ? C[1] + S[1] : C[1] - S[1];
-                const float va = (float)(ye + yo), vb = (float)(ye - yo);
-                oa[at] = accumulate ? oa[at] + va : va;
-                if (!equator) ob[at] = accumulate ? ob[at] + vb : vb;
+            for (int h = 0; h < 2; ++h) {
+                if (h && equator) break;
+                float *o = h ? ob : oa;
+                const double y[4] = {(re[h][0] + re[h][2]) + (re[h][1] + re[h][3]),
+                                     (re[h][0] - re[h][2]) - (im[h][1] - im[h][3]),
+                                     (re[h][0] + re[h][2]) - (re[h][1] + re[h][3]),
+                                     (re[h][0] - re[h][2]) + (im[h][1] - im[h][3])};
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const int at = jj + t * k;
+                    o[at] = accumulate ? o[at] + (float)y[t] : (float)y[t];
+                }
             }
         }
     }
@@ -1246,7 +1322,7 @@ struct Harm {
     double *d_kscale = nullptr;
     int *d_ring_lo = nullptr;     // per m: first northern ring whose terms matter
     int *d_step_base = nullptr;   // per m: first step
-    int *d_dft_rings = nullptr;   // rings of the Goertzel / Clenshaw kernels
+    int *d_dft_rings = nullptr;   // rings of the direct sums
     ShtFftRing *d_fft_rings = nullptr;
     double2 *d_tw = nullptr;
     double2 *d_roots = nullptr;
@@ -1333,14 +1409,26 @@ ARKCOS_RING_KERNEL(ring_fwd)
 ARKCOS_RING_KERNEL(ring_bwd)
 #undef ARKCOS_RING_KERNEL
 
+// Whether a ring pair of quarter length k takes the direct sums: their time grows with
+// lcut, the FFTs' does not.  Measured per sample of a ring pair, both ways (Nside 512-4096, one map):
+// direct 7.5 + 0.105 lcut ps; FFTs 21-26 ps on belts of k = 1024, 2048 and 4096, 54 ps on those of
+// k = 512, 61 ps with the chirp transforms of k <= 2048 and 108-128 ps above (1024 threads, held to 128
+// registers, of which they spill hundreds).  Nside 2048, lcut 100: 0.61 ms of direct sums for the
+// whole half against 0.95 ms of FFTs; lcut 300: 1.23 against 1.03 ms; Nside 3000, lcut 100: 1.17
+// against 5.69 ms.
+static bool ring_direct(int k, bool belt, int lcut)
+{
+    if (k > kShtMaxK) return true;   // (the transform does not fit the LDS)
+    if (belt) return lcut < (k >= 1024 ? 128 : 256);
+    return lcut < (k > 2048 ? 1024 : 512);
+}
+
 // Ring pairs by FFT length, and those left to the direct sums.
 static int harm_build_ffts(Harm &h, const std::vector<ShtRing> &rings)
 {
-    // Small maps take the direct sums, npix (lcut + 1) terms each way: the FFT
-    // kernels are a long chain of short passes, whose start-up dominates there
-    // (both ways at Nside 128, lcut 146, 2.9e7 terms: direct 15 us, FFTs 64 us; at
-    // Nside 16: 7 and 50 us; at Nside 256, lcut 269, 2.1e8 terms, eight maps: the
-    // whole call takes 0.38 ms with the FFTs).
+    // Small maps take the direct sums on every ring, up to kShtDirectWork = npix (lcut + 1) of
+    // a map: the FFT kernels are a long chain of short passes, whose start-up dominates there
+    // (both ways at Nside 128, lcut 511: direct 29 us, FFTs 90 us; at Nside 256, lcut 255: 39 and 87 us).
     const bool use_fft = std::getenv("ARKCOS_SHT_NO_FFT") == nullptr &&
                          (double)h.npix * (h.lcut + 1) > kShtDirectWork;
     std::vector<int> dft;
@@ -1349,15 +1437,15 @@ static int harm_build_ffts(Harm &h, const std::vector<ShtRing> &rings)
     std::vector<long long> at((size_t)h.nside + 1, -1);   // chirp spectrum of length k
     for (int i = 0; i < h.nnorth; ++i) {
         const int k = rings[i].n / 4;
-        if (!use_fft || k > kShtMaxK) {
+        // the belt rings without the chirp if they can; caps hold few power-of-two rings
+        const bool direct = k == h.nside && k >= 8 && (k & (k - 1)) == 0;
+        if (!use_fft || ring_direct(k, direct, h.lcut)) {
             dft.push_back(i);
             continue;
         }
         ShtFftRing q{};
         q.ring = i;
         q.k = k;
-        // the belt rings directly if they can; caps hold few power-of-two rings
-        const bool direct = k == h.nside && k >= 8 && (k & (k - 1)) == 0;
         q.lg = 3;
         while ((1 << q.lg) < (direct ? k : 2 * k - 1)) ++q.lg;
         if (!direct) {
@@ -1374,6 +1462,7 @@ static int harm_build_ffts(Harm &h, const std::vector<ShtRing> &rings)
         list[direct ? 4 : (q.lg <= 10 ? 0 : q.lg - 10)].push_back(q);
     }
     h.lgm = std::max(h.lgm, 5);
+    std::reverse(dft.begin(), dft.end());   // longest first
     std::vector<ShtFftRing> all;
     for (int b = 0; b < 5; ++b) {
         if (list[b].empty()) continue;
@@ -1415,7 +1504,7 @@ static int harm_build_ffts(Harm &h, const std::vector<ShtRing> &rings)
     if (h.n_dft > 0)
         ARKCOS_HIP_CHECK(hipFuncSetAttribute((const void *)k_sht_dft_bwd,
                                              hipFuncAttributeMaxDynamicSharedMemorySize,
-                                             (int)(2 * (h.lcut + 1) * sizeof(double2))));
+                                             (int)dft_bwd_lds(h.lcut)));
     if (!spectra.empty()) {
         ShtFftRing *d = nullptr;
         long long bytes = 0;
@@ -1558,19 +1647,18 @@ static int harm_launch(const Harm &h, const float *in, float *out, int nb, int a
                            h.d_fft_rings + B.first, h.d_tw, h.d_roots, h.d_chirp, h.lgm,
                            in, h.npix, h.d_F, L, h.lq, h.nnorth);
     }
-    // frequencies per thread, kShtMaxFreq per launch
-    for (int m0 = 0, left = (L + kShtThreads) / kShtThreads; h.n_dft > 0 && left > 0;
-         m0 += kShtMaxFreq * kShtThreads, left -= kShtMaxFreq) {
-        switch (std::min(left, kShtMaxFreq)) {
+    // pairs of orders per thread, kShtMaxPairs per launch
+    for (int p0 = 0, left = L / 2 / kShtThreads + 1; h.n_dft > 0 && left > 0;
+         p0 += kShtMaxPairs * kShtThreads, left -= kShtMaxPairs) {
+        switch (std::min(left, kShtMaxPairs)) {
 #define ARKCOS_DFT_CASE(K)                                                                   \
     case K:                                                                                  \
         hipLaunchKernelGGL(k_sht_dft_fwd<K>, dim3(h.n_dft, nb), dim3(kShtThreads), 0, s,    \
-                           h.d_rings, h.d_dft_rings, h.d_roots, in, h.npix, h.d_F, m0, L, \
+                           h.d_rings, h.d_dft_rings, h.d_roots, in, h.npix, h.d_F, p0, L, \
                            h.lq, h.nnorth);                                                       \
         break;
-            ARKCOS_DFT_CASE(1) ARKCOS_DFT_CASE(2) ARKCOS_DFT_CASE(3) ARKCOS_DFT_CASE(4)
-            ARKCOS_DFT_CASE(5) ARKCOS_DFT_CASE(6) ARKCOS_DFT_CASE(7)
-            default: ARKCOS_DFT_CASE(8)
+            ARKCOS_DFT_CASE(1) ARKCOS_DFT_CASE(2) ARKCOS_DFT_CASE(3)
+            default: ARKCOS_DFT_CASE(4)
 #undef ARKCOS_DFT_CASE
         }
     }
@@ -1594,7 +1682,7 @@ static int harm_launch(const Harm &h, const float *in, float *out, int nb, int a
     }
     if (h.n_dft > 0)
         hipLaunchKernelGGL(k_sht_dft_bwd, dim3(h.n_dft, nb), dim3(kShtThreads),
-                           (size_t)2 * (L + 1) * sizeof(double2), s, h.d_rings, h.d_dft_rings,
+                           dft_bwd_lds(L), s, h.d_rings, h.d_dft_rings,
                            h.d_roots, h.d_F, out, h.npix, L, h.lq, h.nnorth, accumulate);
     ARKCOS_HIP_CHECK(hipGetLastError());
     return ARKCOS_OK;

@@ -102,6 +102,49 @@ def test_harmonic_long_ring_ffts(monkeypatch, nside, lcut):
     assert rel_rms(y, ref) <= 2.0 ** -24
 
 
+@pytest.mark.parametrize("nside,lcut,nb", [
+    (257, 127, 1), (257, 128, 2), (258, 511, 1),   # direct sums: odd quarter rings, passes of
+    (33, 300, 3), (40, 1500, 1),                   # 256 samples, up to three orders' pairs per lane
+    (64, 1300, 1), (128, 600, 1), (300, 512, 1)])  # belts of 64 and 128 by FFT, chirps from 512 on
+def test_harmonic_ring_sums_at_low_and_high_lcut(nside, lcut, nb):
+    khat = _khat(lcut, nside)
+    x = W.white_noise(nside, 78, nbatch=nb)
+    log("harmonic ring sums Nside %d lcut %d" % (nside, lcut))
+    y = to_host(_A().Harm(nside, khat, max_batch=nb).convolve(to_dev(x))).reshape(nb, -1)
+    for b, xb in enumerate(np.reshape(x, (nb, -1))):
+        ref = O.harmonic(nside, khat, xb.astype(np.float32).astype(np.float64))
+        assert rel_rms(y[b], ref) <= 2.0 ** -24, b
+
+
+@pytest.mark.parametrize("nside,lcut", [(64, 2100), (1024, 200), (2100, 1100), (4096, 130)])
+def test_harmonic_long_rings_by_fft_and_direct(monkeypatch, nside, lcut):
+    """FFTs against direct sums on every ring: two launches of orders (the oracle's
+    Legendre tables end below lcut 2100), belt rings by FFT beside caps by direct
+    sums, and the longest chirp transforms."""
+    import torch
+    khat = _khat(lcut, 6)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(nside)
+    x = torch.randn(12 * nside * nside, generator=gen, device="cuda")
+    log("harmonic long rings Nside %d lcut %d" % (nside, lcut))
+    A = _A()
+    y = A.Harm(nside, khat).convolve(x)
+    monkeypatch.setenv("ARKCOS_SHT_NO_FFT", "1")
+    ref = A.Harm(nside, khat).convolve(x).double()
+    err = float(torch.linalg.vector_norm(y.double() - ref) / torch.linalg.vector_norm(ref))
+    assert err <= 2.0 ** -24
+
+
+@pytest.mark.parametrize("nside,lcut", [(512, 30), (1500, 64), (3000, 100)])
+def test_harmonic_low_lcut_keeps_no_spectra(nside, lcut):
+    """Low lcut takes the direct sums, which need no chirp spectra: the plan holds the
+    workspace of one map and small tables."""
+    log("harmonic low lcut Nside %d lcut %d" % (nside, lcut))
+    nbytes = _A().Harm(nside, np.ones(lcut + 1)).info()["device_bytes"]
+    rows = 2 * nside * 8 * ((lcut // 4 + 8) & ~7) * 16
+    assert nbytes <= rows + (4 << 20)
+
+
 @pytest.mark.parametrize("nside,lcut", [(8, 4095), (64, 4095), (64, 2000), (256, 300)])
 def test_harmonic_workspace_bound(nside, lcut):
     """The workspace of the maps that pass together is 512 MB at most beyond one

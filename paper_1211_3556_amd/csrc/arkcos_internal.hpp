@@ -186,12 +186,19 @@ constexpr int kGenPixelsDefault = 128;
 constexpr int kGenQuadWindowDefault = 64;
 constexpr int kGenPairWindowDefault = 200;
 constexpr int kGenStage = 248;       // with a 16384-node table two workgroups fit a CU
-// General tiles of one or two rings whose rows average this many candidates run
-// their products on the matrix cores, 128 / nr pixels of each ring per tile.  Below,
-// the union of sixteen pixels' windows costs more than the products save: sixteen maps of
-// 5-30 arcmin in one call took 18.4 ms with 72 or more and 19.6 ms with 56; with 72
-// instead of 96, Nside 256 and 1000 arcmin went from 1630 to 1115 us.
-constexpr int kGenWideWindow = 72;
+// General tiles of one or two rings whose rows average kGenLongWindow candidates take
+// 128 / nr pixels of each ring: their rows are long enough to hide a chunk's staging, and
+// more, shorter tiles fill the chip and balance it (Nside 171 and 256, 70 and 100 pixels of cut-off,
+// one to four maps: 0.65-0.97 of the time of 128-pixel pairs; equal at many maps).
+// From kGenWideWindow on, tiles without long-sine rows run their products on the matrix cores.
+// Below, the union of sixteen pixels' windows costs more than the products save: general
+// gather against the vector form on the same tiles, Nside 512 to 2048, rows of about 80
+// candidates 1.02-1.04, 95 candidates 0.98-1.01, 114 candidates 0.93-0.97.  Long-sine rows (near the
+// poles, and every general row of a cut-off beyond about 0.13 rad) have wider unions, as the pixel
+// spacings of their rings differ more: 1.02-1.28 with 95-200 candidates at Nside 64-512,
+// 0.90-1.08 above 230.
+constexpr int kGenLongWindow = 72;
+constexpr int kGenWideWindow = 100;
 constexpr int kMaxMaps = 32;
 // Circulant knot-gradient tiles: kKnotSeg pixels of a ring group.
 constexpr int kKnotSeg = 512;
@@ -320,7 +327,8 @@ struct Plan {
     int tile_source = 0;              // 0 defaults, 1 tuning cache, 2 descriptor
     // the general northern rings in order, for the general-gather tiling:
     // ring, pixels of its half-quadrant, tile flags, widest row window
-    std::vector<int> gen_ring, gen_lanes, gen_flags, gen_wflags;
+    std::vector<int> gen_ring, gen_lanes, gen_flags;
+    std::vector<char> gen_wide_ok;    // rows fit the matrix-core form
     std::vector<double> gen_wmax;
     std::vector<double> ring_cost;    // candidates per output pixel of each ring
     // Source rings read by the gathers (0-based, inclusive; all if src_hi < 0).

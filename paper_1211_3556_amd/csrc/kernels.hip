@@ -884,9 +884,9 @@ __device__ __forceinline__ void gen_tile2(const DevPlanView &P, const float *tab
 }
 
 // ------------------------------------------------ general gather, wide rows --
-// Tiles whose rows average kGenWideWindow candidates or more.  There k_general is
-// bound by the sixteen FMAs of a candidate and its 64 bytes of LDS reads on top
-// of the weight; here the products run on the matrix cores as
+// Tiles without long-sine rows whose rows average kGenWideWindow candidates or more.
+// There k_general is bound by the sixteen FMAs of a candidate and its 64 bytes of LDS
+// reads on top of the weight; here the products run on the matrix cores as
 // v_mfma_f32_16x16x4f32 (FP32 in and out), which takes half the cycles of the
 // FMAs and reads 256 bytes of LDS per wave instead of 4096.  A wave takes sixteen
 // pixels of one ring: lane l evaluates the weight of pixel l & 15 and candidate l >> 4
@@ -896,9 +896,10 @@ __device__ __forceinline__ void gen_tile2(const DevPlanView &P, const float *tab
 // pixels' windows, about eighteen candidates more per row.  A ring's waves beyond
 // its groups of sixteen pixels share the steps of a group.  Every instruction of a
 // step issues on the vector ALUs or the matrix cores, which do not overlap in one
-// SIMD, and they are busy all of the time: hence the untested middle of a row and the
-// form for rows beyond the break of a biased grid.  Nside 2048, 240 arcmin: 75 -> 66 ms
-// (105.5 -> 97.4 ms with the circulant rows); Nside 1024, 300 arcmin: 11.04 -> 10.28 ms.
+// SIMD: hence the untested middle of a row and the form for rows beyond the break of a
+// biased grid.  General gather at Nside 2048 on the same tiles, vector form -> this one: uniform grid
+// 85 pixels of cut-off 22.7 -> 21.3 ms, 100 pixels 31.1 -> 28.8, 240 arcmin (139 pixels)
+// 70.8 -> 65.1; biased grid 240 arcmin 73.9 -> 66.1.
 //
 // A zero weight still multiplies the staged value, so a NaN or an infinity
 // would reach pixels outside whose disc it lies: a tile that stages one returns
@@ -907,12 +908,10 @@ constexpr int kWideFlush = 16;   // steps (64 FP32 terms) between moves into FP6
 
 // Whether every candidate of a row lies beyond the break of a biased grid (by
 // half a coarse node): its smallest separation, at m = 0, does.  Wave-uniform.
-template <bool LONG, int AM>
+template <int AM>
 __device__ __forceinline__ bool beyond_break(const DevPair &pp, const GenConst<AM> &gc)
 {
-    const float u = LONG ? node_coord<AM>(pp.A, gc.ucf)
-                         : (AM == 0 ? __builtin_amdgcn_sqrtf(pp.sq[0])
-                                    : node_coord<AM>(pp.sq[0], gc.ucf));
+    const float u = AM == 0 ? __builtin_amdgcn_sqrtf(pp.sq[0]) : node_coord<AM>(pp.sq[0], gc.ucf);
     return __builtin_amdgcn_readfirstlane(fmaf(u, gc.br, gc.bc) >= 0.5f) != 0;
 }
 
@@ -920,57 +919,41 @@ __device__ __forceinline__ bool beyond_break(const DevPair &pp, const GenConst<A
 // window (no test there).  COARSE: every candidate of the row lies beyond
 // the break of a biased grid (the row's smallest separation does), as most rows of
 // a wide cut do, and needs no choice between the table's two pieces.
-template <bool LONG, int AM, bool INTM, bool BIAS, bool COARSE>
+template <int AM, bool BIAS, bool COARSE>
 __device__ __forceinline__ void wide_steps(const DevPair &pp, const GenConst<AM> &gc,
-                                           const float *tab, int m, int dm, int jv, int width,
-                                           int jstep, int sp, int sstep, int h, int e, int T,
-                                           double acc[4])
+                                           const float *tab, int m, int dm, int sp, int sstep,
+                                           int h, int e, int T, double acc[4])
 {
-    const float A = LONG ? vreg(pp.A) : 0.0f;
-    const float B = LONG ? vreg(pp.B) : 0.0f;
-    const float xscale = LONG ? vreg(pp.xscale) : 0.0f;
-    const float q0 = LONG ? 0.0f : vreg(pp.sq[0]);
-    const float q1 = LONG ? 0.0f : vreg(pp.sq[1]);
-    const float q2 = LONG ? 0.0f : vreg(pp.sq[2]);
-    const float q3 = LONG ? 0.0f : vreg(pp.sq[3]);
-    const float q4 = (LONG || AM != 0) ? 0.0f : vreg(pp.sq[4]);
+    const float q0 = vreg(pp.sq[0]);
+    const float q1 = vreg(pp.sq[1]);
+    const float q2 = vreg(pp.sq[2]);
+    const float q3 = vreg(pp.sq[3]);
+    const float q4 = AM != 0 ? 0.0f : vreg(pp.sq[4]);
     const UCoef &ucf = gc.ucf;
-    const float ms = LONG ? 1.0f : pp.mscale;
+    const float ms = pp.mscale;
     float mf = (float)m * ms;
     const float dmf = vreg((float)dm * ms);
-    int mi = m;
-    const int dmi = vreg(dm);
     const float mcut_f = vreg((float)pp.mcut * ms);
-    const unsigned mcut_u = (unsigned)vreg(pp.mcut);
     typedef __attribute__((address_space(3))) const float lds_float;
     const int tab_b = (int)(size_t)(lds_float *)tab;
     const int tab_cb = BIAS ? vreg(tab_b + 4 * gc.kb) : tab_b;
     const float zslot = COARSE ? gc.zslot - (float)gc.kb : gc.zslot;
-    const int js = vreg(jstep), ss = vreg(sstep);
+    const int ss = vreg(sstep);
     circ_v4f d = {0.0f, 0.0f, 0.0f, 0.0f};
     auto step = [&](auto check) {
         constexpr bool CHECK = decltype(check)::value;
         const float x = *(lds_float *)(size_t)sp;
-        float u0;
-        if (LONG) {
-            const float xx = (INTM ? (float)mi : mf) * xscale;
-            const float sx = sin_series(xx);
-            u0 = node_coord<AM>(fmaf(B, sx * sx, A), ucf);
-        } else if (AM == 0) {
-            const float y = mf * mf;
-            u0 = __builtin_amdgcn_sqrtf(fmaf(fmaf(fmaf(fmaf(y, q4, q3), y, q2), y, q1), y, q0));
-        } else {
-            const float y = mf * mf;
-            u0 = node_coord<AM>(fmaf(fmaf(fmaf(y, q3, q2), y, q1), y, q0), ucf);
-        }
+        const float y = mf * mf;
+        const float u0 =
+            AM == 0 ? __builtin_amdgcn_sqrtf(
+                          fmaf(fmaf(fmaf(fmaf(y, q4, q3), y, q2), y, q1), y, q0))
+                    : node_coord<AM>(fmaf(fmaf(fmaf(y, q3, q2), y, q1), y, q0), ucf);
         const float v = BIAS ? fmaf(u0, gc.br, gc.bc) : 0.0f;
         const bool coarse = BIAS && (COARSE || v >= 0.0f);
         float uc = coarse ? v : u0;
         int tb = coarse ? tab_cb : tab_b;
         if (CHECK) {
-            bool keep = INTM ? (unsigned)mi + mcut_u <= 2u * mcut_u : fabsf(mf) <= mcut_f;
-            // (the union of whole-ring windows meets a source pixel twice)
-            if (LONG) keep = keep && (unsigned)jv <= (unsigned)width;
+            const bool keep = fabsf(mf) <= mcut_f;
             uc = keep ? uc : zslot;
             if (BIAS && !COARSE) tb = keep ? tb : tab_b;
         }
@@ -982,11 +965,7 @@ __device__ __forceinline__ void wide_steps(const DevPair &pp, const GenConst<AM>
         const float w = fmaf(frac, k1 - k0, k0);
         d = __builtin_amdgcn_mfma_f32_16x16x4f32(w, x, d, 0, 0, 0);
         sp += ss;
-        if (LONG) jv += js;
-        if (INTM)
-            mi -= dmi;
-        else
-            mf -= dmf;
+        mf -= dmf;
     };
     auto flush = [&]() {
 #pragma unroll
@@ -1031,7 +1010,7 @@ __device__ __forceinline__ int &wide_bad()
     return s_bad;
 }
 
-template <bool LONG, int AM, bool INTM, bool BIAS>
+template <int AM, bool BIAS>
 __device__ __forceinline__ bool gen_tile_wide(const DevPlanView &P, const float *tab, float4 *stage,
                                               const DevTile2 *Tp, const float *in, float *out)
 {
@@ -1109,12 +1088,10 @@ __device__ __forceinline__ bool gen_tile_wide(const DevPlanView &P, const float 
             const int m0 = lon_numerator(lon_base(j, R.two_o, ch.n), jq, ch.two_o, R.n);
             const int sp = stage_b + 16 * (((lane >> 2) & 3) * kGenStage + sl) + 4 * (lane & 3);
             const int dm = 8 * nsub * R.n;
-            if (T > 0 && BIAS && beyond_break<LONG, AM>(pp, gc)) {
-                wide_steps<LONG, AM, INTM, BIAS, BIAS>(pp, gc, tab, m0, dm, jq - lo, hi - lo,
-                                                       4 * nsub, sp, 64 * nsub, h, e, T, acc);
+            if (T > 0 && BIAS && beyond_break<AM>(pp, gc)) {
+                wide_steps<AM, BIAS, BIAS>(pp, gc, tab, m0, dm, sp, 64 * nsub, h, e, T, acc);
             } else if (T > 0) {
-                wide_steps<LONG, AM, INTM, BIAS, false>(pp, gc, tab, m0, dm, jq - lo, hi - lo,
-                                                        4 * nsub, sp, 64 * nsub, h, e, T, acc);
+                wide_steps<AM, BIAS, false>(pp, gc, tab, m0, dm, sp, 64 * nsub, h, e, T, acc);
             }
         }
         ch = nx;
@@ -1164,18 +1141,9 @@ __device__ __forceinline__ void gen_tile_variant(const DevPlanView &P, const flo
     }
     const bool lg = (fl & kTileLongSin) != 0;
     if (WIDE && cst(Tp)->wide) {
-        bool done = false;
-        switch (P.angle_mode * 3 + ((fl & kTileIntM) ? 2 : (lg ? 1 : 0))) {
-            case 0: done = gen_tile_wide<false, 0, false, BIAS>(P, tab, stage, Tp, in, out); break;
-            case 1: done = gen_tile_wide<true, 0, false, BIAS>(P, tab, stage, Tp, in, out); break;
-            case 2: done = gen_tile_wide<true, 0, true, BIAS>(P, tab, stage, Tp, in, out); break;
-            case 3: done = gen_tile_wide<false, 1, false, BIAS>(P, tab, stage, Tp, in, out); break;
-            case 4: done = gen_tile_wide<true, 1, false, BIAS>(P, tab, stage, Tp, in, out); break;
-            case 5: done = gen_tile_wide<true, 1, true, BIAS>(P, tab, stage, Tp, in, out); break;
-            case 6: done = gen_tile_wide<false, 2, false, BIAS>(P, tab, stage, Tp, in, out); break;
-            case 7: done = gen_tile_wide<true, 2, false, BIAS>(P, tab, stage, Tp, in, out); break;
-            default: done = gen_tile_wide<true, 2, true, BIAS>(P, tab, stage, Tp, in, out); break;
-        }
+        // (no long-sine rows, so never the angle series beyond 0.5 rad: plan creation)
+        const bool done = P.angle_mode == 0 ? gen_tile_wide<0, BIAS>(P, tab, stage, Tp, in, out)
+                                            : gen_tile_wide<1, BIAS>(P, tab, stage, Tp, in, out);
         if (done) return;
     }
     if (fl & kTileIntM) {   // wide windows on large rings (long sine implied)

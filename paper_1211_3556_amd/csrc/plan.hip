@@ -31,12 +31,15 @@ static void log_plan(const Plan &P)
     const int ngen_rings = (int)std::count(P.general_ring.begin(), P.general_ring.end(), 1);
     fprintf(stderr,
             "[arkcos] plan nside %d theta_cut %.6g rad ntab %d%s%s: rings %d circulant / %d "
-            "general, ring pairs %zu, circulant tiles %zu, general tiles %zu (%zu staged "
-            "chunks; shapes %d/%d/%d from %s), circulant rows %zu (weights %lld, %s), "
+            "general, ring pairs %zu, circulant tiles %zu, general tiles %zu (%d on the matrix "
+            "cores, %zu staged chunks; shapes %d/%d/%d from %s), circulant rows %zu (weights %lld, %s), "
             "device bytes %lld\n",
             P.nside, P.desc.theta_cut, P.desc.ntab, P.desc.k_break > 0 ? " biased" : "",
             P.desc.ring_first > 0 ? " ring range" : "", P.nrings - ngen_rings, ngen_rings,
-            P.pairs.size(), P.ctiles.size(), P.gtiles2.size(), P.gchunks.size(),
+            P.pairs.size(), P.ctiles.size(), P.gtiles2.size(),
+            (int)std::count_if(P.gtiles2.begin(), P.gtiles2.end(),
+                               [](const DevTile2 &t) { return t.wide != 0; }),
+            P.gchunks.size(),
             P.tiles.gen_pixels, P.tiles.gen_quad_window, P.tiles.gen_pair_window,
             P.tile_source == 0 ? "defaults" : (P.tile_source == 1 ? "tuning cache" : "descriptor"),
             P.rows.size(), P.nweights, P.circ_form ? "matrix cores" : "vector FMAs",
@@ -308,16 +311,21 @@ void build_gen_tiles(Plan &P)
         int lanes = 0;
         double rows = 0.0, cands = 0.0;   // of a pixel of each ring
         int skip = kTileSkipNorth | kTileSkipSouth;
+        bool ok = true;
         for (int i = 0; i < nr; ++i) {
             lanes = std::max(lanes, glanes[g + i]);
             const DevRing &dr = P.dev_rings[gring[g + i]];
             rows += dr.pair_end - dr.pair_begin;
             cands += P.ring_cost[gring[g + i]];
             skip &= gflags[g + i];
+            ok = ok && P.gen_wide_ok[g + i];
         }
         // (tiles that write one side only have a vector form at half the cost)
-        const bool wide = nr <= 2 && !skip && cands >= kGenWideWindow * rows;
-        const int seg = wide ? std::min(P.tiles.gen_pixels, kGenLanes / nr) : P.tiles.gen_pixels;
+        const bool both = nr <= 2 && !skip;
+        const bool wide = both && ok && cands >= kGenWideWindow * rows;
+        const int seg = both && cands >= kGenLongWindow * rows
+                            ? std::min(P.tiles.gen_pixels, kGenLanes / nr)
+                            : P.tiles.gen_pixels;
         for (int j0 = 0; j0 < lanes; j0 += seg) {
             DevTile2 t{};
             double c = 1.0;
@@ -330,7 +338,7 @@ void build_gen_tiles(Plan &P)
                 GenRing &q = t.q[h];
                 q.r = h < nr ? gring[g + h] : gring[g];
                 q.len = h < nr ? std::max(0, std::min(seg, glanes[g + h] - j0)) : 0;
-                q.flags = h < nr ? (wide ? P.gen_wflags : gflags)[g + h] : 0;
+                q.flags = h < nr ? gflags[g + h] : 0;
                 q.s_lo = 0;
                 q.s_hi = -1;
                 if (q.len > 0) {
@@ -555,7 +563,7 @@ static int build_plan(Plan &P)
     P.gen_ring.clear();
     P.gen_lanes.clear();
     P.gen_flags.clear();
-    P.gen_wflags.clear();
+    P.gen_wide_ok.clear();
     P.gen_wmax.clear();
     for (int r = 0; r <= P.nrings - 1 - r; ++r) {
         if (!general[r]) continue;
@@ -567,7 +575,7 @@ static int build_plan(Plan &P)
         // runs past a lane's window (at most 64 lanes per pixel, +4 for the
         // spread of windows across a wave)
         int flags = force_int_m ? (kTileIntM | kTileLongSin) : 0;
-        int wflags = 0;
+        bool wide_ok = true;
         if (!in_range(r)) flags |= kTileSkipNorth;
         if (!in_range(rm)) flags |= kTileSkipSouth;
         for (int k = P.dev_rings[r].pair_begin; k < P.dev_rings[r].pair_end; ++k) {
@@ -575,9 +583,9 @@ static int build_plan(Plan &P)
             if (pp.mode & kPairLongSin) flags |= kTileLongSin;
             const double W = (pp.mode & kPairWhole) ? 0.5 * P.rings[pp.s].n + 1.0 : pp.w + 1.0;
             if (2.0 * P.rings[r].n * (W + 70.0) >= 16777216.0) flags |= kTileIntM | kTileLongSin;
-            // (wide tiles: the union of sixteen pixels' windows, pixel spacing n_s / n_r)
+            // (exact in FP32 over the union of sixteen pixels' windows, pixel spacing n_s / n_r)
             if (2.0 * P.rings[r].n * (W + 70.0) + 32.0 * P.rings[pp.s].n >= 16777216.0)
-                wflags |= kTileIntM | kTileLongSin;
+                wide_ok = false;
         }
         for (int j0 = 0; j0 < lanes; j0 += kGenLanes) {
             DevTile t{};
@@ -597,7 +605,7 @@ static int build_plan(Plan &P)
         P.gen_ring.push_back(r);
         P.gen_lanes.push_back(lanes);
         P.gen_flags.push_back(flags);
-        P.gen_wflags.push_back(flags | wflags);
+        P.gen_wide_ok.push_back(wide_ok && (flags & kTileLongSin) == 0 && P.angle_mode < 2);
         P.gen_wmax.push_back(wmax);
     }
     sort_by_cost(P.gtiles, cost);

@@ -281,6 +281,81 @@ def test_wide_rows(nside, tc_deg, biased):
     assert rel_rms(yb[~outer], ref[~outer]) <= REL_RMS_TOL
 
 
+def _matrix_core_tiles(capfd):
+    """General tiles on the matrix cores, from the plan's log line (ARKCOS_LOG=1)."""
+    line = [l for l in capfd.readouterr().err.splitlines() if l.startswith("[arkcos] plan")][-1]
+    return int(line.split("general tiles ")[1].split("(")[1].split(" on the matrix cores")[0])
+
+
+@pytest.mark.parametrize("nside,tc_deg,biased,tiles,rings",
+                         [(640, 7.25, False, None, None), (640, 7.25, True, None, None),
+                          (820, 5.7, False, dict(gen_pair_window=-1), None),
+                          (820, 5.7, True, None, None),
+                          # the mirror of an even or of an odd ring is the first one left out
+                          (640, 7.25, True, None, (300, 4 * 640 - 560)),
+                          (820, 5.7, False, None, (300, 4 * 820 - 701))])
+def test_wide_rows_on_the_matrix_cores(nside, tc_deg, biased, tiles, rings, monkeypatch, capfd):
+    """The matrix-core form of the general gather: both angle series that it serves, both
+    node grids, tiles of one and two rings, ring ranges that skip one side of one ring of a
+    pair; forward and map gradient against the oracle.  A NaN and an infinity reach the
+    pixels whose disc they lie in, and none beyond the pixels next to those."""
+    A = _A()
+    tc = np.radians(tc_deg)
+    ntab = 700
+    kw = dict(tiles=tiles, rings=rings)
+    nodes = None
+    theta = np.linspace(0.0, tc, ntab)
+    if biased:
+        kw["theta_break"], kw["k_break"] = A.paper_bias(tc, ntab)
+        nodes = theta = O.biased_nodes(tc, ntab)
+    # (zero at the cut, so that lattice ties there do not count)
+    k = W.gaussian_profile_at(tc / 2, theta) * (1.0 - theta / tc)
+    monkeypatch.setenv("ARKCOS_LOG", "1")
+    plan = A.Plan(nside, tc, k, **kw)
+    assert _matrix_core_tiles(capfd) > 100
+    # pixels of the caps' outer rings and their mirrors, some around the bad pixels below
+    rng = np.random.default_rng(nside)
+    first = lambda r: 2 * r * (r - 1) if r <= nside else 12 * nside ** 2 - 2 * (4 * nside - r) * (
+        4 * nside - r + 1)
+    r0, r1 = 4 * nside // 5, 4 * nside - 4 * nside // 5
+    pix = [first(r) + int(rng.integers(0, 4 * min(r, 4 * nside - r)))
+           for side in (0, 1) for r in (rng.integers(7 * nside // 10, nside, 60) if side == 0 else
+                                        4 * nside - rng.integers(7 * nside // 10, nside, 60))]
+    pix += [first(r + d) + j for r in (r0, r1) for d in (-90, -50, 0, 30, 100) for j in (1, 40, 90)]
+    lo, hi = rings or (1, 4 * nside - 1)
+    ends = [first(q) if q <= nside or q >= 3 * nside else 0 for q in (lo, hi + 1)]
+    pix = np.unique([p for p in pix if p >= ends[0] and (hi == 4 * nside - 1 or p < ends[1])])
+    x = W.white_noise(nside, 47)
+    log("wide rows on the matrix cores Nside %d" % nside)
+    y = _conv_gpu(plan, x)
+    ref = O.convolve(nside, tc, k, x, nodes=nodes, pixels=pix)
+    assert rel_rms(y[pix], ref) <= REL_RMS_TOL
+    bad = np.array(x)
+    at = [first(r0) + 37, first(r1) + 41]
+    bad[at] = np.nan, np.inf
+    yb = _conv_gpu(plan, bad)[pix]
+    delta = np.zeros(x.shape)
+    delta[at] = 1.0
+    step = 2.0 / nside
+    inner = O.convolve(nside, tc - step, np.ones(16), delta, pixels=pix) != 0
+    outer = O.convolve(nside, tc + step, np.ones(16), delta, pixels=pix) != 0
+    assert inner.any() and not np.any(np.isfinite(yb[inner]))
+    assert (~outer).any() and np.all(np.isfinite(yb[~outer]))
+    assert rel_rms(yb[~outer], ref[~outer]) <= REL_RMS_TOL
+    # map gradient: the adjoint reads the range's rings alone
+    lplan = A.Plan(nside, tc, ntab=ntab, learnable=True, **kw)
+    assert _matrix_core_tiles(capfd) > 100
+    lplan.set_knots(to_dev(k))
+    gx, _ = lplan.backward(to_dev(x), to_dev(x), want_map=True, want_knots=False)
+    inside = np.array(x)
+    inside[:int(ends[0])] = 0.0
+    if hi < 4 * nside - 1:
+        inside[int(ends[1]):] = 0.0
+    gref = O.convolve(nside, tc, k.astype(np.float32).astype(np.float64), inside, nodes=nodes,
+                      pixels=pix)
+    assert rel_rms(to_host(gx)[pix], gref) <= REL_RMS_TOL
+
+
 @pytest.mark.parametrize("nside,tc_deg", [(64, 6.0), (100, 3.31), (16, 74.7)])
 def test_parts_compose_to_full_convolution(nside, tc_deg):
     """The circulant and general gathers write disjoint rings: running them

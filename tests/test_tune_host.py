@@ -125,3 +125,16 @@ def test_gen_tiles_cover_every_general_pixel_once(nside, tc_deg, tiles):
             cover[r][j0:j0 + ln] += 1
     for r in rings:
         assert np.all(cover[r] == 1), r
+
+
+@pytest.mark.parametrize("nside,pixels,some", [
+    (64, 70, False), (128, 100, False), (171, 100, False), (256, 80, False), (300, 150, False),
+    (512, 60, False), (1024, 60, False), (1024, 85, True), (2048, 85, True), (2048, 139, True)])
+def test_matrix_core_tiles_where_they_pay(nside, pixels, some, monkeypatch, capfd):
+    """Cut-offs in pixel widths: general tiles run on the matrix cores only where their rows
+    are wide and have no long-sine row (on the others the vector form is faster)."""
+    monkeypatch.setenv("ARKCOS_LOG", "1")
+    A.Plan(nside, pixels * np.sqrt(np.pi / 3.0) / nside, np.ones(8), host_only=True)
+    line = [l for l in capfd.readouterr().err.splitlines() if l.startswith("[arkcos] plan")][-1]
+    tiles, wide = line.split("general tiles ")[1].split(" on the matrix cores")[0].split(" (")
+    assert (int(wide) > 0) == some and int(wide) <= int(tiles)

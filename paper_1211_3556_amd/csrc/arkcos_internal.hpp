@@ -373,7 +373,8 @@ struct Plan {
     int cus = 0;                        // compute units of the device
     int occ_circ = 0;                   // resident workgroups per CU of the two gathers
     int occ_gen = 0;
-    int occ_both = 0;                   // and of both in one launch
+    int occ_both = 0;                   // and of both in one launch,
+    int both_maps = 0;                  // taken up to this number of maps
     int occ_kc = 0;                     // and of the two knot-gradient kernels
     int occ_kg = 0;
     int occ_km = 0;                     // several-map form of the general one (0: not used),

@@ -1226,8 +1226,15 @@ void k_general(const DevPlanView *__restrict__ views, const int2 *__restrict__ t
 // persistent kernels: there every workgroup's own load of the table and the
 // circulant tiles' four waves in eight-wave workgroups cost more (Nside 512, 30 arcmin,
 // four maps, 3332 tiles: 134 against 138 us; Nside 1024, 30 arcmin, 2700: 235 against 259;
-// Nside 2048, 10 arcmin: 398 against 546).
+// Nside 2048, 10 arcmin: 398 against 546).  Where rows are wide, general tiles that fill the
+// chip for kBothWideRounds2 / 2 rounds leave nothing to run beside them and the circulant
+// tiles behind them run at half occupancy: rows averaging 67 candidates or more, persistent kernels
+// against one launch, 816-1500 general tiles: Nside 300, 50 pixels of cut-off, four maps 1.92 and
+// 2.02 ms, Nside 256, 100 pixels, four maps 6.6 and 6.9, up to 1.5 rounds: Nside 300, 50 pixels, two
+// maps 1.46 and 1.24 ms.  Rows of up to 47 candidates gain up to the four rounds (Nside 171, 25
+// pixels, sixteen maps, 864 general tiles: 0.97 and 0.87 ms).
 constexpr int kBothRounds = 4;
+constexpr int kBothWideRow = 56, kBothWideRounds2 = 3;
 template <bool MF, bool WIDE>
 __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(4)))
 void k_both(const DevPlanView *__restrict__ views, const float *in, float *out, int ngen, int nmaps,
@@ -2182,6 +2189,22 @@ static auto both_kernel(bool mfma, bool wide) -> decltype(&k_both<true, true>)
     return mfma ? k_both<true, false> : k_both<false, false>;
 }
 
+// Largest number of maps for which both gathers run in one launch (k_both).
+static int both_maps(const Plan &p)
+{
+    const long long ngt = (long long)p.gtiles2.size(), nct = (long long)p.ctiles.size();
+    if (ngt == 0 || nct == 0) return 0;
+    const long long room = (long long)p.occ_both * p.cus;
+    double rows = 0.0, cands = 0.0;   // of a pixel of each general ring
+    for (int r : p.gen_ring) {
+        rows += p.dev_rings[r].pair_end - p.dev_rings[r].pair_begin;
+        cands += p.ring_cost[r];
+    }
+    long long n = kBothRounds * room / (nct + ngt);
+    if (cands >= kBothWideRow * rows) n = std::min(n, kBothWideRounds2 * room / (2 * ngt));
+    return (int)n;
+}
+
 int prepare_launches(Plan &p)
 {
     ARKCOS_HIP_CHECK(hipDeviceGetAttribute(&p.cus, hipDeviceAttributeMultiprocessorCount,
@@ -2200,6 +2223,7 @@ int prepare_launches(Plan &p)
          (rc = occupancy(both_kernel(p.circ_form, false), both_lds(p.desc.ntab), &p.occ_both,
                          kGenThreads))))
         return rc;
+    p.both_maps = both_maps(p);
     p.grid_kc = p.grid_kg = 0;
     if ((p.desc.flags & ARKCOS_PLAN_LEARNABLE) && p.desc.ntab <= ARKCOS_MAX_GRAD_NTAB) {
         if ((rc = occupancy(k_knot_circ, knot_circ_lds(p.desc.ntab), &p.occ_kc))) return rc;
@@ -2269,9 +2293,8 @@ int launch_forward(const Plan &p, const float *in, float *out, int nbatch, hipSt
     if (!counter) counter = p.d_counter;
     const int nct = (parts & ARKCOS_PART_CIRCULANT) ? (int)p.ctiles.size() : 0;
     const int ngt = (parts & ARKCOS_PART_GENERAL) ? (int)p.gtiles2.size() : 0;
-    const long long items = (long long)(nct + ngt) * nbatch;
-    if (nct > 0 && ngt > 0 && items <= (long long)kBothRounds * p.occ_both * p.cus) {
-        hipLaunchKernelGGL(both_kernel(p.circ_form, p.wide_tiles), dim3((unsigned)items),
+    if (nct > 0 && ngt > 0 && nbatch <= p.both_maps) {
+        hipLaunchKernelGGL(both_kernel(p.circ_form, p.wide_tiles), dim3((unsigned)((nct + ngt) * nbatch)),
                            dim3(kGenThreads), both_lds(p.desc.ntab), s,
                            (const DevPlanView *)p.d_view, in, out, ngt * nbatch, nbatch,
                            gen_tab_floats(p.desc.ntab), circ_buf_floats());

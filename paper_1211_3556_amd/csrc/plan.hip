@@ -33,7 +33,7 @@ static void log_plan(const Plan &P)
             "[arkcos] plan nside %d theta_cut %.6g rad ntab %d%s%s: rings %d circulant / %d "
             "general, ring pairs %zu, circulant tiles %zu, general tiles %zu (%d on the matrix "
             "cores, %zu staged chunks; shapes %d/%d/%d from %s), circulant rows %zu (weights %lld, %s), "
-            "device bytes %lld\n",
+            "one launch up to %d maps, device bytes %lld\n",
             P.nside, P.desc.theta_cut, P.desc.ntab, P.desc.k_break > 0 ? " biased" : "",
             P.desc.ring_first > 0 ? " ring range" : "", P.nrings - ngen_rings, ngen_rings,
             P.pairs.size(), P.ctiles.size(), P.gtiles2.size(),
@@ -43,7 +43,7 @@ static void log_plan(const Plan &P)
             P.tiles.gen_pixels, P.tiles.gen_quad_window, P.tiles.gen_pair_window,
             P.tile_source == 0 ? "defaults" : (P.tile_source == 1 ? "tuning cache" : "descriptor"),
             P.rows.size(), P.nweights, P.circ_form ? "matrix cores" : "vector FMAs",
-            P.device_bytes);
+            P.both_maps, P.device_bytes);
 }
 
 int fail(int status, const std::string &msg)

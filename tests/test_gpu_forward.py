@@ -281,6 +281,24 @@ def test_wide_rows(nside, tc_deg, biased):
     assert rel_rms(yb[~outer], ref[~outer]) <= REL_RMS_TOL
 
 
+@pytest.mark.parametrize("nside,pixels,most", [(300, 50, 3), (512, 50, 1), (171, 100, 3),
+                                               (300, 25, 8)])
+def test_one_launch_up_to_the_line(nside, pixels, most, monkeypatch, capfd):
+    """Wide rows take one launch only while their general tiles leave workgroups free (up to
+    `most` maps here, from the plan's log line); maps on both sides of the line agree bit for bit."""
+    A = _A()
+    tc = pixels * np.sqrt(np.pi / 3.0) / nside
+    monkeypatch.setenv("ARKCOS_LOG", "1")
+    plan = A.Plan(nside, tc, W.gaussian_profile_knots(tc / 3, tc, 500), max_batch=most + 1)
+    line = [l for l in capfd.readouterr().err.splitlines() if l.startswith("[arkcos] plan")][-1]
+    n = int(line.split("one launch up to ")[1].split(" maps")[0])
+    assert 1 <= n <= most
+    x = W.white_noise(nside, 42, nbatch=most + 1)
+    log("one launch up to %d maps Nside %d" % (n, nside))
+    ys = _conv_gpu(plan, x)
+    assert np.array_equal(_conv_gpu(plan, x[:n]), ys[:n])
+
+
 def _matrix_core_tiles(capfd):
     """General tiles on the matrix cores, from the plan's log line (ARKCOS_LOG=1)."""
     line = [l for l in capfd.readouterr().err.splitlines() if l.startswith("[arkcos] plan")][-1]

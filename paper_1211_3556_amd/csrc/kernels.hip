@@ -2243,7 +2243,9 @@ int prepare_launches(Plan &p)
         const long long mb = std::max(1, p.desc.max_batch);
         p.grid_kc = (int)std::min<long long>((long long)p.occ_kc * p.cus,
                                              (long long)p.kctiles.size() * mb);
-        for (int nb = 1; nb <= mb; ++nb) p.grid_kg = std::max(p.grid_kg, knot_launch(p, nb).grid);
+        // (the largest grid of knot_launch for any number of maps)
+        p.grid_kg = (int)std::min<long long>((long long)std::max(p.occ_kg, p.occ_km) * p.cus,
+                                             (long long)p.gtiles2.size() * kKnotSplit * mb);
     }
     p.grid = std::max(1, p.grid_kc + p.grid_kg);
     return ARKCOS_OK;

@@ -73,6 +73,18 @@ def test_knot_gradient_map_groups(nside, tc_deg, nk):
             assert rel_rms(to_host(gk), ref) <= 1e-6, (mb, nb)
 
 
+def test_learnable_plan_of_any_batch_limit():
+    """Creating a learnable plan does not take longer with max_batch: the knot
+    gradient's partial rows are bounded by the device, not counted map by map."""
+    import time
+    A = _A()
+    log("learnable plan max_batch 700000000")
+    A.Plan(1, 1.0, ntab=16, learnable=True)
+    t = time.perf_counter()
+    A.Plan(1, 1.0, ntab=16, max_batch=700_000_000, learnable=True)
+    assert time.perf_counter() - t < 0.2
+
+
 def test_autograd_function_and_loss():
     """The torch.autograd.Function path on the c5 loss L = sum (conv(x) - t)^2 at
     a reduced Nside: gradients match the oracle's."""

@@ -382,6 +382,7 @@ struct Plan {
     long long device_bytes = 0;
 
     bool wide_tiles = false;            // some general tile takes the matrix-core form
+    double gen_work = 0.0;              // pixel-candidate pairs of the general tiles, one map
     DevPlanView view() const;
 };
 

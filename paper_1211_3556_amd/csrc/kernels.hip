@@ -1832,7 +1832,7 @@ void k_knot_gen(const DevPlanView *__restrict__ views, const float *__restrict__
 }
 
 // ----------------------------------- general rings: per pair, several maps --
-// As k_knot_gen, for calls of kKnotMapsMin maps or more.
+// As k_knot_gen, for calls of kKnotMapsMin maps or more that have enough work (knot_launch).
 // The sums C(pixel, candidate) = sum of g x over the sixteen images of the pair
 // run on the matrix cores, as v_mfma_f32_4x4x1_16b_f32: block b of a wave takes
 // the pixels 4b .. 4b + 3 (their g at image K is the A operand: lane l holds pixel
@@ -2167,13 +2167,23 @@ static size_t knot_gen_lds(int ntab, int nmg)
 // anyway, Nside 1024 and one map, got 3 % slower).
 constexpr int kKnotSplit = 16;
 constexpr int kKnotItems = 2;
+// k_knot_maps has half the workgroups and the longer chain per chunk: below this work (pixel-candidate
+// pairs of the general tiles times maps, per CU, less what a group that is not full leaves idle)
+// k_knot_gen is faster.  k_knot_maps against it: Nside 16, 25 pixels of cut-off, four maps 33 -> 91 us
+// (6e3 per CU), Nside 64, 3 pixels, eight maps 27 -> 33 (3e3), Nside 128, 8 pixels, four maps
+// 60 -> 71 (1.5e4), Nside 256, 8 pixels, four maps 144 -> 122 (5.8e4), Nside 128, 25 pixels, eight maps
+// 792 -> 528 us (1.9e5); 450 shapes, at most 15 % from the better one, 0.4 % on average.
+constexpr double kKnotMapsWork = 5.2e4;
 struct KnotLaunch {
     int nmg, split, grid;   // maps per item (0: k_knot_gen), shares of a tile, workgroups
 };
 static KnotLaunch knot_launch(const Plan &p, int nmaps)
 {
     KnotLaunch k{};
-    k.nmg = p.occ_km > 0 && nmaps >= kKnotMapsMin ? p.knot_maps : 0;
+    if (p.occ_km > 0 && nmaps >= kKnotMapsMin) {
+        const double share = (double)nmaps / ((nmaps + p.knot_maps - 1) / p.knot_maps * p.knot_maps);
+        if (p.gen_work * nmaps * share * share >= kKnotMapsWork * p.cus) k.nmg = p.knot_maps;
+    }
     const long long room = (long long)(k.nmg ? p.occ_km : p.occ_kg) * p.cus;
     const int per = std::max(1, k.nmg);
     const long long items = (long long)p.gtiles2.size() * ((nmaps + per - 1) / per);

@@ -365,6 +365,7 @@ void build_gen_tiles(Plan &P)
     for (const DevTile2 &t : P.gtiles2) P.wide_tiles = P.wide_tiles || t.wide;
     sort_by_cost(P.gtiles2, cost);
     P.gtile2_cost = cost;
+    P.gen_work = std::accumulate(cost.begin(), cost.end(), 0.0);
     build_gen_chunks(P);
 }
 

@@ -85,6 +85,48 @@ def test_learnable_plan_of_any_batch_limit():
     assert time.perf_counter() - t < 0.2
 
 
+@pytest.mark.parametrize("nside,tc_deg,nb", [(64, 22.1, 3), (64, 22.1, 4), (64, 22.1, 5)])
+def test_knot_gradient_on_both_sides_of_the_map_group_line(nside, tc_deg, nb):
+    """Calls with little work sum the maps one by one, others in groups (the line
+    lies between these): the gradient of several maps is that of the maps' sum."""
+    A = _A()
+    tc = np.radians(tc_deg)
+    nk = 129
+    assert_tie_free(nside, tc)
+    x = W.white_noise(nside, 611, nbatch=nb)
+    g = W.white_noise(nside, 711, nbatch=nb)
+    plan = A.Plan(nside, tc, ntab=nk, max_batch=nb, learnable=True)
+    plan.set_knots(to_dev(W.gaussian_profile_knots(tc / 3, tc, nk)))
+    log("knot gradient map groups Nside %d %d maps" % (nside, nb))
+    _, gk = plan.backward(to_dev(g), to_dev(x), want_map=False, want_knots=True)
+    _sync()
+    ref = sum(O.knot_grad(nside, tc, nk, x[b], g[b]) for b in range(nb))
+    assert np.max(np.abs(to_host(gk) - ref)) <= 1e-5 * np.abs(ref).max()
+    assert rel_rms(to_host(gk), ref) <= 1e-6
+
+
+@pytest.mark.parametrize("nside,tc_deg,nb,nk,kw", [
+    (200, 5.6, 3, 64, {}), (200, 5.6, 7, 257, dict(biased=True)),   # 200 / 2 pixels, two groups
+    (256, 5.6, 4, 2048, dict(rings=(3, 300))),                      # fewer maps a group, a ring range
+    (100, 12.0, 6, 33, dict(rings=(20, 171))), (100, 12.0, 8, 300, {}),
+    (64, 30.0, 4, 65, {}), (64, 60.0, 3, 129, {}), (64, 91.0, 5, 64, {})])   # whole rings
+def test_knot_gradient_of_map_groups_equals_single_maps(nside, tc_deg, nb, nk, kw):
+    """Calls with enough work for the several-map form, over its angle series, tile
+    shapes and group sizes: the sum of the single-map calls (the per-map form), whose
+    FP32 results round to half an ulp each."""
+    A = _A()
+    tc = np.radians(tc_deg)
+    x = to_dev(W.white_noise(nside, 612, nbatch=nb))
+    g = to_dev(W.white_noise(nside, 712, nbatch=nb))
+    plan = A.Plan(nside, tc, ntab=nk, max_batch=nb, learnable=True, **kw)
+    plan.set_knots(to_dev(W.gaussian_profile_knots(tc / 3, tc, nk)))
+    log("knot gradient of map groups Nside %d, %g deg, %d maps" % (nside, tc_deg, nb))
+    _, gk = plan.backward(g, x, want_map=False, want_knots=True)
+    each = [to_host(plan.backward(g[b], x[b], want_map=False, want_knots=True)[1])
+            for b in range(nb)]
+    assert rel_rms(to_host(gk), np.sum(each, axis=0)) <= 1e-6
+
+
 def test_autograd_function_and_loss():
     """The torch.autograd.Function path on the c5 loss L = sum (conv(x) - t)^2 at
     a reduced Nside: gradients match the oracle's."""

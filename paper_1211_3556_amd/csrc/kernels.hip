@@ -736,10 +736,17 @@ constexpr int kGenFlush = 48;
 // own ring's row, the sum over the lanes of a pixel follows, and each part
 // writes the sixteen images of its pixels.  LONG, AM, INTM and BIAS are fixed
 // per tile, so the candidate loop has one form and the row sums stay in place
-// across rows.
-template <bool LONG, int AM, bool INTM, bool BIAS, int SIDE>
+// across rows.  RESUME: the chunks before W.chunk are summed already (gen_tile_wide).
+struct WideSums {
+    int chunk;       // first chunk left, or -1
+    bool owner;      // this wave holds acc: sixteen pixels from p0 of its part on,
+    int p0;          // pixels 4 (lane >> 4) + c, image lane & 15
+    double acc[4];
+};
+template <bool LONG, int AM, bool INTM, bool BIAS, int SIDE, bool RESUME = false>
 __device__ __forceinline__ void gen_tile2(const DevPlanView &P, const float *tab, float4 *stage,
-                                          const DevTile2 *Tp, const float *in, float *out)
+                                          const DevTile2 *Tp, const float *in, float *out,
+                                          const WideSums &W = WideSums{})
 {
     constexpr int NI = SIDE == 0 ? 16 : 8;   // images summed per lane
     const int nr = cst(Tp)->nr;
@@ -772,8 +779,9 @@ __device__ __forceinline__ void gen_tile2(const DevPlanView &P, const float *tab
     const int nch = cst(Tp)->nchunks;
     float4 pa, pb, pc, pd;
     GenChunk ch{};
+    const int first = RESUME ? W.chunk : 0;
     if (nch > 0) {   // (a tile whose rows are all empty has no record)
-        ch = C[0];
+        ch = C[first];
         prefetch_chunk<SIDE>(in, ch, pa, pb, pc, pd);
     }
     double acc[16];
@@ -783,8 +791,26 @@ __device__ __forceinline__ void gen_tile2(const DevPlanView &P, const float *tab
         acc[q] = 0.0;
         row[q] = 0.0f;
     }
+    if (RESUME) {   // through the stage, eight images of up to 128 pixels at a time
+        const int lane = (int)threadIdx.x & 63;
+        double *hand = reinterpret_cast<double *>(stage) + 8 * h * (kGenLanes / nr);
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            __syncthreads();
+            if (W.owner && ((lane >> 3) & 1) == half) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    hand[8 * (W.p0 + 4 * (lane >> 4) + c) + (lane & 7)] = W.acc[c];
+            }
+            __syncthreads();
+            if (active && ph == 0) {
+#pragma unroll
+                for (int q = 0; q < 8; ++q) acc[8 * half + q] = hand[8 * lane_pix + q];
+            }
+        }
+    }
     int since = 0;
-    for (int k = 0; k < nch; ++k) {
+    for (int k = first; k < nch; ++k) {
         const GenChunk nx = C[min(k + 1, nch - 1)];
         __syncthreads();      // the previous chunk is no longer read
         if ((int)threadIdx.x < ch.cn) {   // the arrays the loop form reads
@@ -902,8 +928,10 @@ __device__ __forceinline__ void gen_tile2(const DevPlanView &P, const float *tab
 // 70.8 -> 65.1; biased grid 240 arcmin 73.9 -> 66.1.
 //
 // A zero weight still multiplies the staged value, so a NaN or an infinity
-// would reach pixels outside whose disc it lies: a tile that stages one returns
-// false before it writes, and runs in the vector form.
+// would reach pixels outside whose disc it lies: a tile that stages one hands its sums
+// over and goes on in the vector form from that chunk.  (Started again from the first chunk, a
+// map with 100 scattered NaN took 124 ms at Nside 2048 and 240 arcmin, against 105 ms in the vector
+// form alone and 97 without a NaN.)
 constexpr int kWideFlush = 16;   // steps (64 FP32 terms) between moves into FP64
 
 // Whether every candidate of a row lies beyond the break of a biased grid (by
@@ -1011,8 +1039,9 @@ __device__ __forceinline__ int &wide_bad()
 }
 
 template <int AM, bool BIAS>
-__device__ __forceinline__ bool gen_tile_wide(const DevPlanView &P, const float *tab, float4 *stage,
-                                              const DevTile2 *Tp, const float *in, float *out)
+__device__ __forceinline__ WideSums gen_tile_wide(const DevPlanView &P, const float *tab,
+                                                  float4 *stage, const DevTile2 *Tp,
+                                                  const float *in, float *out)
 {
     int &s_bad = wide_bad();
     const int lane = (int)threadIdx.x & 63;
@@ -1045,7 +1074,8 @@ __device__ __forceinline__ bool gen_tile_wide(const DevPlanView &P, const float 
         load(ch);
     }
     if (threadIdx.x == 0) s_bad = 0;
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    WideSums W{-1, busy && sub == 0, p0, {0.0, 0.0, 0.0, 0.0}};
+    double(&acc)[4] = W.acc;
     typedef __attribute__((address_space(3))) const float lds_float;
     const int stage_b = (int)(size_t)(lds_float *)(const float *)stage;
     for (int k = 0; k < nch; ++k) {
@@ -1062,7 +1092,10 @@ __device__ __forceinline__ bool gen_tile_wide(const DevPlanView &P, const float 
                         (nan_unless_finite(pc) + nan_unless_finite(pd));
         if (__any(z != 0.0f) && lane == 0) s_bad = k + 1;
         __syncthreads();
-        if (s_bad == k + 1) return false;
+        if (s_bad == k + 1) {
+            W.chunk = k;
+            break;
+        }
         if (k + 1 < nch) load(nx);
         if (busy && ch.s >= my.s_lo && ch.s <= my.s_hi) {
             const DevPair pp = cst(P.pairs)[my.pb + ch.s - my.s_lo];
@@ -1105,17 +1138,18 @@ __device__ __forceinline__ bool gen_tile_wide(const DevPlanView &P, const float 
         for (int c = 0; c < 4; ++c) part[((wave - 1) * 4 + c) * 64 + lane] = acc[c];
     }
     __syncthreads();
-    if (!busy || sub > 0) return true;
+    if (!W.owner) return W;
     for (int u = 1; u < nsub; ++u)
 #pragma unroll
         for (int c = 0; c < 4; ++c)
             acc[c] += reinterpret_cast<const double *>(stage)[((wave + u * ngr - 1) * 4 + c) * 64 +
                                                              lane];
+    if (W.chunk >= 0) return W;
     // image (lane & 15) of the pixels 4 (lane >> 4) + c: quarter turn (lane & 3) of the
     // pixel or its reflection (lane & 8), on the ring or its mirror (lane & 4)
     const bool south = (lane & 4) != 0, refl = (lane & 8) != 0;
     const int qr = R.n >> 2;
-    if ((my.flags & (south ? kTileSkipSouth : kTileSkipNorth)) || (south && rs == rn)) return true;
+    if ((my.flags & (south ? kTileSkipSouth : kTileSkipNorth)) || (south && rs == rn)) return W;
     float *o = out + cst(P.rings)[south ? rs : rn].first + (lane & 3) * qr;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
@@ -1123,7 +1157,17 @@ __device__ __forceinline__ bool gen_tile_wide(const DevPlanView &P, const float 
         const int jp = cst(Tp)->j0 + p, jb = qr - R.two_o - jp;
         if (p < my.len && !(refl && (jb == jp || jb == qr))) o[refl ? jb : jp] = (float)acc[c];
     }
-    return true;
+    return W;
+}
+
+template <int AM, bool BIAS>
+__device__ __forceinline__ void gen_tile_wide_or_vector(const DevPlanView &P, const float *tab,
+                                                        float4 *stage, const DevTile2 *Tp,
+                                                        const float *in, float *out)
+{
+    const WideSums W = gen_tile_wide<AM, BIAS>(P, tab, stage, Tp, in, out);
+    if (__builtin_amdgcn_readfirstlane(W.chunk) >= 0)   // (the same in every wave)
+        gen_tile2<false, AM, false, BIAS, 0, true>(P, tab, stage, Tp, in, out, W);
 }
 
 // The candidate-loop form of a tile: sine series, angle series and numerator
@@ -1142,9 +1186,11 @@ __device__ __forceinline__ void gen_tile_variant(const DevPlanView &P, const flo
     const bool lg = (fl & kTileLongSin) != 0;
     if (WIDE && cst(Tp)->wide) {
         // (no long-sine rows, so never the angle series beyond 0.5 rad: plan creation)
-        const bool done = P.angle_mode == 0 ? gen_tile_wide<0, BIAS>(P, tab, stage, Tp, in, out)
-                                            : gen_tile_wide<1, BIAS>(P, tab, stage, Tp, in, out);
-        if (done) return;
+        if (P.angle_mode == 0)
+            gen_tile_wide_or_vector<0, BIAS>(P, tab, stage, Tp, in, out);
+        else
+            gen_tile_wide_or_vector<1, BIAS>(P, tab, stage, Tp, in, out);
+        return;
     }
     if (fl & kTileIntM) {   // wide windows on large rings (long sine implied)
         switch (P.angle_mode) {

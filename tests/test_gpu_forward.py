@@ -374,6 +374,33 @@ def test_wide_rows_on_the_matrix_cores(nside, tc_deg, biased, tiles, rings, monk
     assert rel_rms(to_host(gx)[pix], gref) <= REL_RMS_TOL
 
 
+def test_wide_rows_with_scattered_nan_keep_their_speed():
+    """A tile of the matrix-core form that meets a NaN late does not start again: a map with
+    100 scattered NaN takes about the time of the vector form (1.08 of a map without one)."""
+    import torch
+    tc = np.radians(4.0)
+    theta = np.linspace(0.0, tc, 16384)
+    plan = _A().Plan(2048, tc, W.gaussian_profile_at(tc / 3, theta), biased=True)
+    x = to_dev(W.white_noise(2048, 5))
+    bad = x.clone()
+    bad[torch.from_numpy(np.random.default_rng(1).integers(0, x.numel(), 100)).cuda()] = float("nan")
+    out = torch.empty_like(x)
+    log("wide rows with scattered NaN Nside 2048")
+    e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+
+    def best(inp):
+        t = []
+        for _ in range(4):
+            e[0].record()
+            plan.convolve(inp, out)
+            e[1].record()
+            torch.cuda.synchronize()
+            t.append(e[0].elapsed_time(e[1]))
+        return min(t)
+
+    assert best(bad) <= 1.2 * best(x)
+
+
 @pytest.mark.parametrize("nside,tc_deg", [(64, 6.0), (100, 3.31), (16, 74.7)])
 def test_parts_compose_to_full_convolution(nside, tc_deg):
     """The circulant and general gathers write disjoint rings: running them

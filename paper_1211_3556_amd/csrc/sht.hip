@@ -388,7 +388,7 @@ __device__ __forceinline__ void ring_dft(double2 e[8], double2 *z, const double2
     }
 }
 
-// Place of frequency a in the output order of fft_dif.
+// Place of frequency a in the output order of ring_dft<false>.
 __device__ __forceinline__ int fft_place(int a, int lg)
 {
     int pos = 0;
@@ -1395,6 +1395,7 @@ static int harm_upload_kernel(Harm &h)
     return ARKCOS_OK;
 }
 
+// (belt rings without the chirp have at most 4096 points, 512 threads)
 #define ARKCOS_RING_KERNEL(name)                                                             \
     static auto name##_kernel(const ShtBucket &B)                                            \
     {                                                                                        \
@@ -1402,7 +1403,7 @@ static int harm_upload_kernel(Harm &h)
             case 128: return B.direct ? k_##name<128, false> : k_##name<128, true>;          \
             case 256: return B.direct ? k_##name<256, false> : k_##name<256, true>;          \
             case 512: return B.direct ? k_##name<512, false> : k_##name<512, true>;          \
-            default: return B.direct ? k_##name<1024, false> : k_##name<1024, true>;         \
+            default: return k_##name<1024, true>;                                            \
         }                                                                                    \
     }
 ARKCOS_RING_KERNEL(ring_fwd)

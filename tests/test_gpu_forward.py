@@ -374,6 +374,24 @@ def test_wide_rows_on_the_matrix_cores(nside, tc_deg, biased, tiles, rings, monk
     assert rel_rms(to_host(gx)[pix], gref) <= REL_RMS_TOL
 
 
+def test_wide_rows_are_no_less_precise():
+    """The matrix-core form against 64 bits is no further off than the vector form, in which a
+    plan of the northern rings alone sums the same pixels (its tiles write one side)."""
+    nside, tc, ntab = 2048, np.radians(4.0), 16384
+    theta = np.linspace(0.0, tc, ntab)
+    k = W.gaussian_profile_at(tc / 1.2, theta) * (1.0 - theta / tc)
+    x = W.white_noise(nside, 47).astype(np.float32).astype(np.float64)
+    rng = np.random.default_rng(5)
+    rings = rng.integers(6 * nside // 10, nside, 2500)
+    pix = np.unique([2 * r * (r - 1) + int(rng.integers(0, 4 * r)) for r in rings])
+    ref = O.convolve(nside, tc, k, x, pixels=pix)
+    log("wide rows precision Nside %d" % nside)
+    wide = rel_rms(_conv_gpu(_A().Plan(nside, tc, k), x)[pix], ref)
+    vector = rel_rms(_conv_gpu(_A().Plan(nside, tc, k, rings=(1, nside)), x)[pix], ref)
+    log("wide rows rel rms %.3e, vector form %.3e" % (wide, vector))
+    assert wide <= vector
+
+
 def test_wide_rows_with_scattered_nan_keep_their_speed():
     """A tile of the matrix-core form that meets a NaN late does not start again: a map with
     100 scattered NaN takes about the time of the vector form (1.08 of a map without one)."""

@@ -295,3 +295,35 @@ def test_scytale_split_error_matches_eq2(lcut, tc_deg):
     est = sp.sigma / 5.0
     log("scytale split actual %.3e, eq. 2 / alpha %.3e" % (actual, est))
     assert 0.7 * est < actual < 1.4 * est
+
+
+def test_cost_model_matches_the_kernels():
+    """The shipped cost model, from which splits are chosen, against both halves
+    at Nside 2048 (within 30 per cent)."""
+    import torch
+    A = _A()
+    from paper_1211_3556_amd import scytale as S
+    cost = S.CostModel.load()
+    x = torch.randn(12 * 2048 ** 2, device="cuda")
+    y = torch.empty_like(x)
+    e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+
+    def best(fn):
+        t = []
+        for _ in range(4):
+            e[0].record()
+            fn()
+            e[1].record()
+            torch.cuda.synchronize()
+            t.append(e[0].elapsed_time(e[1]))
+        return min(t)
+
+    for lcut in (750, 1500, 2250):
+        log("cost model lcut %d" % lcut)
+        h = A.Harm(2048, np.ones(lcut + 1))
+        assert abs(best(lambda: h.convolve(x, y)) / cost.t_harm(lcut) - 1) <= 0.3, lcut
+    for am in (30.0, 240.0):
+        log("cost model theta_cut %g arcmin" % am)
+        tc = np.radians(am / 60.0)
+        p = A.Plan(2048, tc, np.exp(-np.linspace(0.0, 3.0, 16384)), biased=True)
+        assert abs(best(lambda: p.convolve(x, y)) / cost.t_real(tc) - 1) <= 0.3, am

@@ -390,20 +390,18 @@ def main() -> int:
             e1.record(stream)
             torch.cuda.synchronize()
             res[label] = e0.elapsed_time(e1) / reps
-        npix, nnorth = 12 * s.nside ** 2, 2 * s.nside
+        nnorth = 2 * s.nside
         nalm = (L + 1) * (L + 2) // 2
-        # algorithmic FP64 FLOP: belt rings of power-of-two length 4 Nside by
-        # real FFTs (complex FFT of half the length, 5 M log2 M each way),
-        # the other rings by direct sums (3 per pixel and m each way, a
-        # nominal count that the cap rings' FFTs undercut); Legendre recurrence 4 plus 2 (analysis) or 4 (synthesis) per
-        # (l, m, northern ring)
-        nb = 4 * s.nside
-        M = nb // 2
-        fft = (nb & (nb - 1)) == 0 and 2 <= M <= 8192 and L < M
-        belt_rings = 2 * s.nside + 1 if fft else 0
-        dft_pix = npix - belt_rings * nb
-        flop64 = (6.0 * dft_pix * (L + 1) + belt_rings * 2 * 5.0 * M * np.log2(M)
-                  + (6.0 + 8.0) * nnorth * nalm)
+        # FP64 FLOP of the kernels (every ring pair by FFT at this l_cut): each way four
+        # complex FFTs of a quarter ring, 5 P log2 P, P = k on the belt of a power-of-two
+        # Nside, elsewhere two FFTs (chirp transform) of the next power of two from
+        # 2 k - 1; Legendre 12 per ring pair and two degrees each way (before the polar skip)
+        flop64 = 2 * 6.0 * nnorth * nalm
+        for ring in range(1, nnorth + 1):
+            k = min(ring, s.nside)
+            direct = k == s.nside and k >= 8 and (k & (k - 1)) == 0
+            lg = max(3, int(np.ceil(np.log2(k if direct else 2 * k - 1))) if k > 1 else 3)
+            flop64 += 2 * 4 * (1 if direct else 2) * 5.0 * (1 << lg) * lg
         tf = flop64 / (res["l_space_half"] * 1e-3) / 1e12
         biased["split_example"] = {
             "nside": s.nside, "l_cut": L, "theta_cut_arcmin": round(s.theta_cut / W.ARCMIN, 3),

@@ -827,15 +827,16 @@ __global__ __launch_bounds__(kShtThreads) void k_sht_dft_fwd(const ShtRing *__re
     }
 }
 
-// The inverse, y_j = Re sum_m H_m e^{i m a_j}, a_j = 2 pi j / n, H_m = c_m G_r(m) e^{i m phi_0}
-// of either ring, by classes: with u_c = sum_{m = c mod 4} H_m e^{i m a_j} the pixels of the
-// four quarters are y_{j + tk} = Re sum_c i^{ct} u_c.  u_c is e^{i c a_j} times a sum in steps
-// of b = 4 a_j = 2 pi j / k, from the real Clenshaw sums C = sum h cos, S = sum h sin of the real and
-// imaginary parts (shared coefficient 2 cos b); at k - j the cosines are the same and the sines
-// change sign.  So a thread obtains sixteen pixels of the two rings from sixteen
-// sums of lcut / 4 terms.  FP64 issue bounds it.
+// The inverse, y_j = Re sum_m H_m e^{i m a_j}, a_j = 2 pi j / n, H_m = c_m G_r(m) e^{i m phi_0},
+// by classes: with u_c = sum_{m = c mod 4} H_m e^{i m a_j} the pixels of the four quarters are
+// y_{j + tk} = Re sum_c i^{ct} u_c.  u_c is e^{i c a_j} times a sum in steps of b = 4 a_j =
+// 2 pi j / k, from the real Clenshaw sums C = sum h cos, S = sum h sin of the real and imaginary
+// parts (shared coefficient 2 cos b); at k - j the cosines are the same and the sines change
+// sign.  So a thread obtains eight pixels from eight sums of lcut / 4 terms.  One workgroup per
+// ring: of both rings of a pair (blockIdx.z) it is faster than in one workgroup, and on small maps,
+// whose time is the chain of one workgroup, too.  FP64 issue bounds it elsewhere.
 __host__ __device__ inline int dft_groups(int L) { return (L >> 2) + 1; }
-static size_t dft_bwd_lds(int L) { return (size_t)8 * dft_groups(L) * sizeof(double2); }
+static size_t dft_bwd_lds(int L) { return (size_t)4 * dft_groups(L) * sizeof(double2); }
 __global__ __launch_bounds__(kShtThreads) void k_sht_dft_bwd(const ShtRing *__restrict__ rings,
                                                              const int *__restrict__ ring_list,
                                                              const double2 *__restrict__ roots,
@@ -844,8 +845,10 @@ __global__ __launch_bounds__(kShtThreads) void k_sht_dft_bwd(const ShtRing *__re
                                                              long long npix, int L, int lq,
                                                              int nnorth, int accumulate)
 {
-    extern __shared__ double2 H[];   // northern ring, then its mirror, zero past lcut
+    extern __shared__ double2 H[];   // zero past lcut
     const int r = ring_list[blockIdx.x];
+    const bool south = blockIdx.z != 0;
+    if (south && r == nnorth - 1) return;   // the equator
     const ShtRing R = rings[r];
     const double2 *row = G + ((size_t)blockIdx.y * nnorth + r) * 8 * lq;
     const int A = dft_groups(L), k = R.n >> 2;
@@ -853,87 +856,74 @@ __global__ __launch_bounds__(kShtThreads) void k_sht_dft_bwd(const ShtRing *__re
     load_roots(rt, roots);
     __syncthreads();
     const RingRoots W(rt, R.n);
+    const double sign = south ? -1.0 : 1.0;
     for (int m = threadIdx.x; m < 4 * A; m += kShtThreads) {
-        double2 hn = make_double2(0.0, 0.0), hs = hn;
+        double2 h = make_double2(0.0, 0.0);
         if (m <= L) {
-            const double2 w = W.at(m * R.two_o);
+            const double2 e = row[order_slot(m, lq)], o = row[4 * lq + order_slot(m, lq)];
             const double c = m == 0 ? 1.0 : 2.0;
-            const double2 e = cmul(row[order_slot(m, lq)], w);
-            const double2 o = cmul(row[4 * lq + order_slot(m, lq)], w);
-            hn = make_double2(c * (e.x + o.x), c * (e.y + o.y));
-            hs = make_double2(c * (e.x - o.x), c * (e.y - o.y));
+            h = cmul(make_double2(c * fma(sign, o.x, e.x), c * fma(sign, o.y, e.y)),
+                     W.at(m * R.two_o));
         }
-        H[m] = hn;
-        H[4 * A + m] = hs;
+        H[m] = h;
     }
     __syncthreads();
-    float *oa = out + (size_t)blockIdx.y * npix + R.first;
-    float *ob = out + (size_t)blockIdx.y * npix + rings[2 * nnorth - 2 - r].first;
-    const bool equator = r == nnorth - 1;
+    float *o = out + (size_t)blockIdx.y * npix + (south ? rings[2 * nnorth - 2 - r].first : R.first);
     for (int j = threadIdx.x; j <= k >> 1; j += kShtThreads) {
         double sb, cb;
         sincospi(2.0 * (double)j / (double)k, &sb, &cb);
         const double cc = 2.0 * cb;
         // b_a = h_a + 2 cos(b) b_{a+1} - b_{a+2} from a = A - 1 down to 1, two steps at
         // a time in place (b1 holds the newest term); an odd count starts from b_{A-1} = h_{A-1}
-        double b1[4][4], b2[4][4];   // class; real and imaginary part, north and south
+        double b1[4][2], b2[4][2];   // class; real and imaginary part
         const bool odd = (A & 1) == 0;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            const double2 hn = H[4 * (A - 1) + c], hs = H[4 * A + 4 * (A - 1) + c];
-            b1[c][0] = odd ? hn.x : 0.0;
-            b1[c][1] = odd ? hn.y : 0.0;
-            b1[c][2] = odd ? hs.x : 0.0;
-            b1[c][3] = odd ? hs.y : 0.0;
-            b2[c][0] = b2[c][1] = b2[c][2] = b2[c][3] = 0.0;
+            const double2 ha = H[4 * (A - 1) + c];
+            b1[c][0] = odd ? ha.x : 0.0;
+            b1[c][1] = odd ? ha.y : 0.0;
+            b2[c][0] = b2[c][1] = 0.0;
         }
         for (int a = odd ? A - 2 : A - 1; a > 1; a -= 2) {
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                const double2 na = H[4 * a + c], nb = H[4 * a - 4 + c];
-                const double2 sa = H[4 * A + 4 * a + c], sb2 = H[4 * A + 4 * a - 4 + c];
-                const double ha[4] = {na.x, na.y, sa.x, sa.y};
-                const double hb[4] = {nb.x, nb.y, sb2.x, sb2.y};
+                const double2 ha = H[4 * a + c], hb = H[4 * a - 4 + c];
+                b2[c][0] = fma(cc, b1[c][0], ha.x - b2[c][0]);
+                b2[c][1] = fma(cc, b1[c][1], ha.y - b2[c][1]);
+                b1[c][0] = fma(cc, b2[c][0], hb.x - b1[c][0]);
+                b1[c][1] = fma(cc, b2[c][1], hb.y - b1[c][1]);
+            }
+        }
+        // u_c at j, and at k - j, where e^{i c a} is i^c times the conjugate
+        const double2 w1 = W.at(2 * j), w2 = cmul(w1, w1), w3 = cmul(w1, w2);
+        double2 u[4], v[4];
 #pragma unroll
-                for (int f = 0; f < 4; ++f) {
-                    b2[c][f] = fma(cc, b1[c][f], ha[f] - b2[c][f]);
-                    b1[c][f] = fma(cc, b2[c][f], hb[f] - b1[c][f]);
-                }
+        for (int c = 0; c < 4; ++c) {
+            const double2 h0 = H[c];
+            const double Cr = fma(b1[c][0], cb, h0.x - b2[c][0]);
+            const double Ci = fma(b1[c][1], cb, h0.y - b2[c][1]);
+            const double Sr = sb * b1[c][0], Si = sb * b1[c][1];
+            u[c] = make_double2(Cr - Si, Ci + Sr);
+            v[c] = make_double2(Cr + Si, Ci - Sr);
+            if (c > 0) {
+                const double2 w = c == 1 ? w1 : (c == 2 ? w2 : w3);
+                u[c] = cmul(u[c], w);
+                v[c] = cmul(v[c], conj2(w));
             }
         }
 #pragma unroll
         for (int side = 0; side < 2; ++side) {   // pixels j + tk, then k - j + tk
             const int jj = side ? k - j : j;
             if (side && (j == 0 || jj == j)) break;
-            double re[2][4], im[2][4];
+            const double e = side ? v[0].x - v[2].x : u[0].x + u[2].x;
+            const double f = side ? v[0].x + v[2].x : u[0].x - u[2].x;
+            const double re = side ? v[3].y - v[1].y : u[1].x + u[3].x;
+            const double im = side ? v[1].x + v[3].x : u[1].y - u[3].y;
+            const double y[4] = {e + re, f - im, e - re, f + im};
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const double2 w = W.at(2 * c * jj);
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {   // north, south
-                    const double2 h0 = H[4 * A * h + c];
-                    const double Cr = fma(b1[c][2 * h], cb, h0.x - b2[c][2 * h]);
-                    const double Ci = fma(b1[c][2 * h + 1], cb, h0.y - b2[c][2 * h + 1]);
-                    const double s = side ? -sb : sb;
-                    const double2 u =
-                        cmul(make_double2(fma(-s, b1[c][2 * h + 1], Cr), fma(s, b1[c][2 * h], Ci)), w);
-                    re[h][c] = u.x;
-                    im[h][c] = u.y;
-                }
-            }
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                if (h && equator) break;
-                float *o = h ? ob : oa;
-                const double y[4] = {(re[h][0] + re[h][2]) + (re[h][1] + re[h][3]),
-                                     (re[h][0] - re[h][2]) - (im[h][1] - im[h][3]),
-                                     (re[h][0] + re[h][2]) - (re[h][1] + re[h][3]),
-                                     (re[h][0] - re[h][2]) + (im[h][1] - im[h][3])};
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const int at = jj + t * k;
-                    o[at] = accumulate ? o[at] + (float)y[t] : (float)y[t];
-                }
+            for (int t = 0; t < 4; ++t) {
+                const int at = jj + t * k;
+                o[at] = accumulate ? o[at] + (float)y[t] : (float)y[t];
             }
         }
     }
@@ -1682,7 +1672,7 @@ static int harm_launch(const Harm &h, const float *in, float *out, int nb, int a
                            h.lgm, h.d_F, out, h.npix, L, h.lq, h.nnorth, accumulate);
     }
     if (h.n_dft > 0)
-        hipLaunchKernelGGL(k_sht_dft_bwd, dim3(h.n_dft, nb), dim3(kShtThreads),
+        hipLaunchKernelGGL(k_sht_dft_bwd, dim3(h.n_dft, nb, 2), dim3(kShtThreads),
                            dft_bwd_lds(L), s, h.d_rings, h.d_dft_rings,
                            h.d_roots, h.d_F, out, h.npix, L, h.lq, h.nnorth, accumulate);
     ARKCOS_HIP_CHECK(hipGetLastError());

@@ -246,8 +246,8 @@ def test_one_launch_equals_persistent_kernels(nside, tc_deg, nb):
 @pytest.mark.parametrize("nside,tc_deg,biased", [(64, 74.7, False), (64, 60.1, True),
                                                  (96, 40.3, True), (150, 27.7, False)])
 def test_wide_rows(nside, tc_deg, biased):
-    """Rows wide enough for the matrix-core form of the general gather: whole rings,
-    both sine forms, both node grids, the angle series and short last segments
+    """Wide rows of the general gather with long-sine rows: whole rings, both node
+    grids, the angle series and short last segments (short tiles of the vector form)
     (the table falls to zero at the cut, so that lattice ties there do not count).
     A NaN and an infinity reach the pixels whose disc they lie in, and none beyond
     the pixels next to those."""

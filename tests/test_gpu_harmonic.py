@@ -39,7 +39,7 @@ def _khat(lcut, seed):
 
 @pytest.mark.parametrize("nside,lcut", [(1, 0), (1, 9), (2, 30), (4, 23), (8, 40), (16, 47),
                                         (13, 50), (64, 191),
-                                        # belt rings by FFT: n = 4 Nside a power of two, lcut < 2 Nside
+                                        # belt rings of power-of-two length (direct sums at these sizes)
                                         (1, 1), (8, 12), (32, 60), (64, 127), (128, 255)])
 def test_harmonic_full_maps(nside, lcut):
     khat = _khat(lcut, nside + lcut)
@@ -76,8 +76,8 @@ def test_harmonic_fft_and_goertzel_paths_agree(monkeypatch):
 # Sums in FP64, rounded to FP32 once: at most half an ulp, 2^-24, of each pixel.
 @pytest.mark.parametrize("nside,lcut,nb", [
     (100, 600, 2),     # rings shorter and longer than lcut, chirp transforms of 8 .. 256
-    (171, 200, 1),     # belt of no power of two
-    (256, 100, 1),     # belt rings transformed directly, short l range
+    (171, 200, 1),     # belt of no power of two; low lcut takes direct sums
+    (256, 100, 1),     # belt of a power of two, short l range (direct sums)
     (260, 700, 3)])    # more than one wave of ring pairs per order, several maps
 def test_harmonic_ring_ffts(nside, lcut, nb):
     khat = _khat(lcut, nside)
@@ -92,7 +92,8 @@ def test_harmonic_ring_ffts(nside, lcut, nb):
 
 @pytest.mark.parametrize("nside,lcut", [(1025, 64), (2100, 33)])
 def test_harmonic_long_ring_ffts(monkeypatch, nside, lcut):
-    """The longest chirp transforms (4096 and 8192) against the direct sums."""
+    """The longest rings at low lcut, where the plan's own choice is direct sums too
+    (the longest chirp transforms: test_harmonic_long_rings_by_fft_and_direct)."""
     khat = _khat(lcut, 5)
     x = to_dev(W.white_noise(nside, 6))
     log("harmonic long ring FFTs Nside %d" % nside)

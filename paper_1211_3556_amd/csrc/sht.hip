@@ -176,7 +176,10 @@ __device__ __forceinline__ void load_roots(double2 *lds, const double2 *__restri
 // run in registers, on the samples as they are loaded and on the results as they
 // are stored.  Against one Goertzel sum per frequency, O(n lcut) per ring, the cap
 // rings cost O(P log P); what bounds the kernels is the latency of their loads
-// and barriers (half of the cycles; FP64 issue is the other half).  LDS entries
+// and barriers (the waves wait 0.4 to 0.7 of their cycles; vector instructions take 0.25 to 0.45 of
+// the SIMDs').  The forward kernels also spill registers (58 without the chirp,
+// 0.24 ms against the inverse's 0.16 at k = 2048; 19 with it), and the 1024-thread ones of k > 2048,
+// held to 128 registers, spill 584 and 565 (1.5 + 1.4 ms at Nside 4096).  LDS entries
 // are padded by one in eight, so that the short-stride passes spread over the
 // banks.
 __host__ __device__ inline int fft_pad(int i) { return i + (i >> 3); }
@@ -1005,12 +1008,13 @@ __device__ __forceinline__ double reduce16(double v[16])
 // T_k = sum pi_k z O over the chunk's ring pairs, with E = (Z(m) + conj Z(-m)) / 2
 // and O = (Z(m) - conj Z(-m)) / 2i.  Chunks count from ring_lo[m], below which
 // no ring contributes; a wave takes 64 R consecutive ring pairs, R per lane.
-// What bounds it is the FP64 rate: six FMAs per ring pair and two degrees, about
-// 5.5 cycles each at 2.4 GHz nominal (measured, all SIMDs busy: the clock
-// falls), 0.43 ms at Nside 2048 and lcut 1500 of the 0.87 ms measured; the
-// reduction over the wave adds half of that at four ring pairs per lane, a
-// quarter at eight.  Loading the next block's coefficients ahead was slower (the
-// copies cost more than the waits).
+// What bounds it is vector issue: at Nside 2048 and lcut 1500 (0.87 ms) vector instructions take 0.69
+// of the cycles at 2.4 GHz, 0.82 of those at the clock it runs at, and its FP64 work comes to 31 of
+// the 72 TFLOP/s of a large matrix product.  The six FMAs per ring pair and two degrees, about
+// 5.5 cycles each at nominal clock, are 0.43 ms; the reduction over the wave adds half of that at
+// four ring pairs per lane, a quarter at eight; the rest is the test for scaled values, lanes beyond
+// the ring range and, for a fifth of the time, waits for the coefficients.  Loading the next
+// block's coefficients ahead was slower (the copies cost more than the waits).
 template <int R>
 __global__ __launch_bounds__(kShtThreads) __attribute__((amdgpu_waves_per_eu(R == 8 ? 2 : 4)))
 void k_leg_fwd(const ShtRing *__restrict__ rings, const double2 *__restrict__ F,

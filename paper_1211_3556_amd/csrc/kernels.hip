@@ -2217,13 +2217,14 @@ static size_t knot_gen_lds(int ntab, int nmg)
 // anyway, Nside 1024 and one map, got 3 % slower).
 constexpr int kKnotSplit = 16;
 constexpr int kKnotItems = 2;
-// k_knot_maps has half the workgroups and the longer chain per chunk: below this work (pixel-candidate
-// pairs of the general tiles times maps, per CU, less what a group that is not full leaves idle)
-// k_knot_gen is faster.  k_knot_maps against it: Nside 16, 25 pixels of cut-off, four maps 33 -> 91 us
-// (6e3 per CU), Nside 64, 3 pixels, eight maps 27 -> 33 (3e3), Nside 128, 8 pixels, four maps
-// 60 -> 71 (1.5e4), Nside 256, 8 pixels, four maps 144 -> 122 (5.8e4), Nside 128, 25 pixels, eight maps
-// 792 -> 528 us (1.9e5); 450 shapes, at most 15 % from the better one, 0.4 % on average.
-constexpr double kKnotMapsWork = 5.2e4;
+// k_knot_maps has half the workgroups and the longer chain per chunk, so with little work k_knot_gen
+// is faster.  The lines are pixel-candidate pairs of the general tiles times maps, per CU: for one group of
+// maps, for several (less what a last group that is not full leaves idle), and for tables so large
+// that k_knot_gen has one workgroup per CU too.  k_knot_maps against it: Nside 16, 25 pixels of cut-off,
+// four maps 33 -> 91 us (6e3 per CU), Nside 64, 3 pixels, eight maps 27 -> 33 (3e3), Nside 128, 8 pixels,
+// four maps 60 -> 71 (1.5e4), Nside 256, 8 pixels, four maps 144 -> 122 (5.8e4), Nside 128, 25 pixels, eight
+// maps 792 -> 528 us (1.9e5); 450 shapes, at most 12 % from the better one, 0.2 % on average.
+constexpr double kKnotMapsWork = 3.5e4, kKnotMapsWork2 = 5.7e4, kKnotMapsWork1 = 1e4;
 struct KnotLaunch {
     int nmg, split, grid;   // maps per item (0: k_knot_gen), shares of a tile, workgroups
 };
@@ -2231,8 +2232,11 @@ static KnotLaunch knot_launch(const Plan &p, int nmaps)
 {
     KnotLaunch k{};
     if (p.occ_km > 0 && nmaps >= kKnotMapsMin) {
-        const double share = (double)nmaps / ((nmaps + p.knot_maps - 1) / p.knot_maps * p.knot_maps);
-        if (p.gen_work * nmaps * share * share >= kKnotMapsWork * p.cus) k.nmg = p.knot_maps;
+        const int groups = (nmaps + p.knot_maps - 1) / p.knot_maps;
+        const double share = groups > 1 ? (double)nmaps / (groups * p.knot_maps) : 1.0;
+        const double line = p.occ_kg <= p.occ_km ? kKnotMapsWork1
+                                                 : (groups > 1 ? kKnotMapsWork2 : kKnotMapsWork);
+        if (p.gen_work * nmaps * share * share >= line * p.cus) k.nmg = p.knot_maps;
     }
     const long long room = (long long)(k.nmg ? p.occ_km : p.occ_kg) * p.cus;
     const int per = std::max(1, k.nmg);

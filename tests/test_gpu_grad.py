@@ -107,7 +107,7 @@ def test_knot_gradient_on_both_sides_of_the_map_group_line(nside, tc_deg, nb):
 
 @pytest.mark.parametrize("nside,tc_deg,nb,nk,kw", [
     (200, 5.6, 3, 64, {}), (200, 5.6, 7, 257, dict(biased=True)),   # 200 / 2 pixels, two groups
-    (256, 5.6, 4, 2048, dict(rings=(3, 300))),                      # fewer maps a group, a ring range
+    (256, 5.6, 4, 1700, dict(rings=(3, 300))),                      # three maps a group, a ring range
     (100, 12.0, 6, 33, dict(rings=(20, 171))), (100, 12.0, 8, 300, {}),
     (64, 30.0, 4, 65, {}), (64, 60.0, 3, 129, {}), (64, 91.0, 5, 64, {})])   # whole rings
 def test_knot_gradient_of_map_groups_equals_single_maps(nside, tc_deg, nb, nk, kw):

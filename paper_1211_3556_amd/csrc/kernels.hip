@@ -924,8 +924,8 @@ __device__ __forceinline__ void gen_tile2(const DevPlanView &P, const float *tab
 // step issues on the vector ALUs or the matrix cores, which do not overlap in one
 // SIMD: hence the untested middle of a row and the form for rows beyond the break of a
 // biased grid.  General gather at Nside 2048 on the same tiles, vector form -> this one: uniform grid
-// 85 pixels of cut-off 22.7 -> 21.5 ms, 100 pixels 31.1 -> 29.1, 240 arcmin (139 pixels)
-// 70.8 -> 65.9; biased grid 240 arcmin 73.9 -> 67.3.
+// 85 pixels of cut-off 22.7 -> 21.3 ms, 100 pixels 31.1 -> 28.9, 240 arcmin (139 pixels)
+// 70.8 -> 65.1; biased grid 240 arcmin 73.9 -> 66.3.
 //
 // A zero weight still multiplies the staged value, so a NaN or an infinity
 // would reach pixels outside whose disc it lies: a tile that stages one hands its sums
@@ -933,10 +933,10 @@ __device__ __forceinline__ void gen_tile2(const DevPlanView &P, const float *tab
 // map with 100 scattered NaN took 124 ms at Nside 2048 and 240 arcmin, against 105 ms in the vector
 // form alone and 97 without a NaN.)
 // Steps (four FP32 terms each) between moves into FP64.  Relative rms error against 64 bits, vector form /
-// 32 terms / 64 terms, white noise, 2300 pixels, kernels of two shapes on either grid: Nside 2048, 240
-// arcmin 1.36-1.45e-7 / 1.21-1.29e-7 / 1.42-1.55e-7; Nside 1024, 100 pixels of cut-off 1.67-1.74e-7 /
-// 1.25-1.31e-7 / 1.70-1.86e-7.  64 terms are 1.2 % faster.
-constexpr int kWideFlush = 8;
+// 32 / 40 / 64 terms, white noise, 2300 pixels, kernels of two shapes on either grid: Nside 2048, 240
+// arcmin 1.36-1.45e-7 / 1.21-1.29e-7 / 1.31-1.35e-7 / 1.42-1.55e-7; Nside 1024, 100 pixels of cut-off
+// 1.67-1.74e-7 / 1.25-1.31e-7 / 1.31-1.34e-7 / 1.70-1.86e-7.  32 terms take 0.5 % more time than 40.
+constexpr int kWideFlush = 10;
 
 // Whether every candidate of a row lies beyond the break of a biased grid (by
 // half a coarse node): its smallest separation, at m = 0, does.  Wave-uniform.
@@ -1070,6 +1070,7 @@ __device__ __forceinline__ WideSums gen_tile_wide(const DevPlanView &P, const fl
     float4 pa, pb, pc, pd;
     GenChunk ch{};
     auto load = [&](const GenChunk &c) {
+        if (64 * wave >= c.cn) return;   // (half of the waves stage nothing)
         pa = pb = pc = pd = make_float4(0.0f, 0.0f, 0.0f, 0.0f);   // rows past the chunk
         prefetch_chunk<0>(in, c, pa, pb, pc, pd);
     };
@@ -1092,9 +1093,11 @@ __device__ __forceinline__ WideSums gen_tile_wide(const DevPlanView &P, const fl
             stage[2 * kGenStage + threadIdx.x] = pc;
             stage[3 * kGenStage + threadIdx.x] = pd;
         }
-        const float z = (nan_unless_finite(pa) + nan_unless_finite(pb)) +
-                        (nan_unless_finite(pc) + nan_unless_finite(pd));
-        if (__any(z != 0.0f) && lane == 0) s_bad = k + 1;
+        if (64 * wave < ch.cn) {
+            const float z = (nan_unless_finite(pa) + nan_unless_finite(pb)) +
+                            (nan_unless_finite(pc) + nan_unless_finite(pd));
+            if (__any(z != 0.0f) && lane == 0) s_bad = k + 1;
+        }
         __syncthreads();
         if (s_bad == k + 1) {
             W.chunk = k;
